@@ -9,6 +9,8 @@
 #ifndef FLEXIQ_TEST_H
 #define FLEXIQ_TEST_H
 
+#include <stdint.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -67,6 +69,12 @@ int flexiq_debug_force_conv3(int mode, int rows_per_tile);
  * -1 = automatic (while flexiq_debug_force_conv3 is automatic too).  Returns the block shape (from 1) the last call it was offered
  * ran on, or 0. */
 int flexiq_debug_force_halo(int mode);
+
+/* The block shape that kernel would take for a convolution by its sizes alone (host arithmetic, no device needed; a shape forced by
+ * flexiq_debug_force_halo is the only one looked at): call = {B, H, W, stride, pad, N, C, R, bytes per output element, compute
+ * units}, with R x R filters.  Returns the shape (from 1) and fills plan = {output pixels of a block, its columns, pixel tiles,
+ * column blocks, bytes of LDS}, or 0: it does not qualify. */
+int flexiq_debug_halo_plan(const int64_t *call, int64_t *plan);
 
 /* The kernel that keeps the weights of a block in registers (linear calls of 288 to 1280 channels; last launch: tile shape index -6):
  * 1 = take it whenever the call reaches it and qualifies, 0 = never, -1 = automatic (what the kernels for few rows and short rounds leave).

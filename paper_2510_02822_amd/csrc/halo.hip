@@ -35,7 +35,7 @@ namespace halo {
 
 using namespace resident;
 
-// n / d for the small indices of this kernel: exact while n * d < 2^32 (checked by the launcher), m = ceil(2^32 / d)
+// n / d for the small indices of this kernel: exact while n * d < 2^32 (checked in choose()), m = ceil(2^32 / d)
 struct Div {
     uint32_t m, d;
 };
@@ -362,9 +362,88 @@ int prepare_halo_kernels(int device)
     return FLEXIQ_OK;
 }
 
+namespace halo {
+
+// What the choice of a block shape depends on: the sizes of a call and of its layer.
+struct Sizes {
+    int32_t B, H, W, stride, pad;
+    int32_t N, Npad, C, R, S;
+    int32_t out_bytes;   // per output element
+    int32_t num_cu;
+    bool linear;         // rows of a linear call: B = H = 1, W rows
+};
+struct Choice {
+    int shape = -1;      // of kPlans; -1: the call does not qualify
+    int64_t tiles = 0, ncb = 0, lds = 0;
+    double cost = 0;     // modelled cycles of the busiest compute unit
+    bool crowded = false;
+};
+
+// The block shape for a call (`only` >= 0: that one or none).  Host arithmetic only.
+static Choice choose(const Sizes &s, int only)
+{
+    Choice c;
+    const int taps = s.R * s.S;
+    if (!((s.R == 3 && s.S == 3) || taps == 1) || s.stride > 2) return c;
+    const int Ho = (s.H + 2 * s.pad - s.R) / s.stride + 1, Wo = (s.W + 2 * s.pad - s.S) / s.stride + 1;
+    const int64_t M = (int64_t)s.B * Ho * Wo;
+    const int st = taps == 1 ? 1 : s.stride;
+    const int64_t VH = (int64_t)(Ho - 1) * st + s.R;
+    const int Wv = (Wo - 1) * st + s.S, rowpx = st * ((Wv + st - 1) / st), pxb = s.C + 16;
+    int ppc = 64 / (s.C / 16);
+    if (st == 2) ppc &= ~1;
+    if (ppc < 1) return c;   // (more than 1024 channels; 512 for strided filters)
+    // the kernel's divisions: index times divisor below 2^32
+    if (!s.linear && (M * std::max(Wo, Ho) >= (1ll << 31) || (s.B + 1ll) * VH * VH >= (1ll << 31) || s.W > 4096)) return c;
+    if ((int64_t)s.H * s.W * s.C * (256 / ((int64_t)Ho * Wo) + 2) >= (1 << 30)) return c;   // the images under a tile: one 1 GiB window
+    auto image_rows = [&](int P) {   // LDS rows under P consecutive output pixels, wherever they begin
+        const int64_t nr = std::min<int64_t>((P + Wo - 2) / Wo + 1, (int64_t)s.B * Ho);
+        const int64_t cross = std::min<int64_t>((nr - 1 + Ho - 1) / Ho, s.B - 1);
+        return (nr - 1) * st + cross * (s.R - st) + s.R;
+    };
+    const int units = s.C / kUnit;
+    for (int i = 0; i < kNumPlans; ++i) {
+        const Plan &pl = kPlans[i];
+        if (only >= 0 && only != i) continue;
+        if (pl.wk > units) continue;
+        const int P = 32 * pl.fr * pl.wm, BN = 32 * pl.wn;
+        const int64_t ncb = (s.N + BN - 1) / BN, tiles = (M + P - 1) / P;
+        if (ncb * BN > s.Npad) continue;
+        const int64_t red = (int64_t)(pl.wk - 1) * pl.wm * pl.wn * pl.fr * 4096;
+        const int64_t rows = s.linear ? 1 : image_rows(P), lds = kTabBytes + std::max(rows * (s.linear ? P : rowpx) * pxb, red);
+        const int64_t cpr = s.linear ? (P + ppc - 1) / ppc : (Wv + ppc - 1) / ppc;
+        if (lds > 160 * 1024 || tiles * ncb > 0x3fffffff) continue;
+        if (tiles * ncb * 8 * ncb >= (1ll << 32)) continue;   // (the division of the block index)
+        // Modelled cycles of the busiest compute unit: per block the matrix instructions (or, for blocks of few pixels, the
+        // weight bytes), a price per wave (dispatch, set-up, epilogue) and per output byte; per round of co-resident blocks the
+        // copy of the input tile (per run of a wave) and a constant.  Fitted to 200 convolutions and 220 linear calls; the
+        // shape it picks is within 0.7 % resp. 1.5 % of the best (geometric mean; at worst 17 %), and 3 us + cost * 0.59 ns
+        // is the time of the call within about 10 %.
+        const int waves = pl.wm * pl.wn * pl.wk;
+        const int64_t blocks = tiles * ncb, per_cu = (blocks + s.num_cu - 1) / s.num_cu;
+        const int64_t fits = std::max<int64_t>(1, std::min<int64_t>({160 * 1024 / lds, 16 / waves, 8})), conc = std::min(fits, per_cu);
+        const double mfma = (double)taps * ((units + pl.wk - 1) / pl.wk) * waves * pl.fr * 8.0;
+        const double weights = (double)taps * units * 32.0 * BN * pl.wm;
+        const double body = std::max(mfma, 0.27 * mfma + 0.007 * weights) + 190.0 * waves + 0.1 * P * BN * s.out_bytes;
+        const double round = 200.0 + 370.0 * (double)(rows * cpr) / waves + (pl.wk > 1 ? 300.0 : 0.0);
+        const double cost = (double)per_cu * body + (double)((per_cu + conc - 1) / conc) * round;
+        if (c.shape < 0 || cost < c.cost) {
+            c.shape = i;
+            c.tiles = tiles;
+            c.ncb = ncb;
+            c.lds = lds;
+            c.cost = cost;
+            c.crowded = P == 32 && fits == 1 && ncb > 1 && per_cu > 2;
+        }
+    }
+    return c;
+}
+
+}  // namespace halo
+
 // Launches k_halo when the call qualifies; *taken: the shape of its blocks, from 1 (0: nothing was launched).
-// Qualifying: a 3x3 filter, or
-// a 1x1 filter that is not a plain linear call; plain outputs or int8 output lowered for a consumer; an input tile that fits LDS.
+// Qualifying: a 3x3 filter or a 1x1 filter that is not a plain linear call, stride 1 or 2; plain outputs or int8 output lowered
+// for a consumer; an input tile that fits LDS.
 static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, bool linear, const flexiq_out *out, void *stream_,
                       int *taken, const LowerArgs *lower)
 {
@@ -372,17 +451,29 @@ static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int 
     *taken = 0;
     g_last = 0;
     if (g_force == 0 || (g_force < 0 && conv3_forced())) return FLEXIQ_OK;   // (the 3x3 kernel's hook, in any forced state, keeps this one out of its comparisons)
-    const int taps = L->R * L->S;
-    if (!((L->R == 3 && L->S == 3) || taps == 1) || stride > 2) return FLEXIQ_OK;
     if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
     const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0;
     const bool lowering = lower && lower->ashift;   // (null positions: the consumer has no 4-bit channels at its ratio)
     if (lowering && !q_only) return FLEXIQ_OK;      // (the lowering build writes int8 only)
     const DeviceState &ds = g_dev[L->device];
     if (!ds.ready) return FLEXIQ_OK;
-    Params p = {};
+    const Sizes sizes = {B, H, W, stride, pad, L->N, L->Npad, L->C, L->R, L->S, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, linear};
+    const Choice c = choose(sizes, g_force > 0 ? g_force - 1 : -1);
+    if (c.shape < 0) return FLEXIQ_OK;
+    // A strided filter over many channels whose input tile fits LDS for no more than 32 output pixels: each of several column
+    // blocks copies nine input pixels per output pixel, one block at a time.  With several rounds of them the tiled kernel is
+    // ahead (stride 2, 352 -> 352 at 48 x 39 x 39: 41 us against 55; 512 -> 512 at 42 x 27 x 27: 40 against 44).
+    if (g_force < 0 && L->R * L->S != 1 && stride == 2 && c.crowded) return FLEXIQ_OK;
+    // Linear calls of more than one short round stay with the tiled kernel: its blocks keep several tiles' loads in flight, where
+    // a block here copies, multiplies and stores one after the other (us there and here: 1576 x 768 -> 3072 10.2 and 11.2; 6304 x
+    // 768 -> 3072 22.7 and 26.1; below the line, 1576 x 1024 -> 1024 8.7 and 7.2; 177 x 448 -> 1856 6.4 and 4.9; 1234 x 704 -> 128 7.2
+    // and 5.4: 11 % on average over 131 such calls, the worst 5 % behind).
+    if (linear && g_force < 0 && c.cost > 10000.0) return FLEXIQ_OK;
+    const Plan &pl = kPlans[c.shape];
+    const int P = 32 * pl.fr * pl.wm, taps = L->R * L->S, units = L->C / kUnit;
     const int Ho = (H + 2 * pad - L->R) / stride + 1, Wo = (W + 2 * pad - L->S) / stride + 1;
     const int64_t M = (int64_t)B * Ho * Wo;
+    Params p = {};
     p.st = taps == 1 ? 1 : stride;
     p.step = taps == 1 ? stride : 1;
     p.VH = (Ho - 1) * p.st + L->R;
@@ -393,66 +484,7 @@ static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int 
     p.pxb = L->C + 16;
     p.ppc = 64 / (L->C / 16);
     if (p.st == 2) p.ppc &= ~1;
-    if (p.ppc < 1) return FLEXIQ_OK;   // (more than 1024 channels; 512 for strided filters)
     p.cpr = (p.Wv + p.ppc - 1) / p.ppc;
-    // the kernel's divisions: index times divisor below 2^32
-    if (!linear && (M * std::max(Wo, Ho) >= (1ll << 31) || (int64_t)(B + 1) * p.VH * p.VH >= (1ll << 31) || W > 4096)) return FLEXIQ_OK;
-    if ((int64_t)H * W * L->C * (256 / ((int64_t)Ho * Wo) + 2) >= (1 << 30)) return FLEXIQ_OK;   // the images under a tile: one 1 GiB window
-    // ---- shape of a block
-    auto image_rows = [&](int P) {   // LDS rows under P consecutive output pixels, wherever they begin
-        const int64_t nr = std::min<int64_t>((P + Wo - 2) / Wo + 1, (int64_t)B * Ho);
-        const int64_t cross = std::min<int64_t>((nr - 1 + Ho - 1) / Ho, B - 1);
-        return (nr - 1) * p.st + cross * (L->R - p.st) + L->R;
-    };
-    int best = -1;
-    double best_cost = 0;
-    int64_t best_lds = 0;
-    bool crowded = false;
-    const int units = L->C / kUnit;
-    const int out_bytes = (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0);
-    for (int i = 0; i < kNumPlans; ++i) {
-        const Plan &pl = kPlans[i];
-        if (g_force > 0 && g_force - 1 != i) continue;
-        if (pl.wk > units) continue;
-        const int P = 32 * pl.fr * pl.wm, BN = 32 * pl.wn;
-        const int64_t ncb = (L->N + BN - 1) / BN, tiles = (M + P - 1) / P;
-        if (ncb * BN > L->Npad) continue;
-        const int64_t red = (int64_t)(pl.wk - 1) * pl.wm * pl.wn * pl.fr * 4096;
-        const int64_t rows = linear ? 1 : image_rows(P), lds = kTabBytes + std::max(rows * (linear ? P : p.rowpx) * p.pxb, red);
-        const int64_t cpr = linear ? (P + p.ppc - 1) / p.ppc : p.cpr;
-        if (lds > 160 * 1024 || tiles * ncb > 0x3fffffff) continue;
-        // Modelled cycles of the busiest compute unit: per block the matrix instructions (or, for blocks of few pixels, the
-        // weight bytes), a price per wave (dispatch, set-up, epilogue) and per output byte; per round of co-resident blocks the
-        // copy of the input tile (per run of a wave) and a constant.  Fitted to 200 convolutions and 220 linear calls; the
-        // shape it picks is within 0.7 % resp. 1.5 % of the best (geometric mean; at worst 17 %), and 3 us + cost * 0.59 ns
-        // is the time of the call within about 10 %.
-        const int waves = pl.wm * pl.wn * pl.wk;
-        const int64_t blocks = tiles * ncb, per_cu = (blocks + ds.num_cu - 1) / ds.num_cu;
-        const int64_t fits = std::max<int64_t>(1, std::min<int64_t>({160 * 1024 / lds, 16 / waves, 8})), conc = std::min(fits, per_cu);
-        const double mfma = (double)taps * ((units + pl.wk - 1) / pl.wk) * waves * pl.fr * 8.0;
-        const double weights = (double)taps * units * 32.0 * BN * pl.wm;
-        const double body = std::max(mfma, 0.27 * mfma + 0.007 * weights) + 190.0 * waves + 0.1 * P * BN * out_bytes;
-        const double round = 200.0 + 370.0 * (double)(rows * cpr) / waves + (pl.wk > 1 ? 300.0 : 0.0);
-        const double cost = (double)per_cu * body + (double)((per_cu + conc - 1) / conc) * round;
-        if (best < 0 || cost < best_cost) {
-            best = i;
-            best_cost = cost;
-            best_lds = lds;
-            crowded = P == 32 && fits == 1 && ncb > 1 && per_cu > 2;
-        }
-    }
-    if (best < 0) return FLEXIQ_OK;
-    // A strided filter over many channels whose input tile fits LDS for no more than 32 output pixels: each of several column
-    // blocks copies nine input pixels per output pixel, one block at a time.  With several rounds of them the tiled kernel is
-    // ahead (stride 2, 352 -> 352 at 48 x 39 x 39: 41 us against 55; 512 -> 512 at 42 x 27 x 27: 40 against 44).
-    if (g_force < 0 && p.st == 2 && crowded) return FLEXIQ_OK;
-    // Linear calls of more than one short round stay with the tiled kernel: its blocks keep several tiles' loads in flight, where
-    // a block here copies, multiplies and stores one after the other (us there and here: 1576 x 768 -> 3072 10.2 and 11.2; 6304 x
-    // 768 -> 3072 22.7 and 26.1; below the line, 1576 x 1024 -> 1024 8.7 and 7.2; 177 x 448 -> 1856 6.4 and 4.9; 1234 x 704 -> 128 7.2
-    // and 5.4: 11 % on average over 131 such calls, the worst 5 % behind).
-    if (linear && g_force < 0 && best_cost > 10000.0) return FLEXIQ_OK;
-    const Plan &pl = kPlans[best];
-    const int P = 32 * pl.fr * pl.wm, BN = 32 * pl.wn;
     p.X = X; p.W8 = L->d_w8; p.ashift = L->dynamic ? L->d_ashift_dyn : L->d_ashift; p.cs = L->d_cs;
     p.acc = out->acc; p.y = out->y; p.q = out->q;
     p.r_out = out->q ? 1.0f / out->out_scale : 1.0f;
@@ -472,15 +504,15 @@ static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int 
     p.pad = pad;
     auto div = [](int d) { return Div{d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d), (uint32_t)d}; };
     p.dWo = div(p.Wo); p.dHo = div(p.Ho); p.dVH = div(p.VH); p.dCpr = div(p.cpr); p.dPiece = div(L->C / 16);
-    p.ncb = (L->N + BN - 1) / BN;
-    p.tiles = (int)((M + P - 1) / P);
+    p.ncb = (int)c.ncb;
+    p.tiles = (int)c.tiles;
     p.wn_log2 = __builtin_ctz(pl.wn); p.wmn_log2 = __builtin_ctz(pl.wm * pl.wn); p.wk = pl.wk;
     p.dBand = div(8 * p.ncb); p.dTail = div(p.tiles % 8 ? p.tiles % 8 : 1);
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
-    hipLaunchKernelGGL(kernel(pl.fr, taps, q_only, lowering), dim3((unsigned)(p.tiles * p.ncb)), dim3(64 * pl.wm * pl.wn * pl.wk), (size_t)best_lds, (hipStream_t)stream_, p);
+    hipLaunchKernelGGL(kernel(pl.fr, taps, q_only, lowering), dim3((unsigned)(p.tiles * p.ncb)), dim3(64 * pl.wm * pl.wn * pl.wk), (size_t)c.lds, (hipStream_t)stream_, p);
     FLEXIQ_HIP(hipGetLastError());
-    *taken = 1 + best;
-    g_last = 1 + best;
+    *taken = 1 + c.shape;
+    g_last = 1 + c.shape;
     return FLEXIQ_OK;
 }
 
@@ -513,4 +545,25 @@ extern "C" int flexiq_debug_force_halo(int mode)
     if (mode < -1 || mode > flexiq::halo::kNumPlans) return FLEXIQ_EINVAL;
     flexiq::halo::g_force = mode;
     return flexiq::halo::g_last;
+}
+
+extern "C" int flexiq_debug_halo_plan(const int64_t *call, int64_t *plan)
+{
+    using namespace flexiq::halo;
+    if (!call || !plan) return FLEXIQ_EINVAL;
+    const int64_t N = call[5], C = call[6], R = call[7];
+    for (int i = 0; i < 10; ++i)
+        if (call[i] < (i == 4 || i == 8 ? 0 : 1) || call[i] > 0x7fffffff) return FLEXIQ_EINVAL;
+    if (C % flexiq::kUnit || C > (1 << 20) || N > (1 << 24) || call[1] > (1 << 20) || call[2] > (1 << 20) || call[4] > (1 << 10) || std::min(call[1], call[2]) + 2 * call[4] < R)
+        return FLEXIQ_EINVAL;
+    const Sizes sizes = {(int32_t)call[0], (int32_t)call[1], (int32_t)call[2], (int32_t)call[3], (int32_t)call[4], (int32_t)N, (int32_t)((N + 255) & ~255ll),
+                         (int32_t)C, (int32_t)R, (int32_t)R, (int32_t)call[8], (int32_t)call[9], false};
+    const Choice c = choose(sizes, g_force > 0 ? g_force - 1 : -1);
+    if (c.shape < 0) return 0;
+    plan[0] = 32 * kPlans[c.shape].fr * kPlans[c.shape].wm;
+    plan[1] = 32 * kPlans[c.shape].wn;
+    plan[2] = c.tiles;
+    plan[3] = c.ncb;
+    plan[4] = c.lds;
+    return 1 + c.shape;
 }
