@@ -393,6 +393,7 @@ static Choice choose(const Sizes &s, int only)
     int ppc = 64 / (s.C / 16);
     if (st == 2) ppc &= ~1;
     if (ppc < 1) return c;   // (more than 1024 channels; 512 for strided filters)
+    if (M > 0x7fffffff - 512) return c;   // (row indices are 32-bit: a tile may begin at the last row; such calls are refused further on)
     // the kernel's divisions: index times divisor below 2^32
     if (!s.linear && (M * std::max(Wo, Ho) >= (1ll << 31) || (s.B + 1ll) * VH * VH >= (1ll << 31) || s.W > 4096)) return c;
     if ((int64_t)s.H * s.W * s.C * (256 / ((int64_t)Ho * Wo) + 2) >= (1 << 30)) return c;   // the images under a tile: one 1 GiB window

@@ -647,6 +647,8 @@ def test_launch_limits_are_refused_without_a_launch(env):
     assert lib.flexiq_mixed_conv_implicit(hl._h, x.data_ptr(), 1, 4, 4, 0, 1, C.byref(o), None) == -1     # stride 0
     assert lib.flexiq_mixed_conv_implicit(hl._h, x.data_ptr(), 1, 1, 1, 1, 0, C.byref(o), None) == -1     # filter larger than image
     assert lib.flexiq_mixed_gemm(hl._h, x.data_ptr(), 4, C.byref(o), None) == -1                          # not a linear layer
+    down = both_layers(workloads.make_conv("limits_1x1", 7, 142, 1, 4, 4, 32, 16, 1, 1, 2, 0, 32))[1]
+    assert lib.flexiq_mixed_conv_implicit(down._h, x.data_ptr(), (1 << 31) - 200, 1, 1, 2, 0, C.byref(o), None) == -1   # 32-bit row indices
     lin = both_layers(workloads.make_linear("limits_lin", 8, 141, 4, 64, 16, 32))[1]
     assert lib.flexiq_mixed_gemm(lin._h, x.data_ptr(), (1 << 31) - 512, C.byref(o), None) == -1           # 32-bit row indices
     assert lib.flexiq_mixed_gemm(lin._h, x.data_ptr() + 4, 4, C.byref(o), None) == -2                     # alignment

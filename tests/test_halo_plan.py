@@ -39,6 +39,8 @@ def _lds_bytes(P, B, H, W, stride, pad, ch, R):
 
 
 @pytest.mark.parametrize("call", [
+    (2 ** 31 - 200, 1, 1, 2, 0, 16, 32, 1),         # row indices beyond what any kernel takes
+    (2 ** 31 - 500, 1, 1, 2, 0, 256, 64, 1),
     (12000, 60, 60, 2, 0, 16384, 32, 1),            # many column blocks times many tiles: the block index divided by 8 per column block
     (300000, 7, 7, 1, 1, 8192, 32, 3)])
 def test_beyond_the_index_arithmetic(plan, call):
