@@ -27,9 +27,9 @@ int flexiq_debug_force_packed4(int mode);
  * 0 = automatic (one resident wave of blocks; the default), n > 0 = at most n blocks, n < 0 = one block per tile. */
 int flexiq_debug_max_blocks(int n);
 
-/* What the last GEMM / convolution launch used.  which = 0: tile shape index (below 0: another kernel, from the table's size on: a
- * block shape of flexiq_debug_force_halo), 1: blocks launched,
- * 2: blocks of that kernel resident per compute unit. */
+/* What the last GEMM / convolution launch used.  which = 0: tile shape index of the tiled kernel; below 0: another kernel (-2 row-
+ * streaming, -3 3x3 with resident weights, -4 few rows, -5 tile per block, -6 weights in registers); from the table's size on: the
+ * kernel of flexiq_debug_force_halo.  1: blocks launched, 2: blocks of that kernel resident per compute unit (0 for the others). */
 int flexiq_debug_last_launch(int which);
 
 /* The few-row kernels (linear calls with at most 64 rows; last launch: tile shape index -4): 1 = the matrix-core kernel
@@ -57,14 +57,14 @@ int flexiq_debug_force_tile_splitk(int mode);
 int flexiq_debug_force_stream(int mode);
 
 /* The 3x3 convolution kernel with resident weights for 64 or 128 input channels, stride 1, padding 1 (last launch: tile shape
- * index -3, as for every 3x3 filter at stride 1 that leaves the tiled kernel):
+ * index -3):
  * mode 1 = take it whenever the layer form qualifies (whatever the tile count), 0 = never, -1 = automatic;
  * rows_per_tile > 0 forces the output rows of an image tile (0 = automatic).  Returns whether the last convolution call
  * ran on it. */
 int flexiq_debug_force_conv3(int mode, int rows_per_tile);
 
 /* The convolution kernel that keeps the input tile in LDS and streams the weights past it (3x3 filters, strided or padded 1x1
- * filters; last launch: tile shape index -3 for 3x3 filters at stride 1, else the number of tiled shapes plus its block shape):
+ * filters, at strides 1 and 2; last launch: the number of tiled shapes plus its block shape, counted from 0):
  * mode k >= 1 = take it with the k-th block shape of its table whenever the call qualifies and that shape fits, 0 = never,
  * -1 = automatic (while flexiq_debug_force_conv3 is automatic too).  Returns the block shape (from 1) the last call it was offered
  * ran on, or 0. */

@@ -62,7 +62,7 @@ def test_conv3_forced(env, B, H, W, C, N, gs, rows):
             # the tiled kernel gives the same bytes
             fq.debug_force_conv3(0, 0)
             tiled = fq.flexiq_mixed_conv_implicit(hl, Xd, 1, 1, q=True, out_scale=so)["q"]
-            assert fq.debug_last_launch()["tile"] >= 0
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
             fq.debug_force_conv3(1, rows)
             assert (tiled.cpu().numpy() == got_q).all(), r
     finally:
@@ -109,9 +109,10 @@ def test_conv3_blocks_walk_many_tiles_and_buffers(env):
 
 
 def test_conv3_automatic_route(env):
-    """A stage-1-like layer at a batch that fills the chip takes this kernel by itself; strided, padded-differently and
-    wide-channel layers do not."""
+    """A stage-1-like layer whose batch gives every compute unit a block or two goes to the kernel with a resident input tile
+    instead, strided or not."""
     torch, oracle, fq, dev = env
+    n_tiled = fq.debug_force_tile(-1)
     case = workloads.make_conv("c3auto", 13, 3, 100, 28, 28, 64, 64, 3, 3, 1, 1, 32)
     ol, hl, x_scale = both_layers(case)
     Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[..., ol.perm])
@@ -120,11 +121,11 @@ def test_conv3_automatic_route(env):
     ref = oracle.forward_conv(ol, Xq, 1, 1, 0.5)
     so = float(np.abs(oracle.dequant_f64(ref, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9)
     got = fq.flexiq_mixed_conv_implicit(hl, Xd, 1, 1, q=True, out_scale=so)["q"].cpu().numpy()
-    assert fq.debug_last_launch()["tile"] == -3
+    assert fq.debug_last_launch()["tile"] >= n_tiled and fq.debug_force_conv3(-1, 0) == 0 and fq.debug_force_halo(-1) > 0
     check_q(got, ref, ol, so)
     assert (got == requant_fp32_sequence(ref, ol, so)).all()
-    got = fq.flexiq_mixed_conv_implicit(hl, Xd, 2, 1, acc=True)["acc"].cpu().numpy()   # stride 2: the tiled kernel
-    assert fq.debug_last_launch()["tile"] >= 0
+    got = fq.flexiq_mixed_conv_implicit(hl, Xd, 2, 1, acc=True)["acc"].cpu().numpy()   # stride 2
+    assert fq.debug_last_launch()["tile"] >= n_tiled and fq.debug_force_conv3(-1, 0) == 0
     assert (got == oracle.forward_conv(ol, Xq, 2, 1, 0.5)).all()
 
 
@@ -165,7 +166,7 @@ def test_conv3_lowers_for_consumer(env, B, H, W, C, N1, gs2, rows):
             assert (low.cpu().numpy().astype(np.int32) == want).all(), r2
             fq.debug_force_conv3(0, 0)
             tiled = fq.flexiq_mixed_conv_implicit(h1, X1d, 1, 1, q=True, out_scale=s_mid, lower_for=h2)["q"]
-            assert fq.debug_last_launch()["tile"] >= 0
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
             assert (tiled.cpu().numpy() == low.cpu().numpy()).all(), r2
             fq.flexiq_input_prelowered(h2, True)
             got = fq.flexiq_mixed_conv_implicit(h2, low, 1, 0, acc=True)["acc"].cpu().numpy()

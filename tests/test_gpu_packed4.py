@@ -240,7 +240,7 @@ def test_few_row_dot_kernel_reads_packed_codes(env, K, N, gs):
         fq.flexiq_set_ratio(hl, 1.0)
         Xd = _dev(torch, np.ascontiguousarray(np.repeat(Xq, 3, axis=0)), dev)
         out = fq.flexiq_mixed_gemm_packed4(hl, Xd, fq.flexiq_lower_packed4(hl, Xd), acc=True)
-        assert fq.debug_last_launch()["tile"] >= 0
+        assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
         assert (out["acc"].cpu().numpy() == np.repeat(oracle.forward_gemm(ol, Xq, 1.0), 3, axis=0)).all()
     finally:
         fq.debug_force_few_rows(-1)

@@ -165,7 +165,7 @@ def test_tile_splitk_kernel(env, M, K, N, gs, shape):
             assert (got_q == requant_fp32_sequence(ref, ol, so)).all()
             fq.debug_force_tile_splitk(0)
             tiled = fq.flexiq_mixed_gemm(hl, Xd, q=True, out_scale=so)["q"]       # the tiled kernel gives the same bytes
-            assert fq.debug_last_launch()["tile"] >= 0 or fq.debug_last_launch()["tile"] == -2
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1) or fq.debug_last_launch()["tile"] == -2
             fq.debug_force_tile_splitk(shape)
             assert (tiled.cpu().numpy() == got_q).all(), r
         # activations that arrive lowered

@@ -56,7 +56,7 @@ def test_linear_forced(env, M, K, N, gs, kernel):
             fq.debug_force_stream(0)
             fq.debug_force_few_rows(0)
             tiled = fq.flexiq_mixed_gemm(hl, Xd, q=True, out_scale=so)["q"]
-            assert fq.debug_last_launch()["tile"] >= 0
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
             fq.debug_force_few_rows(-1)
             fq.debug_force_stream(kernel)
             assert (tiled.cpu().numpy() == got_q).all(), r
@@ -206,7 +206,7 @@ def test_producer_lowers_for_consumer(env, M, K1, N1, N2, gs2, kernel):
             assert (low.cpu().numpy().astype(np.int32) == want).all(), r2
             fq.debug_force_stream(0)
             tiled = fq.flexiq_mixed_gemm(h1, Xd, q=True, out_scale=s_mid, lower_for=h2)["q"]       # the tiled kernel lowers alike
-            assert fq.debug_last_launch()["tile"] >= 0
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
             assert (tiled.cpu().numpy() == low.cpu().numpy()).all(), r2
             fq.flexiq_input_prelowered(h2, True)
             got = fq.flexiq_mixed_gemm(h2, low, acc=True)["acc"].cpu().numpy()
@@ -215,7 +215,7 @@ def test_producer_lowers_for_consumer(env, M, K1, N1, N2, gs2, kernel):
             assert (got == oracle.forward_gemm(o2, X2, r2)).all(), r2
         # an output that is not int8 alone next to lower_for is served by the tiled kernel, with the same int8 rows
         both = fq.flexiq_mixed_gemm(h1, Xd, acc=True, q=True, out_scale=s_mid, lower_for=h2)
-        assert fq.debug_last_launch()["tile"] >= 0
+        assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
         assert (both["q"].cpu().numpy() == low.cpu().numpy()).all() and (both["acc"].cpu().numpy() == acc1[:, o2.perm]).all()
     finally:
         fq.debug_force_stream(-1)
