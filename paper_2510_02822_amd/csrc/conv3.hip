@@ -319,6 +319,7 @@ static int g_last = 0;
 }  // namespace conv3
 
 bool conv3_forced() { return conv3::g_force >= 0; }
+void conv3_not_taken() { conv3::g_last = 0; }
 
 int prepare_conv3_kernels(int device)
 {
@@ -335,34 +336,29 @@ int prepare_conv3_kernels(int device)
     return FLEXIQ_OK;
 }
 
-// Launches the 3x3 kernel when the call qualifies; *taken says whether it did (0: nothing was launched).  Qualifying: a 3x3
-// filter, stride 1, padding 1, 64 or 128 input channels, plain outputs or int8 output lowered for a consumer (`lower`:
-// flexiq_out.lower_for, checked by the caller; no consumer to scan for), an image whose
-// tile of at least one output row fits a 40 KB buffer, and enough tiles to occupy the chip.
-int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream_,
-                 int *taken, const LowerArgs *lower)
+// The tile rows of a call that qualifies: a 3x3 filter, stride 1, padding 1, 64 or 128 input channels, plain outputs or int8
+// output lowered for a consumer (`lower`: flexiq_out.lower_for, checked by the caller; no consumer to scan for), an image whose
+// tile of at least one output row fits a 40 KB buffer.
+Conv3Choice conv3_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower)
 {
     using namespace conv3;
-    *taken = 0;
-    g_last = 0;
-    if (g_force == 0) return FLEXIQ_OK;
-    if (L->R != 3 || L->S != 3 || stride != 1 || pad != 1 || (L->C != 64 && L->C != 128)) return FLEXIQ_OK;
-    if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
-    const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0;
-    const bool lowering = lower && lower->ashift;   // (null positions: the consumer has no 4-bit channels at its ratio)
-    if (lowering && !q_only) return FLEXIQ_OK;   // (the lowering build writes int8 only)
+    Conv3Choice c;
+    if (g_force == 0) return c;
+    if (L->R != 3 || L->S != 3 || stride != 1 || pad != 1 || (L->C != 64 && L->C != 128)) return c;
+    if (out->scan_for || out->x4 || out->x6) return c;
+    if (lower && lower->ashift && !(out->q && !out->acc && !out->y && (L->N & 15) == 0)) return c;   // (the lowering build writes int8 only)
     const DeviceState &ds = g_dev[L->device];
-    if (!ds.ready) return FLEXIQ_OK;
-    if ((int64_t)H * W * L->C >= (1 << 29) || W > 1024) return FLEXIQ_OK;
+    if (!ds.ready) return c;
+    if ((int64_t)H * W * L->C >= (1 << 29) || W > 1024) return c;
     const int units = L->C / kUnit;
     const int wbytes = 9 * units * 2 * (kCols + 2) * 16 + 3 * kCols * 4;
     const int gy = (L->N + kCols - 1) / kCols;
     // output rows per tile: every choice whose buffer fits 40 KB, whose pixels fit sixteen fragments and of which two
     // buffers fit next to the weights; the one with the least estimated time of the busiest compute unit (matrix
     // instructions of its fragments per SIMD, plus a fixed cost per tile)
-    int best_tr = 0, best_nbuf = 0;
     double best_cost = 0;
     const int blocks = std::max(1, ds.num_cu / gy);
+    const int out_bytes = (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0);
     for (int tr = 1; tr <= H; ++tr) {
         if (g_rows > 0 && tr != g_rows) continue;
         const int npix = (tr + 2) * (W + 2);
@@ -373,21 +369,31 @@ int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, in
         if (nbuf < 2) break;
         const int64_t tiles = (int64_t)B * ((H + tr - 1) / tr);
         const int64_t rounds = (tiles + blocks - 1) / blocks;
-        const double cost = (double)rounds * ((frags > kWaves ? 2 : 1) * 2.0 * units * 18 * 32 + 700.0);
-        if (best_tr == 0 || cost < best_cost) {
-            best_tr = tr;
-            best_nbuf = nbuf;
+        const double matrix = (frags > kWaves ? 2 : 1) * 2.0 * units * 18 * 32;
+        const double cost = (double)rounds * (matrix + 700.0);
+        if (c.rows == 0 || cost < best_cost) {
+            c.rows = tr;
+            c.buffers = nbuf;
             best_cost = cost;
+            // the time of the call, for the choice between kernels (gemm.hip, which says how well it is met): weights and first tile,
+            // then per tile of a block its matrix instructions, copies and lowering, and the output
+            const double lowered = L->x_prelowered ? 0.0 : (double)L->max_4bit_ch / (double)L->C;
+            c.us = 9.4 + (double)rounds * (0.556e-3 * matrix + (0.0164 + 0.0177 * lowered) * copies) + 0.148e-6 * (double)B * H * W * L->N * out_bytes;
         }
     }
-    if (best_tr == 0) return FLEXIQ_OK;
-    const int64_t tiles = (int64_t)B * ((H + best_tr - 1) / best_tr);
-    if (tiles > 0x7fffffff) return FLEXIQ_OK;
-    // The kernel that keeps the input tile instead (halo.hip) starts faster and reads its operands with less waiting: it is ahead
-    // everywhere (batch 128, us at r = 0 / 0.5 / 1 here and there: 64 -> 64 @28x28 (100 images) 11.7 / 11.9 / 12.0 and 7.3 / 7.4 / 7.4;
-    // 128 -> 128 @28x28 24.2 / 24.8 / 25.7 and 21.2 / 20.6 / 20.0; 64 -> 64 @56x56 26.8 / 25.9 / 27.2 and 25.2 / 25.2 / 24.6) but for narrow
-    // layers with very many pixels whose activations arrive lowered (64 -> 64 @56x56: 23.3 and 25.5 us; at half that batch 16.9 and 14.2).
-    if (g_force < 0 && !(L->C == 64 && gy == 1 && L->x_prelowered && (int64_t)B * H * W >= 1200 * (int64_t)ds.num_cu)) return FLEXIQ_OK;
+    if (c.rows > 0 && (int64_t)B * ((H + c.rows - 1) / c.rows) > 0x7fffffff) c.rows = 0;
+    return c;
+}
+
+int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, const flexiq_out *out, void *stream_, const Conv3Choice &c,
+                 const LowerArgs *lower)
+{
+    using namespace conv3;
+    const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0, lowering = lower && lower->ashift;
+    const DeviceState &ds = g_dev[L->device];
+    const int units = L->C / kUnit, gy = (L->N + kCols - 1) / kCols;
+    const int wbytes = 9 * units * 2 * (kCols + 2) * 16 + 3 * kCols * 4;
+    const int64_t tiles = (int64_t)B * ((H + c.rows - 1) / c.rows);
     Params p = {};
     p.X = X; p.W8 = L->d_w8; p.ashift = L->dynamic ? L->d_ashift_dyn : L->d_ashift; p.cs = L->d_cs;
     p.acc = out->acc; p.y = out->y; p.q = out->q;
@@ -397,12 +403,12 @@ int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, in
     p.units4 = L->max_4bit_ch / kUnit;
     p.x_pre = L->x_prelowered ? 1 : 0;
     p.gs_shift = L->group_size == 64 ? 1 : 0;
-    p.TR = best_tr;
-    p.tiles_per_img = (H + best_tr - 1) / best_tr;
+    p.TR = c.rows;
+    p.tiles_per_img = (H + c.rows - 1) / c.rows;
     p.tiles = (int)tiles;
-    p.npix = (best_tr + 2) * (W + 2);
+    p.npix = (c.rows + 2) * (W + 2);
     p.copies = (p.npix * L->C + 1023) / 1024;
-    p.nbuf = best_nbuf;
+    p.nbuf = c.buffers;
     const size_t lds = (size_t)wbytes + (size_t)p.nbuf * p.copies * 1024;
     int64_t gx64 = std::max<int64_t>(1, std::min<int64_t>(tiles, ds.num_cu / gy));
     if (gy > 1 && gx64 >= 8) gx64 &= ~(int64_t)7;   // the column blocks of a tile share an XCD and its L2
@@ -411,7 +417,6 @@ int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, in
     if (lowering) fn = units == 2 ? k_conv3<2, true, true> : k_conv3<4, true, true>;
     hipLaunchKernelGGL(fn, dim3((unsigned)gx64, (unsigned)gy), dim3(64 * (kWaves + 1)), lds, (hipStream_t)stream_, p);
     FLEXIQ_HIP(hipGetLastError());
-    *taken = 1;
     g_last = 1;
     return FLEXIQ_OK;
 }

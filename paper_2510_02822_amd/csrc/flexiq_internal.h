@@ -98,18 +98,34 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
 int launch_stream(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, bool rows_contiguous, int *taken,
                   const uint8_t *X4 = nullptr, const LowerArgs *lower = nullptr);
 // (conv3.hip) 3x3 convolutions, stride 1, padding 1, with 64 or 128 input channels: weights of all taps resident in LDS,
-// image tiles streamed past them; *taken = 0: the call does not qualify
-int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream, int *taken,
-                 const LowerArgs *lower = nullptr);
-// test hooks that are not in the automatic state (conv3.hip, smallm.hip, stream.hip, halo.hip)
+// image tiles streamed past them.  rows = 0: the call does not qualify, else the output rows of a tile; us: its modelled time
+struct Conv3Choice {
+    int rows = 0, buffers = 0;
+    double us = 0;
+};
+Conv3Choice conv3_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower);
+int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, const flexiq_out *out, void *stream, const Conv3Choice &c,
+                 const LowerArgs *lower);
+// test hooks that are not in the automatic state (conv3.hip, smallm.hip, stream.hip, halo.hip), and what they report for calls that
+// are not offered to their kernel
 bool conv3_forced();
 bool few_rows_forced();
 bool stream_forced();
-bool halo_rows_forced();
-// (halo.hip) 3x3 convolutions and strided or padded 1x1 ones: the input tile resident in LDS, weights streamed past it;
-// *taken = 0: the call does not qualify, else the shape of its blocks, from 1
-int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream, int *taken,
-                const LowerArgs *lower = nullptr);
+bool halo_forced();
+void conv3_not_taken();
+void stream_not_taken();
+// (halo.hip) 3x3 convolutions and strided or padded 1x1 ones: the input tile resident in LDS, weights streamed past it.
+// shape < 0: the call does not qualify; cost: modelled cycles of the busiest compute unit, us: modelled time of the call; one_round:
+// every block is resident from the start
+struct HaloChoice {
+    int shape = -1;
+    int64_t tiles = 0, ncb = 0, lds = 0;
+    double cost = 0, us = 0;
+    bool one_round = false;
+};
+HaloChoice halo_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower);
+int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream,
+                const HaloChoice &c, const LowerArgs *lower);
 int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken,
                      const LowerArgs *lower = nullptr);
 // (wreg.hip) linear calls of 288 to 1280 channels: the weights of a block resident in registers, row tiles streamed

@@ -372,17 +372,11 @@ struct Sizes {
     int32_t num_cu;
     bool linear;         // rows of a linear call: B = H = 1, W rows
 };
-struct Choice {
-    int shape = -1;      // of kPlans; -1: the call does not qualify
-    int64_t tiles = 0, ncb = 0, lds = 0;
-    double cost = 0;     // modelled cycles of the busiest compute unit
-    bool crowded = false;
-};
 
 // The block shape for a call (`only` >= 0: that one or none).  Host arithmetic only.
-static Choice choose(const Sizes &s, int only)
+static HaloChoice choose(const Sizes &s, int only)
 {
-    Choice c;
+    HaloChoice c;
     const int taps = s.R * s.S;
     if (!((s.R == 3 && s.S == 3) || taps == 1) || s.stride > 2) return c;
     const int Ho = (s.H + 2 * s.pad - s.R) / s.stride + 1, Wo = (s.W + 2 * s.pad - s.S) / s.stride + 1;
@@ -434,7 +428,13 @@ static Choice choose(const Sizes &s, int only)
             c.ncb = ncb;
             c.lds = lds;
             c.cost = cost;
-            c.crowded = P == 32 && fits == 1 && ncb > 1 && per_cu > 2;
+            // The time of the call, for the choice between kernels (gemm.hip, which says how well it is met): the parts of the same
+            // sum at their own rates, and where several blocks share a compute unit its last round counts by half.
+            const double even = conc == 1 ? (double)per_cu : std::max((double)conc, 0.5 * (per_cu + (double)blocks / s.num_cu));
+            const double rounds = conc == 1 ? (double)per_cu : std::max(1.0, 0.5 * ((per_cu + conc - 1) / conc + (double)blocks / s.num_cu / conc));
+            c.one_round = per_cu <= conc;
+            c.us = 3.3 + 1e-3 * (even * (0.78 * std::max(mfma, 0.27 * mfma + 0.007 * weights) + 0.57 * 190.0 * waves + 0.42 * 0.1 * P * BN * s.out_bytes) +
+                                 (taps == 1 ? 0.65 : 0.48) * rounds * 370.0 * (double)(rows * cpr) / waves);
         }
     }
     return c;
@@ -442,34 +442,28 @@ static Choice choose(const Sizes &s, int only)
 
 }  // namespace halo
 
-// Launches k_halo when the call qualifies; *taken: the shape of its blocks, from 1 (0: nothing was launched).
-// Qualifying: a 3x3 filter or a 1x1 filter that is not a plain linear call, stride 1 or 2; plain outputs or int8 output lowered
-// for a consumer; an input tile that fits LDS.
-static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, bool linear, const flexiq_out *out, void *stream_,
-                      int *taken, const LowerArgs *lower)
+// The shape of a call that qualifies: a 3x3 filter or a 1x1 filter that is not a plain linear call, stride 1 or 2; plain outputs or
+// int8 output lowered for a consumer; an input tile that fits LDS.
+static HaloChoice choice_any(const flexiq_layer *L, int B, int H, int W, int stride, int pad, bool linear, const flexiq_out *out, const LowerArgs *lower)
 {
     using namespace halo;
-    *taken = 0;
     g_last = 0;
-    if (g_force == 0 || (g_force < 0 && conv3_forced())) return FLEXIQ_OK;   // (the 3x3 kernel's hook, in any forced state, keeps this one out of its comparisons)
-    if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
+    if (g_force == 0 || (g_force < 0 && conv3_forced())) return HaloChoice();   // (the 3x3 kernel's hook, in any forced state, keeps this one out of its comparisons)
+    if (out->scan_for || out->x4 || out->x6) return HaloChoice();
     const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0;
     const bool lowering = lower && lower->ashift;   // (null positions: the consumer has no 4-bit channels at its ratio)
-    if (lowering && !q_only) return FLEXIQ_OK;      // (the lowering build writes int8 only)
+    if (lowering && !q_only) return HaloChoice();   // (the lowering build writes int8 only)
     const DeviceState &ds = g_dev[L->device];
-    if (!ds.ready) return FLEXIQ_OK;
+    if (!ds.ready) return HaloChoice();
     const Sizes sizes = {B, H, W, stride, pad, L->N, L->Npad, L->C, L->R, L->S, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, linear};
-    const Choice c = choose(sizes, g_force > 0 ? g_force - 1 : -1);
-    if (c.shape < 0) return FLEXIQ_OK;
-    // A strided filter over many channels whose input tile fits LDS for no more than 32 output pixels: each of several column
-    // blocks copies nine input pixels per output pixel, one block at a time.  With several rounds of them the tiled kernel is
-    // ahead (stride 2, 352 -> 352 at 48 x 39 x 39: 41 us against 55; 512 -> 512 at 42 x 27 x 27: 40 against 44).
-    if (g_force < 0 && L->R * L->S != 1 && stride == 2 && c.crowded) return FLEXIQ_OK;
-    // Linear calls of more than one short round stay with the tiled kernel: its blocks keep several tiles' loads in flight, where
-    // a block here copies, multiplies and stores one after the other (us there and here: 1576 x 768 -> 3072 10.2 and 11.2; 6304 x
-    // 768 -> 3072 22.7 and 26.1; below the line, 1576 x 1024 -> 1024 8.7 and 7.2; 177 x 448 -> 1856 6.4 and 4.9; 1234 x 704 -> 128 7.2
-    // and 5.4: 11 % on average over 131 such calls, the worst 5 % behind).
-    if (linear && g_force < 0 && c.cost > 10000.0) return FLEXIQ_OK;
+    return choose(sizes, g_force > 0 ? g_force - 1 : -1);
+}
+
+static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, bool linear, const flexiq_out *out, void *stream_,
+                      const HaloChoice &c, const LowerArgs *lower)
+{
+    using namespace halo;
+    const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0, lowering = lower && lower->ashift;
     const Plan &pl = kPlans[c.shape];
     const int P = 32 * pl.fr * pl.wm, taps = L->R * L->S, units = L->C / kUnit;
     const int Ho = (H + 2 * pad - L->R) / stride + 1, Wo = (W + 2 * pad - L->S) / stride + 1;
@@ -512,18 +506,22 @@ static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int 
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
     hipLaunchKernelGGL(kernel(pl.fr, taps, q_only, lowering), dim3((unsigned)(p.tiles * p.ncb)), dim3(64 * pl.wm * pl.wn * pl.wk), (size_t)c.lds, (hipStream_t)stream_, p);
     FLEXIQ_HIP(hipGetLastError());
-    *taken = 1 + c.shape;
     g_last = 1 + c.shape;
     return FLEXIQ_OK;
 }
 
-int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream_,
-                int *taken, const LowerArgs *lower)
+HaloChoice halo_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower)
 {
-    return launch_any(L, X, B, H, W, stride, pad, false, out, stream_, taken, lower);
+    return choice_any(L, B, H, W, stride, pad, false, out, lower);
 }
 
-bool halo_rows_forced() { return halo::g_force >= 0; }
+int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream_,
+                const HaloChoice &c, const LowerArgs *lower)
+{
+    return launch_any(L, X, B, H, W, stride, pad, false, out, stream_, c, lower);
+}
+
+bool halo_forced() { return halo::g_force >= 0; }
 
 // The same for a linear call of M rows of at most 1024 channels (the rows of a tile are all there is to its image): *taken = 0 also
 // where the tiled kernel is ahead.
@@ -536,7 +534,16 @@ int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fl
         if (L->N & (out->q ? 15 : 3)) return FLEXIQ_OK;   // (ragged output rows leave element by element here)
         if (few_rows_forced() || stream_forced()) return FLEXIQ_OK;   // (those hooks compare with the tiled kernel)
     }
-    return launch_any(L, X, 1, 1, (int)M, 1, 0, true, out, stream_, taken, lower);
+    const HaloChoice c = choice_any(L, 1, 1, (int)M, 1, 0, true, out, lower);
+    if (c.shape < 0) return FLEXIQ_OK;
+    // Linear calls of more than one short round stay with the tiled kernel: its blocks keep several tiles' loads in flight, where
+    // a block here copies, multiplies and stores one after the other (us there and here: 1576 x 768 -> 3072 10.2 and 11.2; 6304 x
+    // 768 -> 3072 22.7 and 26.1; below the line, 1576 x 1024 -> 1024 8.7 and 7.2; 177 x 448 -> 1856 6.4 and 4.9; 1234 x 704 -> 128 7.2
+    // and 5.4: 11 % on average over 131 such calls, the worst 5 % behind).
+    if (halo::g_force < 0 && c.cost > 10000.0) return FLEXIQ_OK;
+    const int rc = launch_any(L, X, 1, 1, (int)M, 1, 0, true, out, stream_, c, lower);
+    if (rc == FLEXIQ_OK) *taken = 1 + c.shape;
+    return rc;
 }
 
 }  // namespace flexiq
@@ -559,7 +566,7 @@ extern "C" int flexiq_debug_halo_plan(const int64_t *call, int64_t *plan)
         return FLEXIQ_EINVAL;
     const Sizes sizes = {(int32_t)call[0], (int32_t)call[1], (int32_t)call[2], (int32_t)call[3], (int32_t)call[4], (int32_t)N, (int32_t)((N + 255) & ~255ll),
                          (int32_t)C, (int32_t)R, (int32_t)R, (int32_t)call[8], (int32_t)call[9], false};
-    const Choice c = choose(sizes, g_force > 0 ? g_force - 1 : -1);
+    const flexiq::HaloChoice c = choose(sizes, g_force > 0 ? g_force - 1 : -1);
     if (c.shape < 0) return 0;
     plan[0] = 32 * kPlans[c.shape].fr * kPlans[c.shape].wm;
     plan[1] = 32 * kPlans[c.shape].wn;

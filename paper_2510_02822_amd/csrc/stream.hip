@@ -550,14 +550,15 @@ int prepare_stream_kernels(int device)
     return FLEXIQ_OK;
 }
 
+bool stream_forced() { return stream::g_force >= 0; }
+void stream_not_taken() { stream::g_last = 0; }
+
 // Launches the row-streaming kernel when the call qualifies; *taken says whether it did (0: nothing was launched).
 // Qualifying: rows are contiguous [M][C] (linear layers; 1x1 convolutions with stride 1 and no padding), C is 64, 128
 // or 256, plain outputs or int8 rows lowered for a consumer (`lower`: flexiq_out.lower_for, checked by the caller; no
 // consumer to scan for), and enough rows to give every compute unit several tiles.
 // X4 (optional): the packed 4-bit codes of the layer's leading (max_4bit_ch / 64) * 64 channels; taken only when int8 rows
 // are the call's only output (the caller has checked alignment and that M * C / 2 fits 31 bits).
-bool stream_forced() { return stream::g_force >= 0; }
-
 int launch_stream(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, bool rows_contiguous, int *taken,
                   const uint8_t *X4, const LowerArgs *lower)
 {

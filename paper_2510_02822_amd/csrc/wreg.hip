@@ -431,7 +431,7 @@ int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_
     *taken = 0;
     g_last = 0;
     if (g_force == 0 || L->C <= 256 || L->C > 1280) return FLEXIQ_OK;
-    if (g_force < 0 && (few_rows_forced() || stream_forced() || halo_rows_forced())) return FLEXIQ_OK;   // (those hooks compare with the tiled kernel)
+    if (g_force < 0 && (few_rows_forced() || stream_forced() || halo_forced())) return FLEXIQ_OK;   // (those hooks compare with the tiled kernel)
     if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
     const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0;
     const bool lowering = lower && lower->ashift;   // (null positions: the consumer has no 4-bit channels at its ratio)

@@ -129,6 +129,33 @@ def test_conv3_automatic_route(env):
     assert (got == oracle.forward_conv(ol, Xq, 2, 1, 0.5)).all()
 
 
+# Calls of more than one round of blocks, each on the kernel that measures fastest there: with resident weights where pixels are many and images
+# wide, with a resident input tile in between, tiled where the input tile leaves LDS few output pixels or images are wide and channels
+# many.  The last: an index limit keeps the resident input tile out, resident weights take the call (2^31 pixels times a side).
+ROUTES = [(32, 200, 200, 64, 64, 1, "weights"), (512, 56, 56, 64, 64, 1, "weights"), (64, 56, 56, 64, 64, 1, "input"), (128, 28, 28, 128, 128, 1, "input"),
+          (8, 56, 56, 384, 384, 1, "tiled"), (8, 48, 48, 512, 512, 1, "tiled"), (16, 112, 112, 128, 256, 2, "tiled"), (12300, 56, 56, 64, 64, 1, "weights")]
+
+
+@pytest.mark.parametrize("B,H,W,C,N,stride,kernel", ROUTES)
+def test_route_of_large_calls(env, B, H, W, C, N, stride, kernel):
+    torch, oracle, fq, dev = env
+    images = 2   # different ones, over and over
+    case = workloads.make_conv("c3route", 13, 500 + B + H + C, images, H, W, C, N, 3, 3, stride, 1, 32)
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[..., ol.perm])
+    fq.flexiq_set_ratio(hl, 0.5)
+    ref = oracle.forward_conv(ol, Xq, stride, 1, 0.5)
+    so = float(np.abs(oracle.dequant_f64(ref, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9)
+    Xd = _dev(torch, Xq, dev).repeat(B // images, 1, 1, 1)
+    got = fq.flexiq_mixed_conv_implicit(hl, Xd, stride, 1, q=True, out_scale=so)["q"]
+    tile = fq.debug_last_launch()["tile"]
+    n_tiled = fq.debug_force_tile(-1)
+    assert kernel == ("weights" if tile == -3 else "input" if tile >= n_tiled else "tiled"), tile
+    assert (fq.debug_force_conv3(-1, 0) == 1) == (kernel == "weights") and (fq.debug_force_halo(-1) > 0) == (kernel == "input")
+    want = _dev(torch, requant_fp32_sequence(ref, ol, so), dev)
+    assert bool((got.view(B // images, *want.shape) == want).all())
+
+
 @pytest.mark.parametrize("B,H,W,C,N1,gs2,rows", [(2, 9, 12, 64, 64, 32, 0), (3, 7, 9, 128, 96, 32, 2), (1, 14, 14, 64, 128, 64, 3)])
 def test_conv3_lowers_for_consumer(env, B, H, W, C, N1, gs2, rows):
     # the fused producer (Section 4.1 applied where the tensor is produced) on the 3x3 kernel: the NHWC int8 output in the
