@@ -84,3 +84,32 @@ def test_lowered_for_a_consumer_and_positions_found_at_run_time(env, M, C, N):
         pre = fq.flexiq_mixed_gemm(h2, got, acc=True)["acc"]
         fq.flexiq_input_prelowered(h2, False)
         assert (pre == fq.flexiq_mixed_gemm(h2, plain, acc=True)["acc"]).all().item()
+
+
+# Calls whose blocks would walk several tiles and leave much of the grid unused go to the tiled kernel: (M, C, N, outputs, taken).  Shares of
+# 0.46 and 0.91 with whole quads; 0.61 with two outputs, ragged and not; 0.53 and 0.85 with one ragged output; 0.55 with two; one tile per
+# block and 0.53
+@pytest.mark.parametrize("M,C,N,outs,taken", [(3018, 384, 636, "q", False), (1320, 1024, 2880, "q", True), (4000, 384, 639, "qy", False), (4000, 384, 640, "qy", True),
+                                              (6054, 512, 547, "y", False), (11400, 736, 1409, "y", True), (505, 384, 4597, "qy", False), (1000, 1280, 1101, "qy", True)])
+def test_route_by_the_used_share_of_the_grid(env, M, C, N, outs, taken):
+    torch, oracle, fq, dev = env
+    case = workloads.make_linear("wregshare", 22, M + N, M, C, N, 32)
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[:, ol.perm])
+    fq.flexiq_set_ratio(hl, 0.5)
+    hooks = (fq.debug_force_few_rows, fq.debug_force_tile_splitk, fq.debug_force_halo, fq.debug_force_wreg)
+    for hook in hooks:
+        hook(-1)
+    try:
+        out = fq.flexiq_mixed_gemm(hl, torch.from_numpy(Xq).to(dev), out_scale=0.5, **{o: True for o in outs})
+        tile = fq.debug_last_launch()["tile"]
+        assert tile == -6 if taken else 0 <= tile < fq.debug_force_tile(-1), tile
+    finally:
+        for hook, mode in zip(hooks, (0, 0, 0, 1)):
+            hook(mode)
+    pick = np.r_[0:min(M, 40), M - 1]
+    ref = oracle.forward_gemm(ol, Xq[pick], 0.5)
+    if "q" in outs:
+        assert (out["q"].cpu().numpy()[pick] == requant_fp32_sequence(ref, ol, 0.5)).all()
+    if "y" in outs:
+        check_y(out["y"].cpu().numpy()[pick], ref, ol)
