@@ -29,7 +29,8 @@ int flexiq_debug_max_blocks(int n);
 
 /* What the last GEMM / convolution launch used.  which = 0: tile shape index of the tiled kernel; below 0: another kernel (-2 row-
  * streaming, -3 3x3 with resident weights, -4 few rows, -5 tile per block, -6 weights in registers); from the table's size on: the
- * kernel of flexiq_debug_force_halo.  1: blocks launched, 2: blocks of that kernel resident per compute unit (0 for the others). */
+ * kernel of flexiq_debug_force_halo.  1: blocks launched, 2: blocks of that kernel resident per compute unit (0 for the others).
+ * 3: 1 if it was a few-row kernel that reads packed codes for the 4-bit weights on the matrix cores, else 0. */
 int flexiq_debug_last_launch(int which);
 
 /* The few-row kernels (linear calls with at most 64 rows; last launch: tile shape index -4): 1 = the matrix-core kernel

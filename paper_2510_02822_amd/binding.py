@@ -400,10 +400,11 @@ def debug_max_blocks(n: int) -> None:
 
 
 def debug_last_launch() -> dict:
-    """Tile shape index, block count and resident blocks per CU of the last GEMM / convolution launch."""
+    """Tile shape index, block count and resident blocks per CU of the last GEMM / convolution launch; packed: a few-row kernel that
+    read packed codes for the 4-bit weights on the matrix cores."""
     L = load()
     return {"tile": L.flexiq_debug_last_launch(0), "blocks": L.flexiq_debug_last_launch(1),
-            "resident": L.flexiq_debug_last_launch(2)}
+            "resident": L.flexiq_debug_last_launch(2), "packed": L.flexiq_debug_last_launch(3) == 1}
 
 
 def debug_force_conv3(mode: int, rows_per_tile: int = 0) -> int:

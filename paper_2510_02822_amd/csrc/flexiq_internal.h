@@ -110,6 +110,7 @@ int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, co
 // are not offered to their kernel
 bool conv3_forced();
 bool few_rows_forced();
+bool few_rows_last_packed();
 bool stream_forced();
 bool halo_forced();
 void conv3_not_taken();

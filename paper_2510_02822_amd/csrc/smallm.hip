@@ -746,9 +746,11 @@ constexpr int kTileMinRows = 32;   // up to here the few-row kernels measure fas
 static int g_force_cg = 0;      // test hook: column groups per block of k_few_rows_dot (0 = automatic)
 static int g_force_rows = -1;   // test hook: 1 / 2 = take k_few_rows / k_few_rows_dot whenever the call qualifies (3: k_few_rows with packed weight codes), 0 = never, -1 = automatic
 static int g_last_rows = 0;
+static bool g_last_codes = false;   // ... and whether that was a build that reads packed weight codes
 
 }  // namespace smallm
 
+bool few_rows_last_packed() { return smallm::g_last_codes; }
 bool few_rows_forced() { return smallm::g_force_rows >= 0 || smallm::g_force_tile_splitk >= 0; }
 
 // Launches k_few_rows (*taken = 1) or k_few_rows_dot (*taken = 2) for a linear call with at most 64 rows; *taken = 0: the call
@@ -759,6 +761,7 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     using namespace smallm;
     *taken = 0;
     g_last_rows = 0;
+    g_last_codes = false;
     if (g_force_rows == 0 || M < 1 || M > 64) return FLEXIQ_OK;
     if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
     if (out->lower_for && !lower) return FLEXIQ_OK;   // (the caller has checked the consumer; null positions: nothing to lower)
@@ -840,6 +843,7 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     FLEXIQ_HIP(hipGetLastError());
     *taken = 1;
     g_last_rows = 1;
+    g_last_codes = p4;
     return FLEXIQ_OK;
 }
 
@@ -877,6 +881,7 @@ int launch_few_rows_fp6(const flexiq_layer *L, const int8_t *X, const uint8_t *X
     FLEXIQ_HIP(hipGetLastError());
     *taken = 1;
     g_last_rows = 3;
+    g_last_codes = false;
     return FLEXIQ_OK;
 }
 

@@ -249,9 +249,12 @@ def test_packed_weight_codes(env, K, N):
                 for pre, X in ((False, Xq), (True, low.astype(np.int8))):
                     fq.flexiq_input_prelowered(hl, pre)
                     out = fq.flexiq_mixed_gemm(hl, torch.from_numpy(X).to(dev), acc=True, q=True, out_scale=so)
-                    assert fq.debug_force_few_rows(3) == 1
+                    assert fq.debug_force_few_rows(3) == 1 and fq.debug_last_launch()["packed"] == (r > 0)
                     assert (out["acc"].cpu().numpy() == ref).all(), (M, r, pre)
                     assert (out["q"].cpu().numpy() == requant_fp32_sequence(ref, ol, so)).all(), (M, r, pre)
                 fq.flexiq_input_prelowered(hl, False)
+        fq.debug_force_few_rows(1)   # expanded copies
+        out = fq.flexiq_mixed_gemm(hl, torch.from_numpy(Xq).to(dev), acc=True)
+        assert not fq.debug_last_launch()["packed"] and (out["acc"].cpu().numpy() == ref).all()
     finally:
         fq.debug_force_few_rows(-1)
