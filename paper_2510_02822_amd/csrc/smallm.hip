@@ -11,7 +11,7 @@
 //     position byte.
 // k_few_rows (3 .. 64 rows) feeds the matrix cores as the tiled kernel does: 4-bit units from the position-expanded int8 copy
 // (16 bytes per lane like 8-bit units), their activations bit-lowered (same int8 MFMA, same int32 sums); up to 16 rows against
-// weights of 40 MB and more from the packed codes (P4 builds).
+// weights of 40 MiB and more from the packed codes (P4 builds).
 // k_few_rows_dot (1 .. 4 rows) multiplies on the vector ALU, 4-bit units as the packed 4-bit codes (Section 7's shifted
 // accumulation): the kernel for calls that are bound by weight bytes.
 // Both give the tiled kernel's results bit for bit.
@@ -98,7 +98,7 @@ constexpr int kRowCols = 16;   // output columns per block
 // expansion cost more than it saved was the sign and the position of every code; here a code stays where it is in the upper
 // half of its byte, code * 16 as an int8 value, two operations per four codes (`and`, or `shift` and `and`), and the position
 // of a column, one per group, is applied to the group's four sums of a lane, exactly: sum >> (4 - position).
-// (Groups of 32, two matrix instructions per K-step, half of each masked: 2 % faster at 67 MB of weights and 16 rows, slower below. Not kept.)
+// (Groups of 32, two matrix instructions per K-step, half of each masked: on 67 MB of weights 2 % faster with 16 rows and 4 to 6 % with 5, slower below. Not kept.)
 template <int MF, bool COOP, bool FP6 = false, bool P4 = false>
 __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
 {
@@ -831,11 +831,16 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     const size_t rows_bytes = (size_t)M * (32 * (size_t)p.units4 + 16);
     const bool coop = M <= 8 && !p.x_pre && p.units4 > 0 && lds + rows_bytes <= 64 * 1024;
     if (coop) lds += rows_bytes;
-    // Packed codes where the weight bytes decide: from 40 MB of 8-bit weights on (us with the expanded copies and with the codes,
-    // weights from HBM, r = 0.5 / 1: 16384 x 4096, 5 rows 16.6 / 17.0 and 14.0 / 14.0, 16 rows 18.6 / 19.4 and 16.9 / 17.4; 11008 x 4096, 5 rows
-    // 11.0 / 11.9 and 10.1 / 10.8; 8192 x 4096, 16 rows 10.8 / 10.9 and 11.1 / 11.4; 4096 x 1024, 16 rows 4.1 and 4.2 / 4.3).
+    // Packed codes where the weight bytes decide (us with the expanded copies and with the codes, weights from HBM, r = 0.25 / 0.5 / 1).
+    // Up to eight rows, which the block lowers once, from 40 MiB of 8-bit weights on: 16384 x 4096, 5 rows 17.0 / 16.9 / 17.0 and 15.9 / 14.5 /
+    // 14.2; 8192 x 5120 (40 MiB), 8 rows 12.4 / 12.4 / 13.4 and 12.5 / 12.5 / 12.1, kept in cache 6 to 25 % faster.  (At 32 MiB, 8192 x 4096, the codes are
+    // ahead from HBM, 9.9 / 10.2 against 10.4 / 11.4 with 8 rows at r = 0.5 / 1, but not for every shape kept in cache; at 16 MiB, 4096 x 4096, r >= 0.5, they gain
+    // 3 to 6 % from HBM and lose 17 to 30 % in cache.)  More rows are lowered in every wave, which takes more than 40 MiB and half of the channels at 4 bits to pay
+    // for: 16384 x 4096, 16 rows 18.5 / 18.5 / 19.2 and 18.0 / 16.9 / 16.4; 11008 x 4096 (43 MiB), 12 rows 13.0 / 13.0 / 13.6 and 13.2 / 12.6 / 12.5; 8192 x
+    // 5120, 12 rows 11.9 / 11.9 / 12.2 and 12.4 / 12.6 / 12.3.
     p.s4 = p.units4 / 2;
-    const bool p4 = mf == 1 && L->group_size == 64 && p.s4 > 0 && (g_force_rows == 3 || (g_force_rows < 0 && (int64_t)L->N * L->C >= (40 << 20)));
+    const bool p4 = mf == 1 && L->group_size == 64 && p.s4 > 0 && (g_force_rows == 3 || (g_force_rows < 0 && (M <= 8 ? (int64_t)L->N * L->C >= (40 << 20)
+                                                                                                                     : (int64_t)L->N * L->C > (41 << 20) && 2 * L->max_4bit_ch >= L->C)));
     void (*fn)(const RowsParams) =
         mf == 1 ? (p4 ? (coop ? k_few_rows<1, true, false, true> : k_few_rows<1, false, false, true>) : (coop ? k_few_rows<1, true> : k_few_rows<1, false>))
                 : (mf == 2 ? k_few_rows<2, false> : (mf == 3 ? k_few_rows<3, false> : k_few_rows<4, false>));

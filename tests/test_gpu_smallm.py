@@ -258,3 +258,26 @@ def test_packed_weight_codes(env, K, N):
         assert not fq.debug_last_launch()["packed"] and (out["acc"].cpu().numpy() == ref).all()
     finally:
         fq.debug_force_few_rows(-1)
+
+
+# Packed weight codes by themselves: up to 8 rows from 40 MiB of 8-bit weights on, more rows above 41 MiB with half of the channels at 4 bits
+@pytest.mark.parametrize("K,N", [(1024, 32768), (5120, 8192), (1024, 43008)])   # 32, 40 and 42 MiB
+def test_packed_weight_codes_route(env, K, N):
+    torch, oracle, fq, dev = env
+    rng = np.random.default_rng(K)
+    W = rng.standard_normal((N, K), dtype=np.float32) * np.float32(0.02)
+    amax = np.exp(rng.standard_normal(K)).astype(np.float32)
+    hl = fq.flexiq_quantize_pack(W, amax, float(amax.max()) / 127, 64)
+    X = torch.randint(-127, 128, (16, K), device=dev, dtype=torch.int8)
+    for M in (5, 8, 9, 16):
+        for r in (0.0, 0.25, 0.5, 1.0):
+            fq.flexiq_set_ratio(hl, r)
+            x = X[:M].contiguous()
+            got = fq.flexiq_mixed_gemm(hl, x, acc=True)["acc"]
+            want_codes = r > 0 and (N * K >= 40 << 20 if M <= 8 else N * K > 41 << 20 and r >= 0.5)
+            assert fq.debug_last_launch()["packed"] == want_codes and fq.debug_force_few_rows(-1) == 1, (M, r)
+            fq.debug_force_few_rows(1)
+            other = fq.flexiq_mixed_gemm(hl, x, acc=True)["acc"]
+            assert not fq.debug_last_launch()["packed"]
+            fq.debug_force_few_rows(-1)
+            assert torch.equal(got, other), (M, r)
