@@ -27,8 +27,8 @@ def env():
 
 
 # (M, C, N, gs): every number of units held (16, 24, 32, 40), full, short of one unit and of seven, odd; one tile, ragged last tiles,
-# blocks of one to six tiles (around the three and four slots of the ring), several column blocks with a ragged last one, more
-# column blocks than compute units' share of row groups, N not a multiple of 32, of 16 and of 4
+# blocks of one to three tiles (the loop and its last rounds; the ring in use beyond its slots: test_many_tiles_per_block), several
+# column blocks with a ragged last one, more column blocks than compute units' share of row groups, N not a multiple of 32, of 16 and of 4
 CASES = [(1, 512, 256, 64), (31, 288, 40, 32), (33, 480, 300, 32), (1000, 768, 3072, 64), (1025, 544, 2816, 32), (700, 736, 4100, 32),
          (2100, 1024, 2049, 64), (450, 992, 6144, 32), (830, 800, 6160, 32), (97, 1280, 16384, 64), (300, 1248, 10000, 32), (161, 1056, 16400, 32),
          (193, 320, 20000, 64)]
@@ -57,6 +57,83 @@ def test_sums_and_codes(env, M, C, N, gs):
         for kind in ("q", "y"):   # builds that write one output
             only = fq.flexiq_mixed_gemm(hl, Xd, out_scale=so, **{kind: True})[kind]
             assert fq.debug_force_wreg(1) == 1 and (only == out[kind]).all().item(), (r, kind)
+
+
+def _tiles_per_block(torch, M, N):
+    """Row tiles of the fullest and of the emptiest block, as the launcher deals them out."""
+    cols, tiles = -(-N // 256), -(-M // 32)
+    groups = max(1, min(tiles, torch.cuda.get_device_properties(0).multi_processor_count // cols))
+    return -(-tiles // groups), tiles // groups
+
+
+def _ring(C):
+    """LDS slots for row tiles: four while four of them and the tables fit, else three."""
+    held = -(-(C // 32) // 8) * 8
+    return 4 if held * 1024 * 4 + 3 * 256 * 4 <= 160 * 1024 else 3
+
+
+# Every number of units held, full (each piece of a tile copied by every wave) and not, by one unit and by seven: blocks of more than twice as
+# many tiles as the ring has slots, so that every slot is filled again with rows that are multiplied, some blocks one tile ahead of others
+@pytest.mark.parametrize("C,gs", [(512, 64), (480, 32), (288, 32), (768, 32), (544, 32), (736, 32), (1024, 64), (992, 32), (800, 32), (1280, 32), (1248, 32), (1056, 32)])
+def test_many_tiles_per_block(env, C, gs):
+    torch, oracle, fq, dev = env
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    N = 64 * cus + 16   # three groups of blocks on 256 compute units, and a last column block of 16 columns
+    slots = _ring(C)
+    M = 32 * ((2 * slots + 1) * (cus // -(-N // 256)) + 1) - 11
+    most, least = _tiles_per_block(torch, M, N)
+    assert least > 2 * slots and most == least + 1
+    case = workloads.make_linear("wregring", 22, C, M, C, N, gs)
+    case.X *= 2.0
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[:, ol.perm])
+    Xd = torch.from_numpy(Xq).to(dev)
+    rows = np.r_[0, 31, 32, 32 * slots + 3, M // 2, M - 33, M - 1]
+    for r in sorted({0.0, gs / C, 0.5, 1.0}):
+        fq.flexiq_set_ratio(hl, r)
+        ref = oracle.forward_gemm(ol, np.ascontiguousarray(Xq[rows]), r)
+        so = float(np.abs(oracle.dequant_f64(ref, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9)
+        fq.debug_force_wreg(0)   # the tiled kernel: every row
+        want = fq.flexiq_mixed_gemm(hl, Xd, acc=True, y=True, q=True, out_scale=so)
+        assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
+        assert (want["acc"].cpu().numpy()[rows] == ref).all() and (want["q"].cpu().numpy()[rows] == requant_fp32_sequence(ref, ol, so)).all()
+        fq.debug_force_wreg(1)
+        for kinds in ("q", "y", ("acc", "y", "q")):
+            got = fq.flexiq_mixed_gemm(hl, Xd, out_scale=so, **{k: True for k in kinds})
+            assert fq.debug_force_wreg(1) == 1
+            for k in kinds:
+                assert torch.equal(got[k], want[k]), (r, k, len(kinds))
+
+
+# the same for the builds that lower for a consumer (of at most 159 channel groups: fewer columns, more rows)
+@pytest.mark.parametrize("C", [512, 288, 768, 544, 1024, 992, 1280, 1056])
+def test_many_tiles_per_block_lowered_for_a_consumer(env, C):
+    torch, oracle, fq, dev = env
+    N, slots = 5120, _ring(C)
+    M = 32 * ((2 * slots + 1) * (torch.cuda.get_device_properties(0).multi_processor_count // (N // 256)) + 1) - 5
+    assert _tiles_per_block(torch, M, N)[1] > 2 * slots
+    first = workloads.make_linear("wregring1", 22, C, M, C, N, 32)
+    second = workloads.make_linear("wregring2", 22, C + 1, 64, N, 64, 64)
+    x_scale = oracle.absmax_scale(first.Xcal)
+    o2, h2, _ = both_layers(second)
+    hl = fq.flexiq_quantize_pack(first.W, np.abs(first.Xcal).max(0), x_scale, 32, bias=first.bias, out_perm=o2.perm)
+    X = torch.from_numpy(np.ascontiguousarray(oracle.quantize(first.X, x_scale)[:, hl.info()["perm"]])).to(dev)
+    for r1, r2 in ((0.0, 0.5), (0.5, 1.0), (1.0, 0.25)):
+        fq.flexiq_set_ratio(hl, r1)
+        k4 = fq.flexiq_set_ratio(h2, r2)
+        so = float(fq.flexiq_mixed_gemm(hl, X[:64].contiguous(), y=True)["y"].abs().max()) / 127
+        plain = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=so)["q"]
+        assert fq.debug_force_wreg(0) == 1
+        want = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=so, lower_for=h2)["q"]
+        assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
+        fq.debug_force_wreg(1)
+        got = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=so, lower_for=h2)["q"]
+        assert fq.debug_force_wreg(1) == 1 and torch.equal(got, want)
+        # ... and from the definition: the codes of the consumer's 4-bit channels clamped and cleared at its positions
+        sh = torch.from_numpy(np.repeat(o2.a_shift.astype(np.int32), 64)[:k4]).to(dev)
+        low = plain.to(torch.int32)
+        low[:, :k4] = ((low[:, :k4] >> sh).clamp(-8, 7)) << sh
+        assert torch.equal(got.to(torch.int32), low) and not torch.equal(got, plain)
 
 
 @pytest.mark.parametrize("M,C,N", [(2500, 768, 1024), (700, 1248, 512)])
