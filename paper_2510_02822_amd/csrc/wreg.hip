@@ -141,6 +141,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
         bi_t = p.cs[p.Npad + n_blk + tid];
     }
     issue();
+    __builtin_amdgcn_sched_barrier(0);   // (in this order: the waits below count on it)
     // ---- weights: columns n_blk + 32 wave + fr, k-half fh of every unit
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.W8, 0, 2 * p.w4x_delta, kRsrcFlags);
     const int wlane = (fh * p.Npad + n_blk + 32 * wave + fr) * 16;
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
         const int v = EXACT || u <= NU - 8 ? u : min(u, p.units - 1);
         w[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, wlane, v * 32 * p.Npad + (v < p.units4 ? p.w4x_delta : 0), 0));
     }
-    __builtin_amdgcn_sched_barrier(0);   // (in this order: the waits below count on it)
+    __builtin_amdgcn_sched_barrier(0);   // (likewise)
 #pragma unroll
     for (int k = 1; k < S - 1; ++k) issue();
 
