@@ -102,11 +102,25 @@ def _check(rc: int):
         raise FlexiqError("flexiq status %d: %s" % (rc, msg))
 
 
-def _stream() -> int:
-    """The current stream of the current device (torch.cuda.current_stream() builds an object for it: 3.0 us a call against 0.2;
-    a small call is 7 us in all)."""
+def _pick_stream():
+    """How to get the current stream's handle: torch.cuda.current_stream() builds an object for it, 3.0 us a call against 0.2 of the
+    functions behind it (a small call is 7 us in all); those are private, so only where this torch has them."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_stream_handle = None
+
+
+def _stream() -> int:
+    """The current stream of the current device."""
+    global _stream_handle
+    if _stream_handle is None:
+        _stream_handle = _pick_stream()
+    return _stream_handle()
 
 
 def _f32(a) -> np.ndarray:

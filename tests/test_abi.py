@@ -112,3 +112,17 @@ def test_missing_library_is_loud(monkeypatch):
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/libflexiq.so")
     with pytest.raises(b.FlexiqError):
         b.load()
+
+
+@pytest.mark.parametrize("gone", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_current_stream_without_torchs_private_functions(monkeypatch, gone):
+    # a torch that lacks either of the private functions: the public one serves every call
+    import torch
+    import paper_2510_02822_amd.binding as b
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    for name in gone:
+        monkeypatch.delattr(torch._C, name)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77}))
+    monkeypatch.setattr(b, "_stream_handle", None)
+    assert b._stream() == (77 if gone else 1003) and b._stream() == (77 if gone else 1003)
