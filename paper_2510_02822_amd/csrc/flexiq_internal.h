@@ -117,12 +117,13 @@ void conv3_not_taken();
 void stream_not_taken();
 // (halo.hip) 3x3 convolutions and strided or padded 1x1 ones: the input tile resident in LDS, weights streamed past it.
 // shape < 0: the call does not qualify; cost: modelled cycles of the busiest compute unit, us: modelled time of the call; one_round:
-// every block is resident from the start
+// every block is resident from the start; crowded: a strided 3x3 filter whose input tile fits LDS for no more than 32 output pixels
+// and one block at a time, with several column blocks that each copy nine input pixels per output pixel
 struct HaloChoice {
     int shape = -1;
     int64_t tiles = 0, ncb = 0, lds = 0;
     double cost = 0, us = 0;
-    bool one_round = false;
+    bool one_round = false, crowded = false;
 };
 HaloChoice halo_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower);
 int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream,

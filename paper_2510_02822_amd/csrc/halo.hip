@@ -433,6 +433,7 @@ static HaloChoice choose(const Sizes &s, int only)
             const double even = conc == 1 ? (double)per_cu : std::max((double)conc, 0.5 * (per_cu + (double)blocks / s.num_cu));
             const double rounds = conc == 1 ? (double)per_cu : std::max(1.0, 0.5 * ((per_cu + conc - 1) / conc + (double)blocks / s.num_cu / conc));
             c.one_round = per_cu <= conc;
+            c.crowded = taps != 1 && st == 2 && P == 32 && fits == 1 && ncb > 1 && per_cu > 2;
             c.us = 3.3 + 1e-3 * (even * (0.78 * std::max(mfma, 0.27 * mfma + 0.007 * weights) + 0.57 * 190.0 * waves + 0.42 * 0.1 * P * BN * s.out_bytes) +
                                  (taps == 1 ? 0.65 : 0.48) * rounds * 370.0 * (double)(rows * cpr) / waves);
         }

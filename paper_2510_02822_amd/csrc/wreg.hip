@@ -425,13 +425,13 @@ int prepare_wreg_kernels(int device)
 // weights fit LDS: k_stream; above, they do not fit the registers of 256-column blocks).  It is offered what the kernels for
 // few rows and for one short round of blocks leave (where those qualify they are ahead: blocks of one or two tiles pay for the weights alone;
 // 3262 x 512 -> 576 at r = 0.5, fp32: 9.1 us against 7.0 in k_halo).  Of that it takes all but the calls that give its blocks several
-// tiles and leave too much of the grid unused, in a last round of few tiles and in columns beyond N: the tiled kernel has smaller tiles to
-// fill the chip with.  Measured on 6300 calls by the used share of the grid (time here over time there, geometric means): rows of whole
-// quads, two tiles per block, below 0.4 / to 0.5 / 0.6 / 0.7 / 1: 1.12 / 1.01 / 0.90 / 0.90 / 0.88, three tiles 1.04 up to 0.5 and 0.96 / 0.94 / 0.90 beyond (int32
-// sums alone, which the tiled kernel stores in an epilogue of their own, 1.05 up to 0.6).  Rows that
-// leave element by element (N not a multiple of 4), whose stores the tiled kernel hides better, one output: two and three tiles 1.07 to
-// 1.16 up to 0.5, 1.02 to 0.7, 0.98 beyond; two or three outputs 1.17 to 1.26 up to 0.5, 1.11 to 0.7, 1.05 to 0.8, 0.98 beyond.  With one tile per block it is
-// ahead whatever the share (0.78, 0.83 and 0.93).
+// tiles and leave too much of the grid unused, in a last round of few tiles or in columns beyond N: the tiled kernel has smaller tiles to
+// fill the chip with.  Measured on 10800 calls (200 to 400 thousand rows) by the used share of the grid; time here over time there, geometric
+// means.  Rows of whole quads, share below 0.2 / 0.3 / 0.4 / 0.5 / 0.6 / 1: 1.33 / 1.15 / 1.05 / 0.96 / 0.87 / 0.80, hardly changed by how many tiles a block
+// walks; int32 sums alone, which the tiled kernel stores in an epilogue of their own: 1.05 to 1.2 up to 0.55.  Rows that leave element by element (N
+// not a multiple of 4), whose stores a block hides behind its other tiles: with two or three tiles 1.00 to 1.11 up to 0.6 for one output and
+// 1.03 to 1.24 up to 0.8 for more, with more tiles 1.05 to 1.46 below 0.2 and 0.85 to 1.0 beyond.  With one tile per block it is ahead whatever
+// the share (0.78, 0.83 and 0.93).
 int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
 {
     using namespace wreg;
@@ -466,7 +466,8 @@ int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_
     {
         const int per_block = p.per_group + (p.extra > 0 ? 1 : 0), outputs = (out->acc ? 1 : 0) + (out->y ? 1 : 0) + (out->q ? 1 : 0);
         const double used = (double)M * L->N / ((double)ds.num_cu * per_block * kRows * kCols);
-        if (g_force < 0 && per_block > 1 && used < ((L->N & 3) == 0 ? (out->acc && outputs == 1 ? 0.6 : 0.5) : (outputs == 1 ? 0.7 : 0.8))) return FLEXIQ_OK;
+        const double least = (L->N & 3) ? (per_block > 3 ? 0.25 : outputs == 1 ? 0.6 : 0.8) : (out->acc && outputs == 1 ? 0.55 : 0.4);
+        if (g_force < 0 && per_block > 1 && used < least) return FLEXIQ_OK;
     }
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
     const Out kind = lowering ? kLowered : (q_only ? kCodes : (out->y && !out->q && !out->acc && (L->N & 3) == 0 ? kFloats : kAny));
