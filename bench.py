@@ -17,8 +17,9 @@ milliseconds of work to settle at its running clocks, and a short timed region a
 low; for the same reason about 50 ms of untimed steps run before the requested warm-up steps.
 `roofline` covers the GEMM kernel (the only kernel in the timed region): algorithmic ops per launch
 = 2*M*N*K, average launch duration = HIP-event time of the timed region / launches in it.  `cpu_baseline` times the
-CPU oracle on a bounded row sample of the same workload.  `shapes` (after the timed region, not part of `value`)
-carries the other workloads of the benchmark spec: ViT-B fc2, ViT-L fc1 / fc2 (int8 kernel and the FP6 variant of the
+CPU oracle on a bounded row sample of the same workload.  After the timed region, and not part of `value`, the side
+measurements: one record per line on stderr ("shapes: ..."), their number in the line (`shapes_records`), all of them in a file with
+--shapes-json (in the line they made it 50 KB long).  They are ViT-B fc2, ViT-L fc1 / fc2 (int8 kernel and the FP6 variant of the
 4-bit phase), fc1 -> fc2 chains, the 3x3 convolution, the ResNet-50 pass with the seeded ratio schedule, few-row
 calls, the residual reorder operator and a plain 2 GiB device copy as the HBM ceiling.
 """
@@ -42,8 +43,8 @@ RATIOS = (0.0, 0.25, 0.5, 0.75, 1.0)
 
 # Bytes per launch of the GEMM kernel on the default workload (fc1, int8 output) measured with
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the readings of a 256 MiB device copy (fetch x2.0,
-# write x1.0): median fetch 25.8 MB + write 19.4 MB.  See profiles/k_mixed_vitb_fc1_hbm_traffic.txt.
-MEASURED_TRAFFIC_BYTES = {("fc1", "q"): 45.2e6}
+# write x1.0): median fetch 22.5 MB + write 19.4 MB.  See profiles/k_wreg_vitb_fc1_hbm_traffic.txt.
+MEASURED_TRAFFIC_BYTES = {("fc1", "q"): 41.9e6}
 
 
 def log(*a):
@@ -106,7 +107,7 @@ def _calib(case):
 
 
 def measure_shapes(torch, fq, workloads, dev, resnet=True):
-    """The other workloads of the benchmark spec (not in `value`): one compact record per (workload, variant, r)."""
+    """The other workloads (not in `value`): one compact record per (workload, variant, r), each logged as it is made."""
     out = []
 
     def rec(workload, variant, r, us, ops=None, byts=None, **kw):
@@ -567,6 +568,7 @@ def main():
     ap.add_argument("--cpu-rows", type=int, default=4096, help="rows of the workload the CPU oracle is timed on (0: skip)")
     ap.add_argument("--eager", action="store_true", help="launch from Python instead of replaying a captured HIP graph")
     ap.add_argument("--no-shapes", action="store_true", help="skip the side measurements of the other workloads (`shapes`)")
+    ap.add_argument("--shapes-json", default=None, metavar="FILE", help="write the side measurements to this file")
     ap.add_argument("--no-resnet", action="store_true", help="skip the ResNet-50 pass inside `shapes`")
     ap.add_argument("--profile-only", default=None, choices=PROFILE_TARGETS,
                     help="run only this side workload, eagerly, --steps launches per ratio in {0, 0.5, 1} (for rocprofv3)")
@@ -686,6 +688,9 @@ def main():
             ts.append(a0.elapsed_time(a1) * 1e3 / 50)
         per_r_us[r] = float(np.median(ts))
         del g
+    tile = fq.debug_last_launch()["tile"]   # (the kernel of the timed region: one route for every ratio)
+    kernel_name = {-6: "flexiq::wreg::k_wreg (int8 MFMA, weights in registers)"}.get(
+        tile, "flexiq::k_mixed (int8 MFMA, tile shape %d)" % tile if 0 <= tile < fq.debug_force_tile(-1) else "flexiq launch code %d" % tile)
 
     # the same GEMM when the producing layer has lowered the activations already (flexiq_out.lower_for on the
     # producer, flexiq_input_prelowered on this layer): what the fused producer epilogue buys the consumer.
@@ -813,7 +818,7 @@ def main():
                       "algorithmic_GBs": round(algorithmic_bytes(M, N, K, r, out_bytes, "w4x") / us / 1e3, 1)})
     avg_us = dev_us / (args.steps * len(RATIOS))
     achieved = ops_call / avg_us / 1e6 if avg_us else value
-    roofline = {"bound": "mfma", "kernel": "flexiq::k_mixed (int8 MFMA mixed GEMM)", "achieved": round(achieved, 1),
+    roofline = {"bound": "mfma", "kernel": kernel_name, "achieved": round(achieved, 1),
                 "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": round(achieved / INT8_MFMA_PEAK_TOPS, 4),
                 "avg_launch_us": round(avg_us, 2) if avg_us else None,
                 "ops_per_launch": ops_call, "traffic": MEASURED_TRAFFIC_BYTES.get((args.layer, args.out))}
@@ -855,6 +860,9 @@ def main():
         t_sh = time.time()
         shapes = measure_shapes(torch, fq, workloads, dev, resnet=not args.no_resnet)
         log("shapes: %.0f s" % (time.time() - t_sh))
+        if args.shapes_json:
+            with open(args.shapes_json, "w") as f:
+                json.dump(shapes, f, indent=0)
 
     line = {
         "metric": METRIC, "value": round(value, 2), "unit": "TOPS", "n_gpus": 1, "steps": args.steps,
@@ -865,7 +873,7 @@ def main():
                                                           {"q": "int8 requant", "y": "fp32 dequant", "acc": "int32 dump"}[args.out]),
                    "M": M, "K": K, "N": N, "group_size": gs, "ratios": list(RATIOS), "steps_per_graph": chunk},
         "roofline": roofline, "cpu_baseline": cpu, "per_r": per_r, "prelowered_input": pre, "dynamic_positions": dyn, "fused_scan": fused_scan, "ratio_switch": ratio_switch, "parity": parity,
-        "shapes": shapes,
+        "shapes_records": len(shapes) if shapes is not None else 0,
     }
     print(json.dumps(line), flush=True)
 
