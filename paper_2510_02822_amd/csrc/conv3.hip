@@ -6,7 +6,8 @@
 // and right, are copied from global memory straight into one of two or three LDS buffers, one or two tiles ahead; the
 // bit-lowering of the 4-bit groups (Section 4.1) is one pass over the landed tile, in place, once per activation
 // instead of once per tap; the nine taps are nine shifted reads of the same LDS image.  Same int8 MFMA, int32
-// accumulators and epilogue arithmetic as the tiled kernel: bit-identical outputs.
+// accumulators and epilogue arithmetic as the tiled kernel: bit-identical outputs.  It is ahead where pixels are many and image rows
+// wide (conv_route() in gemm.hip); the kernel with a resident input tile (halo.hip) takes the others.
 //
 // Block: eight computing waves and one loading wave.  Computing wave w owns the output pixels 32 w .. 32 w + 31 and
 // 32 (w + 8) .. of the tile (row-major over its rows) and both 32-column fragments; the loading wave issues every copy

@@ -1,6 +1,6 @@
-// Convolutions whose input tile stays in LDS while the weights stream past it: 3x3 filters at any stride and padding with
-// any multiple of 32 input channels, and strided or padded 1x1 filters (ResNet stages 2-4, downsampling layers, small
-// batches).  Linear layers of up to 1024 channels are served as well where a call is one short round of blocks.
+// Convolutions whose input tile stays in LDS while the weights stream past it: 3x3 filters at stride 1 or 2 and any padding with
+// any multiple of 32 input channels, and strided (2) or padded 1x1 filters (ResNet stages 2-4, downsampling layers, small
+// batches).  Which calls it gets beyond one round of blocks: conv_route() in gemm.hip.  Linear layers of up to 1024 channels are served as well where a call is one short round of blocks.
 //
 // What bounded these calls in the tiled implicit-GEMM kernel (k_mixed) was not matrix work: a K-step there is 64 channels of
 // one filter tap, whose activations are fetched (and, for 4-bit groups, bit-lowered) again for each of the nine taps through

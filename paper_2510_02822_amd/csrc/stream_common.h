@@ -1,5 +1,6 @@
-// Pieces shared by the kernels that keep a block's weights resident in LDS and stream activations past them
-// (stream.hip: rows of a linear layer; conv3.hip: image rows of a 3x3 convolution): vector types, the bit-lowering of
+// Pieces shared by the kernels that keep one operand of a block resident and stream the other past it (stream.hip and conv3.hip:
+// weights in LDS, rows of a linear layer or image rows of a 3x3 convolution; halo.hip: the input tile in LDS; wreg.hip: weights in
+// registers): vector types, the bit-lowering of
 // four activation bytes (Section 4.1), the LDS piece permutation, and the epilogue of one 32 x 32 accumulator fragment.
 #pragma once
 #include "flexiq_internal.h"

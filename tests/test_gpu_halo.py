@@ -1,4 +1,4 @@
-"""GPU parity of the convolution kernel whose input tile is resident in LDS (3x3 filters at any stride and padding, strided or
+"""GPU parity of the convolution kernel whose input tile is resident in LDS (3x3 filters at stride 1 or 2 and any padding, strided or
 padded 1x1 filters) against the CPU oracle, through flexiq_mixed_conv_implicit: int32 sums and int8 codes bit for bit."""
 import numpy as np
 import pytest
@@ -62,6 +62,20 @@ def test_all_block_shapes(env, B, H, W, C, N, R, stride, pad, gs):
     assert len(ran) >= 3
     fq.flexiq_mixed_conv_implicit(hl, Xd, stride, pad, acc=True)
     assert fq.debug_force_halo(-1) in ran   # the automatic route
+
+
+@pytest.mark.parametrize("R,stride,pad", [(3, 3, 1), (1, 3, 0), (3, 4, 2)])
+def test_larger_strides_stay_with_the_tiled_kernel(env, R, stride, pad):
+    torch, oracle, fq, dev = env
+    case = workloads.make_conv("halostride", 21, R + stride, 2, 13, 11, 64, 48, R, R, stride, pad, 32)
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[..., ol.perm])
+    fq.flexiq_set_ratio(hl, 0.5)
+    for k in (-1, 1):
+        fq.debug_force_halo(k)
+        got = fq.flexiq_mixed_conv_implicit(hl, torch.from_numpy(Xq).to(dev), stride, pad, acc=True)["acc"].cpu().numpy()
+        assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1) and fq.debug_force_halo(-1) == 0
+        assert (got == oracle.forward_conv(ol, Xq, stride, pad, 0.5)).all()
 
 
 def test_positions_found_at_run_time_and_lowered_input(env):
