@@ -83,6 +83,7 @@ def load():
     L.flexiq_debug_force_conv3.argtypes = [C.c_int, C.c_int]
     L.flexiq_debug_force_halo.argtypes = [C.c_int]
     L.flexiq_debug_force_wreg.argtypes = [C.c_int]
+    L.flexiq_debug_force_wreg6.argtypes = [C.c_int]
     L.flexiq_debug_force_tile.argtypes = [C.c_int]
     L.flexiq_debug_force_packed4.argtypes = [C.c_int]
     L.flexiq_debug_max_blocks.argtypes = [C.c_int]
@@ -443,6 +444,14 @@ def debug_force_wreg(mode: int) -> int:
     """Kernel with the weights resident in registers: 1 = whenever the call reaches it and qualifies, 0 = never, -1 = automatic.
     Returns whether the last call it was offered ran on it."""
     rc = load().flexiq_debug_force_wreg(int(mode))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def debug_force_wreg6(mode: int) -> int:
+    """The same for flexiq_mixed_gemm_fp6."""
+    rc = load().flexiq_debug_force_wreg6(int(mode))
     if rc < 0:
         _check(rc)
     return rc

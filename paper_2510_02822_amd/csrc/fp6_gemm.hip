@@ -136,11 +136,11 @@ extern "C" int flexiq_mixed_gemm_fp6(const flexiq_layer *L, const int8_t *X, con
         return FLEXIQ_EINVAL;   // FP6 output needs the consumer's positions
     }
 
+    LowerArgs la;
+    la.ashift = p.next_ashift; la.K4 = p.next_K4; la.gs_log2 = p.next_gs_log2;   // (checked above; null: the call names no consumer)
+    la.x6 = p.nx6; la.K6 = p.next_K6; la.S = p.next_S;
     if ((M > 16 || out->lower_for) && g_force_shape < 0) {   // few output tiles, a long reduction: a tile per block whose waves split the reduction (smallm.hip)
         int taken = 0;
-        LowerArgs la;
-        la.ashift = p.next_ashift; la.K4 = p.next_K4; la.gs_log2 = p.next_gs_log2;   // (checked above; null: the call names no consumer)
-        la.x6 = p.nx6; la.K6 = p.next_K6; la.S = p.next_S;
         const int rc = launch_tile_splitk_fp6(L, X, X6, M, out, stream, K6, g_dev[dev].num_cu, &taken, &la);
         if (rc != FLEXIQ_OK) return rc;
         if (taken) {
@@ -154,6 +154,16 @@ extern "C" int flexiq_mixed_gemm_fp6(const flexiq_layer *L, const int8_t *X, con
         if (rc != FLEXIQ_OK) return rc;
         if (taken) {
             g_last_shape = -4;
+            return FLEXIQ_OK;
+        }
+    }
+
+    if (g_force_shape < 0) {   // all of at most 1280 channels as FP6: the weights of a block resident in registers (wreg6.hip)
+        int taken = 0;
+        const int rc = launch_wreg6(L, X6, M, out, stream, K6, &taken, &la);
+        if (rc != FLEXIQ_OK) return rc;
+        if (taken) {
+            g_last_shape = -7;
             return FLEXIQ_OK;
         }
     }
