@@ -10,13 +10,13 @@ namespace flexiq {
 namespace fp6 {
 
 constexpr int kNumShapes = 4;
-static const Shape *shapes()
+template <bool ALL6> static const Shape *shapes()
 {
     // (a 320 x 256 tile does not fit the register file next to the FP6 fragments)
-    static const Shape tab[kNumShapes] = {make_shape<2, 4, 4, 2>(),    // 256 x 256
-                                          make_shape<2, 4, 3, 2>(),    // 192 x 256
-                                          make_shape<2, 4, 2, 2>(),    // 128 x 256
-                                          make_shape<2, 4, 1, 2>()};   //  64 x 256
+    static const Shape tab[kNumShapes] = {make_shape<2, 4, 4, 2, ALL6>(),    // 256 x 256
+                                          make_shape<2, 4, 3, 2, ALL6>(),    // 192 x 256
+                                          make_shape<2, 4, 2, 2, ALL6>(),    // 128 x 256
+                                          make_shape<2, 4, 1, 2, ALL6>()};   //  64 x 256
     return tab;
 }
 
@@ -41,9 +41,9 @@ int prepare_fp6_kernels(int device)
     hipDeviceProp_t prop;
     FLEXIQ_HIP(hipGetDeviceProperties(&prop, device));
     d.num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    const Shape *tab = shapes();
-    for (int i = 0; i < kNumShapes; ++i)
-        FLEXIQ_HIP(hipFuncSetAttribute((const void *)tab[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, tab[i].lds));
+    for (const Shape *tab : {shapes<false>(), shapes<true>()})
+        for (int i = 0; i < kNumShapes; ++i)
+            FLEXIQ_HIP(hipFuncSetAttribute((const void *)tab[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, tab[i].lds));
     d.ready = true;
     return FLEXIQ_OK;
 }
@@ -169,7 +169,7 @@ extern "C" int flexiq_mixed_gemm_fp6(const flexiq_layer *L, const int8_t *X, con
     }
 
     const DeviceState &ds = g_dev[dev];
-    const Shape *tab = shapes();
+    const Shape *tab = K6 == L->C ? shapes<true>() : shapes<false>();
     int best = 0;
     if (g_force_shape >= 0) {
         best = g_force_shape;

@@ -19,7 +19,13 @@
 // channels (4-bit groups outside the FP6 prefix from the position-expanded copy with activations that arrive
 // lowered, 8-bit groups as they are).  Nothing is lowered or expanded in this kernel: every operand tile is a plain
 // copy from global memory straight into LDS (buffer loads that write LDS), three K-steps ahead of its use, into a
-// ring of four stages.  FP6 operands arrive packed by the producing layer (or by the stand-alone lowering kernel):
+// ring of four stages (five and six in the ALL6 builds, which hold no int8 operands).  What counts in an FP6 step, 512 matrix cycles of
+// a 256 x 256 tile, is what a wave does beside it: with the number of copies in flight known at run time only (a ladder of
+// branches), the step's scale words read from LDS in front of its first matrix instruction, and a wait for all LDS reads at its end, a step
+// took 600 cycles more than its matrix instructions.  Now the counts are constants in all but the last steps, the scale words are read in
+// the step before, their byte is an immediate, and reads stay in flight across the barrier.  Measured at r = 1, int8 out, us before and
+// after: 12608 x 4096 -> 1024 40.6 -> 32.5 (fp32 out 48.9 -> 39.9), 1576 x 4096 -> 1024 26.9 -> 17.7, 6304 x 3072 -> 768 24.8 -> 18.6; at r = 0.5
+// 12608 x 4096 -> 1024 51.9 -> 47.6.  (A ring of six stages alone, without the rest: 40.9.)  FP6 operands arrive packed by the producing layer (or by the stand-alone lowering kernel):
 //   * a K-step is 64 channels = two units of 32; the 32 codes of a (row, unit) are 24 bytes; the first 16 bytes of
 //     unit h form "plane h", the last 8 bytes of both units share "plane 2" (unit h in half h ^ ((row >> 4) & 1),
 //     which makes the 8-byte fragment reads of 32 consecutive rows hit 32 different bank pairs);
@@ -90,7 +96,8 @@ __device__ __forceinline__ void dma4(__amdgpu_buffer_rsrc_t r, void *dst, int vo
 #define FQ6_SPREAD6 1
 #define FQ6_SPREAD8 2
 
-template <int WAVES_M, int WAVES_N, int TM, int TN>
+// ALL6: every channel is on the FP6 path.  A stage then holds FP6 operands only, and LDS six of them.
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool ALL6>
 struct Cfg {
     static constexpr int NW = WAVES_M * WAVES_N;
     static_assert(NW == 8, "eight waves per block: two per SIMD");
@@ -103,8 +110,8 @@ struct Cfg {
     static constexpr int X8 = BM * 64;           // int8 activation tile, row-major
     static constexpr int STAGE8 = X8 + 4 * WP;
     static constexpr int STAGE6 = 3 * XP + 3 * WP;
-    static constexpr int STAGE = STAGE8 > STAGE6 ? STAGE8 : STAGE6;
-    static constexpr int NSTAGE = 4;
+    static constexpr int STAGE = ALL6 || STAGE6 > STAGE8 ? STAGE6 : STAGE8;
+    static constexpr int NSTAGE = ALL6 ? 6 : 4;
     static constexpr int RING = NSTAGE * STAGE;
     // scales, biases, consumer positions (per column); activation positions (192 entries: three copy instructions);
     // weight block scales: per wave two sets (the current and the next group of four K-steps) of TN x 64 registers' worth
@@ -120,11 +127,11 @@ struct Cfg {
     static constexpr int L8 = BM / 64 > 4 ? BM / 64 : 4;
 };
 
-template <int WAVES_M, int WAVES_N, int TM, int TN>
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool ALL6>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params p)
 {
-    using C_ = Cfg<WAVES_M, WAVES_N, TM, TN>;
-    constexpr int NW = C_::NW, BM = C_::BM, BN = C_::BN, XP = C_::XP, WP = C_::WP, X8 = C_::X8, STAGE = C_::STAGE;
+    using C_ = Cfg<WAVES_M, WAVES_N, TM, TN, ALL6>;
+    constexpr int NW = C_::NW, BM = C_::BM, BN = C_::BN, XP = C_::XP, WP = C_::WP, X8 = C_::X8, STAGE = C_::STAGE, NSTAGE = C_::NSTAGE;
     constexpr int NF = TM + TN, NMF = TM * TN;
     constexpr int L6 = C_::L6, L8 = C_::L8;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -167,7 +174,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
     // k-plane slot ^ ((row/4)%4)); 4 planes x BN/64 blocks of weights (wave - 4 = block, j = plane).
     static_assert(BN == 256 && NW == 8, "four weight blocks of 64 rows, one per wave 4..7");
     constexpr int RB = BM / 64;
-    constexpr int LMAX = L6 > L8 ? L6 : L8;
+    constexpr int LMAX = L6 > L8 ? L6 : L8, CX6 = (3 * RB + 3) / 4;
     const bool xwave = wave < 4;
     const int w4 = wave & 3;
     const int w4x_delta = p.U * 32 * p.Npad;   // from the 8-bit copy to the expanded 4-bit copy
@@ -184,13 +191,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
         cvo = lane * 16;
 #pragma unroll
         for (int j = 0; j < LMAX; ++j) {
-            const int i = w4 + 4 * j;
+            const int i = (w4 + 4 * j) % (3 * RB);   // (where the tile's copies do not divide by four, some are made twice: a count for all waves)
             const int rb = i % RB, pl = i / RB;
             cso[j] = xwave ? (int)(((m0 >> 6) + rb) * (int64_t)S * 3072) + pl * 1024 : (j * p.Npad + n0 + w4 * 64) * 16;
             cd[j] = xwave ? pl * XP + rb * 1024 : 3 * XP + j * WP + w4 * 1024;
         }
         cstep = xwave ? 3072 : 3 * p.Npad * 16;
-        ncopies = xwave ? (3 * RB - w4 + 3) / 4 : 3;
+        ncopies = xwave ? CX6 : 3;
         mode8 = false;
     };
     auto set_int8_copies = [&]() {
@@ -209,7 +216,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
     };
     // Copies of K-step t into `stage`: issue_begin() says how many this wave has (0 when the K loop is over) and
     // switches the tables at the first int8 step; issue_item() issues copy j.  issue() does all of them at once.
+    // (ALL6: beyond the last K-step the copies go on, of nothing: a window of size 0.)
     auto issue_begin = [&](int t) -> int {
+        if (ALL6) {
+            cdesc = __builtin_amdgcn_make_buffer_rsrc(xwave ? (void *)p.X6 : (void *)p.W6, 0, t >= S ? 0 : xwave ? (int)p.x6_bytes : S * 3 * p.Npad * 16, kRsrcFlags);
+            return ncopies;
+        }
         if (t >= S) return 0;
         if (t == S6) set_int8_copies();   // (t only ever grows: from here on every K-step is an int8 step)
         return ncopies;
@@ -227,22 +239,25 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
         for (int j = 0; j < LMAX; ++j) issue_item(t, j, n, stage);
         return n;
     };
-    // waits until at most n of this wave's loads are outstanding (n: one of a few wave-uniform values)
+    // Waits until at most n (x, w) copies of this wave are outstanding.  A run-time n costs a ladder of branches, 300 cycles of a K-step
+    // of 512 matrix cycles: only the last steps of a phase use it.
     auto wait_vm = [&](int n) {
         switch (n) {
-            case 0: __builtin_amdgcn_s_waitcnt(0x0070); break;
-            case 1: __builtin_amdgcn_s_waitcnt(0x0071); break;
-            case 2: __builtin_amdgcn_s_waitcnt(0x0072); break;
-            case 3: __builtin_amdgcn_s_waitcnt(0x0073); break;
-            case 4: __builtin_amdgcn_s_waitcnt(0x0074); break;
-            case 5: __builtin_amdgcn_s_waitcnt(0x0075); break;
-            case 6: __builtin_amdgcn_s_waitcnt(0x0076); break;
-            case 7: __builtin_amdgcn_s_waitcnt(0x0077); break;
-            case 8: __builtin_amdgcn_s_waitcnt(0x0078); break;
-            default: __builtin_amdgcn_s_waitcnt(0x0079); break;
+            case 0: __builtin_amdgcn_s_waitcnt(0x0f70); break;
+            case 1: __builtin_amdgcn_s_waitcnt(0x0f71); break;
+            case 2: __builtin_amdgcn_s_waitcnt(0x0f72); break;
+            case 3: __builtin_amdgcn_s_waitcnt(0x0f73); break;
+            default: __builtin_amdgcn_s_waitcnt(0x0f74); break;
         }
     };
-    static_assert(L6 + TN <= 9 && L8 + TN <= 9, "wait counts covered by wait_vm");
+    static_assert(L6 <= 4 && L8 <= 4, "copies of a K-step covered by wait_vm");
+    auto wait_xw = [&](auto x_, auto w_) {
+        constexpr int x = decltype(x_)::value, w = decltype(w_)::value;
+        static_assert(x <= 15 && w <= 15, "the low four bits of the counter");
+        if (x == w || xwave) __builtin_amdgcn_s_waitcnt(0x0f70 | x);
+        else __builtin_amdgcn_s_waitcnt(0x0f70 | w);
+    };
+    using std::integral_constant;
 
     // ---- prologue: tables (scales, biases, consumer positions per column, activation positions per group) and K-steps
     // 0, 1, 2 on their way, all straight into LDS
@@ -259,11 +274,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
         }
         if (wave < 3) dma4(ras, as_tab + wave * 64, (wave * 64 + lane) * 4, 0);   // (past the table: zeros)
     }
-    if (S6 > 0) set_fp6_copies();
+    // Block scales (E8M0 bytes).  Weights: per fragment column and lane (output channel, unit) one 32-bit word holds
+    // the bytes of four consecutive K-steps; a wave copies the words of its own columns straight into LDS a group of
+    // four steps ahead (no register is the target of a memory load inside the K loop, so no wait for such a register
+    // can ever drain the copies in flight) and reads the word of the current group at every step.
+    // Activations: one word per group of four steps, built from the position table.
+    const __amdgpu_buffer_rsrc_t rws = __builtin_amdgcn_make_buffer_rsrc((void *)p.W6S, 0, ((S + 3) >> 2) * p.Npad * 8, kRsrcFlags);
+    int *const ws_mine = ws_tab + wave * (2 * TN * 64);
+    auto fetch_wscales = [&](int grp) {   // words of group `grp` -> this wave's set grp % 2
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+            dma4(rws, ws_mine + ((grp & 1) * TN + a) * 64, ((n0 + (wn * TN + a) * 32 + (lane & 31)) * 2 + (lane >> 5)) * 4, grp * p.Npad * 8);
+    };
+    if (ALL6 || S6 > 0) fetch_wscales(0);   // (before the K-steps: the wait below leaves the later ones of those in flight)
+    if (ALL6 || S6 > 0) set_fp6_copies();
     else set_int8_copies();
-    (void)issue(0, lds);
-    (void)issue(1, lds + STAGE);
-    (void)issue(2, lds + 2 * STAGE);
+#pragma unroll
+    for (int t = 0; t < NSTAGE - 1; ++t) (void)issue(t, lds + t * STAGE);
 
     // ---- fragments
     const int fr = lane & 31, fh = lane >> 5;
@@ -297,19 +324,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
         x_hi[i].b = t.y;
     };
     auto op8 = [](const v4i &lo, const Hi2 &hi) { return (v8i){lo.x, lo.y, lo.z, lo.w, hi.a, hi.b, 0, 0}; };
-    // Block scales (E8M0 bytes).  Weights: per fragment column and lane (output channel, unit) one 32-bit word holds
-    // the bytes of four consecutive K-steps; a wave copies the words of its own columns straight into LDS a group of
-    // four steps ahead (no register is the target of a memory load inside the K loop, so no wait for such a register
-    // can ever drain the copies in flight) and reads the word of the current group at every step.
-    // Activations: one word per group of four steps, built from the position table.
-    const __amdgpu_buffer_rsrc_t rws = __builtin_amdgcn_make_buffer_rsrc((void *)p.W6S, 0, ((S + 3) >> 2) * p.Npad * 8, kRsrcFlags);
-    int *const ws_mine = ws_tab + wave * (2 * TN * 64);
-    auto fetch_wscales = [&](int grp) {   // words of group `grp` -> this wave's set grp % 2
-#pragma unroll
-        for (int a = 0; a < TN; ++a)
-            dma4(rws, ws_mine + ((grp & 1) * TN + a) * 64, ((n0 + (wn * TN + a) * 32 + fr) * 2 + fh) * 4, grp * p.Npad * 8);
-    };
-    if (S6 > 0) fetch_wscales(0);
 
     v16f accf[TN][TM];
 #pragma unroll
@@ -319,8 +333,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
 #pragma unroll
             for (int i = 0; i < 16; ++i) accf[a][b][i] = 0.0f;
 
-    // K-steps 0 and 1 have landed (and 2, the tables and the first weight scales)
-    __builtin_amdgcn_s_waitcnt(0x0070);
+    // K-steps 0 and 1 have landed, the tables and the first weight scales too
+    if constexpr (ALL6) wait_xw(integral_constant<int, (NSTAGE - 3) * CX6>{}, integral_constant<int, (NSTAGE - 3) * 3>{});
+    else __builtin_amdgcn_s_waitcnt(0x0070);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_s_barrier();
     // When int8 is the only scaled output, the table's scales and biases become the requantisation multiplier and
@@ -354,30 +369,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
             else __builtin_amdgcn_s_setprio(0);
         }
     };
-    int o_cur = 0, o_nx1 = STAGE, o_nx2 = 2 * STAGE, o_nx3 = 3 * STAGE;
+    int o_cur = 0, o_nx1 = STAGE, o_to = (NSTAGE - 1) * STAGE;   // stages of K-steps s, s + 1 and s + NSTAGE - 1
     auto rotate = [&]() {
-        const int t = o_cur;
-        o_cur = o_nx1; o_nx1 = o_nx2; o_nx2 = o_nx3; o_nx3 = t;
+        o_to = o_cur;
+        o_cur = o_nx1;
+        o_nx1 = o_nx1 == (NSTAGE - 1) * STAGE ? 0 : o_nx1 + STAGE;
     };
     int s = 0;
 
     // ---- FP6 phase.  Step s multiplies the fragments in register set `cur` (read during the previous step) and
     // reads those of step s + 1 into the other set (after the last FP6 step that read brings bytes nobody uses),
-    // while the copies of step s + 3 are issued.  The scale byte of step s is byte s % 4 of the scale registers.
-    int as_cur = as_of(0);
-    auto step6 = [&](v4i(&cur_lo)[TN], Hi2(&cur_hi)[TN], v4i(&nxt_lo)[TN], Hi2(&nxt_hi)[TN]) {
-        const unsigned char *nx1 = lds + o_nx1;
-        unsigned char *nx3 = lds + o_nx3;
-        // at the first step of a group of four: the scale words of the next group (older than this step's copies, so
-        // the wait at the end of the step, which lets only those stay in flight, covers them)
-        if ((s & 3) == 0) fetch_wscales((s >> 2) + 1);
-        const int ncp = issue_begin(s + 3);
-        const int issued = ncp;
-        const int sh = 8 * (s & 3);
-        int wsc[TN];
+    // while the copies of step s + NSTAGE - 1 are issued.  The scale byte of step s is byte s % 4 of the scale registers, whose words
+    // are read in the last step of the group before.  LEAN: the number of copies of the K-steps that may stay in flight is a constant.
+    int as_cur = as_of(0), wsc[TN];
+    auto read_wscales = [&](int grp) {
 #pragma unroll
-        for (int a = 0; a < TN; ++a) wsc[a] = ws_mine[(((s >> 2) & 1) * TN + a) * 64 + lane] >> sh;
-        const int asc = as_cur >> sh;
+        for (int a = 0; a < TN; ++a) wsc[a] = ws_mine[((grp & 1) * TN + a) * 64 + lane];
+    };
+    auto step6 = [&](auto byte_, auto lean_, v4i(&cur_lo)[TN], Hi2(&cur_hi)[TN], v4i(&nxt_lo)[TN], Hi2(&nxt_hi)[TN]) {
+        constexpr int BYTE = decltype(byte_)::value;   // s % 4
+        constexpr bool LEAN = decltype(lean_)::value;
+        const unsigned char *nx1 = lds + o_nx1;
+        unsigned char *to = lds + o_to;
+        // at the first step of a group of four: the scale words of the next group (older than the copies of the group's other three
+        // steps, so the waits at their ends cover them)
+        if (BYTE == 0) fetch_wscales((s >> 2) + 1);
+        const int ncp = issue_begin(s + NSTAGE - 1);
+        int wnx[TN], anx = 0;
         FQ6_SB();
 #pragma unroll
         for (int b = 0; b < TM; ++b)
@@ -385,18 +403,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
             for (int a = 0; a < TN; ++a) {
                 const int slot = b * TN + a;
 #pragma unroll
-                for (int j = 0; j < LMAX; ++j)   // the copies of K-step s + 3, spread over the first matrix instructions
+                for (int j = 0; j < LMAX; ++j)   // the copies of K-step s + NSTAGE - 1, spread over the first matrix instructions
                     if ((j * FQ6_SPREAD6 < NMF ? j * FQ6_SPREAD6 : NMF - 1) == slot) {
-                        issue_item(s + 3, j, ncp, nx3);
+                        issue_item(s + NSTAGE - 1, j, ncp, to);
                         FQ6_SB();
                     }
                 set_prio(slot, NMF);
                 accf[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(op8(cur_lo[a], cur_hi[a]), op8(x_lo[b], x_hi[b]), accf[a][b], 2, 2,
-                                                                             0, wsc[a], 0, asc);
+                                                                             BYTE, wsc[a], BYTE, as_cur);
                 FQ6_PIN(accf[a][b]);
                 FQ6_SB();
                 if (b == 0) {   // next step's weight fragments, early
                     read6w(nxt_lo, nxt_hi, a, nx1);
+                    FQ6_SB();
+                }
+                if (BYTE == 3 && slot == TN - 1) {   // the next group's scale words (in place since the step before last)
+#pragma unroll
+                    for (int k = 0; k < TN; ++k) wnx[k] = ws_mine[((((s >> 2) + 1) & 1) * TN + k) * 64 + lane];
+                    anx = as_of(s + 1);
                     FQ6_SB();
                 }
                 if (a == TN - 1) {   // this activation fragment is done for this step
@@ -404,36 +428,57 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
                     FQ6_SB();
                 }
             }
-        if ((s & 3) == 3) as_cur = as_of(s + 1);
-        // The copies of K-step s + 2 have landed (this step's own may stay in flight); nothing else has to be
+        if constexpr (BYTE == 3) {
+#pragma unroll
+            for (int k = 0; k < TN; ++k) wsc[k] = wnx[k];
+            as_cur = anx;
+        }
+        // The copies of K-step s + 2 have landed (later ones may stay in flight); nothing else has to be
         // complete at the barrier: the fragment reads issued above go to the next step's stage, which no copy touches
         // for two more steps, and every register they fill is waited for where it is used.
-        wait_vm(issued);
+        if constexpr (LEAN) wait_xw(integral_constant<int, (NSTAGE - 3) * CX6>{}, integral_constant<int, (NSTAGE - 3) * 3>{});
+        else wait_vm(ncp);
         __builtin_amdgcn_s_barrier();
         FQ6_SB();
         rotate();
         ++s;
     };
-    if (S6 > 0) {
+    if (ALL6 || S6 > 0) {
+        read_wscales(0);
 #pragma unroll
         for (int k = 0; k < TN; ++k) read6w(wa_lo, wa_hi, k, lds);
 #pragma unroll
         for (int k = 0; k < TM; ++k) read6x(k, lds);
-        while (s + 1 < S6) {
-            step6(wa_lo, wa_hi, wb_lo, wb_hi);
-            step6(wb_lo, wb_hi, wa_lo, wa_hi);
+        auto group = [&](auto lean, int steps) {   // up to four steps from a multiple of four on
+            step6(integral_constant<int, 0>{}, lean, wa_lo, wa_hi, wb_lo, wb_hi);
+            if (steps > 1) step6(integral_constant<int, 1>{}, lean, wb_lo, wb_hi, wa_lo, wa_hi);
+            if (steps > 2) step6(integral_constant<int, 2>{}, lean, wa_lo, wa_hi, wb_lo, wb_hi);
+            if (steps > 3) step6(integral_constant<int, 3>{}, lean, wb_lo, wb_hi, wa_lo, wa_hi);
+        };
+        using T = integral_constant<bool, true>;
+        using F = integral_constant<bool, false>;
+        // (the copies of step s + 3 are those of an FP6 step up to S6 - 4)
+        while (s + (ALL6 ? 4 : 7) <= S6) group(T{}, 4);
+        if constexpr (ALL6) {
+            if (s < S6) group(T{}, S6 - s);
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // (copies of nothing)
+        } else {
+            if (s < S6) group(F{}, S6 - s);
+            if (s < S6) group(F{}, S6 - s);
         }
-        if (s < S6) step6(wa_lo, wa_hi, wb_lo, wb_hi);
     }
 
-    // ---- fp32 -> int32 in place: the sums are exact integers below 2^24
+    // ---- fp32 -> int32 in place: the sums are exact integers below 2^24 (ALL6: the epilogue takes them as they are)
     v16i acc[TN][TM];
+    if constexpr (!ALL6) {
 #pragma unroll
-    for (int a = 0; a < TN; ++a)
+        for (int a = 0; a < TN; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
+            for (int b = 0; b < TM; ++b)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = (int)accf[a][b][i];
+                for (int i = 0; i < 16; ++i) acc[a][b][i] = (int)accf[a][b][i];
+    }
+    auto sum = [&](int a, int b, int e) { return ALL6 ? accf[a][b][e] : (float)acc[a][b][e]; };
 
     // ---- int8 phase: two k-halves per K-step, register set ga for the first, gb for the second (the read ahead of
     // the last step brings bytes nobody uses)
@@ -442,13 +487,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
         if (i < TN) f[i] = *reinterpret_cast<const v4i *>(stage + w8_frag + kh * 2 * WP + i * 512);
         else f[i] = *reinterpret_cast<const v4i *>(stage + (kh ? x8_frag1 : x8_frag0) + (i - TN) * 2048);
     };
-    if (s < S) {
+    if constexpr (!ALL6) if (s < S) {
 #pragma unroll
         for (int k = 0; k < NF; ++k) read8(ga, k, lds + o_cur, 0);
-        while (s < S) {
+        auto step8 = [&](auto lean) {
             const unsigned char *cur = lds + o_cur;
             const unsigned char *nx1 = lds + o_nx1;
-            unsigned char *nx3 = lds + o_nx3;
+            unsigned char *nx3 = lds + o_to;
             const int issued = issue_begin(s + 3);
             FQ6_SB();
 #pragma unroll
@@ -477,12 +522,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
                                 FQ6_SB();
                             }
                     }
-            wait_vm(issued);
+            if constexpr (decltype(lean)::value) wait_xw(integral_constant<int, RB>{}, integral_constant<int, 4>{});
+            else __builtin_amdgcn_s_waitcnt(0x0f70);   // (none issued)
             __builtin_amdgcn_s_barrier();
             FQ6_SB();
             rotate();
             ++s;
-        }
+        };
+        while (s + 3 < S) step8(integral_constant<bool, true>{});
+        while (s < S) step8(integral_constant<bool, false>{});
     }
 
     // ---- epilogue.  Lane: output row m = tile row 32 b + fr of its wave; per accumulator quad g the four
@@ -506,10 +554,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
 #pragma unroll
                 for (int b = 0; b < TM; ++b) {
                     uint32_t qw = 0;
-                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf((float)acc[a][b][4 * g], mu.x, ad.x), 0, qw);
-                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf((float)acc[a][b][4 * g + 1], mu.y, ad.y), 1, qw);
-                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf((float)acc[a][b][4 * g + 2], mu.z, ad.z), 2, qw);
-                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf((float)acc[a][b][4 * g + 3], mu.w, ad.w), 3, qw);
+                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(sum(a, b, 4 * g), mu.x, ad.x), 0, qw);
+                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(sum(a, b, 4 * g + 1), mu.y, ad.y), 1, qw);
+                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(sum(a, b, 4 * g + 2), mu.z, ad.z), 2, qw);
+                    qw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(sum(a, b, 4 * g + 3), mu.w, ad.w), 3, qw);
                     qrow[b][g] = qw ^ 0x80808080u;
                 }
             }
@@ -546,13 +594,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
                 const float4 cs = *reinterpret_cast<const float4 *>(cs_tab + nl);
                 const float4 bi = *reinterpret_cast<const float4 *>(cs_tab + BN + nl);
                 const float csv[4] = {cs.x, cs.y, cs.z, cs.w}, biv[4] = {bi.x, bi.y, bi.z, bi.w};
-                const int iv[4] = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+                const float fv[4] = {sum(a, b, 4 * g), sum(a, b, 4 * g + 1), sum(a, b, 4 * g + 2), sum(a, b, 4 * g + 3)};
+                auto whole = [&](int i) { return ALL6 ? (int)fv[i] : acc[a][b][4 * g + i]; };
                 uint32_t qw = 0;
                 if (want_q) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const float mul = pre_scaled ? csv[i] : csv[i] * p.r_out, add = pre_scaled ? biv[i] : biv[i] * p.r_out + 128.0f;
-                        float t = __builtin_fmaf((float)iv[i], mul, add);
+                        float t = __builtin_fmaf(fv[i], mul, add);
                         // for the consumer's 4-bit channels: clamp to its 4-bit range at its position
                         if (to6 || low8) t = __builtin_amdgcn_fmed3f(t, (float)(128 - (8 << sp)), (float)(127 + (8 << sp)));
                         qw = __builtin_amdgcn_cvt_pk_u8_f32(t, i, qw);
@@ -565,20 +614,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
                 if (!m_ok || n >= p.N) continue;
                 const int64_t o = m * p.N + n;
                 if (n_vec) {
-                    if (want_acc) *reinterpret_cast<v4i *>(p.acc + o) = (v4i){iv[0], iv[1], iv[2], iv[3]};
+                    if (want_acc) *reinterpret_cast<v4i *>(p.acc + o) = (v4i){whole(0), whole(1), whole(2), whole(3)};
                     if (want_y) {
                         float4 y;
-                        y.x = __builtin_fmaf((float)iv[0], csv[0], biv[0]);
-                        y.y = __builtin_fmaf((float)iv[1], csv[1], biv[1]);
-                        y.z = __builtin_fmaf((float)iv[2], csv[2], biv[2]);
-                        y.w = __builtin_fmaf((float)iv[3], csv[3], biv[3]);
+                        y.x = __builtin_fmaf(fv[0], csv[0], biv[0]);
+                        y.y = __builtin_fmaf(fv[1], csv[1], biv[1]);
+                        y.z = __builtin_fmaf(fv[2], csv[2], biv[2]);
+                        y.w = __builtin_fmaf(fv[3], csv[3], biv[3]);
                         *reinterpret_cast<float4 *>(p.y + o) = y;
                     }
                     if (want_q && !q_rows) *reinterpret_cast<uint32_t *>(p.q + o) = qw;
                 } else {
                     for (int i = 0; i < 4 && n + i < p.N; ++i) {
-                        if (want_acc) p.acc[o + i] = iv[i];
-                        if (want_y) p.y[o + i] = __builtin_fmaf((float)iv[i], csv[i], biv[i]);
+                        if (want_acc) p.acc[o + i] = whole(i);
+                        if (want_y) p.y[o + i] = __builtin_fmaf(fv[i], csv[i], biv[i]);
                         if (want_q) p.q[o + i] = (int8_t)((qw >> (8 * i)) & 0xFF);
                     }
                 }
@@ -629,11 +678,11 @@ struct Shape {
     int BM, BN, threads, lds;
     kernel_fn fn;
 };
-template <int WAVES_M, int WAVES_N, int TM, int TN>
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool ALL6>
 inline Shape make_shape()
 {
-    using C_ = Cfg<WAVES_M, WAVES_N, TM, TN>;
-    return Shape{C_::BM, C_::BN, C_::NT, C_::LDS_BYTES, k_fp6<WAVES_M, WAVES_N, TM, TN>};
+    using C_ = Cfg<WAVES_M, WAVES_N, TM, TN, ALL6>;
+    return Shape{C_::BM, C_::BN, C_::NT, C_::LDS_BYTES, k_fp6<WAVES_M, WAVES_N, TM, TN, ALL6>};
 }
 
 }  // namespace fp6
