@@ -2,10 +2,18 @@
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional
 
 import numpy as np
+
+import torch   # noqa: F401  (its libraries are what _calls is linked with)
+
+try:
+    from . import _calls   # the run-time entry points as native calls (csrc/calls.cpp); the functions below serve what it does not
+except ImportError:   # not built for this torch: they serve every call
+    _calls = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libflexiq.so")   # built in-tree; there is no non-HIP path
@@ -91,7 +99,14 @@ def load():
     for name in exported_symbols():
         getattr(L, name)
     _lib = L
+    if _calls is not None:
+        _calls.connect({name: C.cast(getattr(L, name), C.c_void_p).value for name in exported_symbols()}, _check)
     return L
+
+
+def _native(function):
+    """The entry point as a native call where there is one."""
+    return function if _calls is None else functools.update_wrapper(_calls.wrap(function), function)
 
 
 def _check(rc: int):
@@ -128,16 +143,18 @@ def _f32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.float32)
 
 
-class Layer:
+class Layer(object if _calls is None else _calls.Handle):
     """Owns a flexiq_layer handle; frees it on garbage collection."""
 
     def __init__(self, handle: int, N: int, Cc: int, R: int, S: int, group_size: int):
         self._h = C.c_void_p(handle)
+        self._ptr = handle   # (for native calls; 0 once freed)
         self.N, self.C, self.R, self.S, self.group_size = N, Cc, R, S, group_size
 
     def __del__(self):
         try:
             if self._h and _lib is not None:
+                self._ptr = 0
                 _lib.flexiq_layer_free(self._h)
                 self._h = None
         except Exception:
@@ -198,6 +215,7 @@ def flexiq_set_ratio(layer: Layer, r: float) -> int:
     return k4.value
 
 
+@_native
 def flexiq_quantize_act(x, scale: float, out=None):
     import torch
     assert x.is_cuda and x.dtype == torch.float32 and x.is_contiguous()
@@ -216,6 +234,7 @@ def flexiq_bitlower(src, group_size: int, shifts, per_row: bool, mode: int = 0):
     return dst
 
 
+@_native
 def flexiq_dynamic_positions(layer: Layer, X) -> None:
     """Scan X (int8, [..., C] contiguous, stored channel order) for the run-time extraction positions of the
     groups that are 4-bit under the current ratio; later GEMM / conv calls on the handle use them."""
@@ -248,6 +267,7 @@ def flexiq_layer_positions(layer: Layer) -> np.ndarray:
     return out
 
 
+@_native
 def flexiq_permute_channels(layer: Layer, src):
     import torch
     assert src.is_cuda and src.dtype == torch.int8 and src.is_contiguous()
@@ -283,6 +303,7 @@ def flexiq_packed4_bytes(layer: Layer, M: int) -> int:
     return n
 
 
+@_native
 def flexiq_lower_packed4(layer: Layer, X, x4=None):
     """Stand-alone producer of the packed 4-bit activations (uint8 cuda [M][C/2])."""
     import torch
@@ -294,6 +315,7 @@ def flexiq_lower_packed4(layer: Layer, X, x4=None):
     return x4
 
 
+@_native
 def flexiq_mixed_gemm_packed4(layer: Layer, X, x4, acc: bool = False, y: bool = False, q: bool = False, out_scale: float = 1.0,
                               bufs: Optional[dict] = None, lower_for: Optional[Layer] = None, x4_out=None):
     """flexiq_mixed_gemm with the leading 4-bit channels read from packed codes.  x4_out: with lower_for, the consumer's
@@ -308,6 +330,7 @@ def flexiq_mixed_gemm_packed4(layer: Layer, X, x4, acc: bool = False, y: bool = 
     return res
 
 
+@_native
 def flexiq_lower_fp6(layer: Layer, X, x6=None, need_xlow: Optional[bool] = None):
     """Stand-alone producer of the FP6 activations: returns (x6, xlow).  xlow is X itself unless some 4-bit channels
     lie outside the FP6 prefix (then a copy with those channels lowered)."""
@@ -327,6 +350,7 @@ def flexiq_lower_fp6(layer: Layer, X, x6=None, need_xlow: Optional[bool] = None)
     return x6, (xlow if xlow is not None else X)
 
 
+@_native
 def flexiq_mixed_gemm_fp6(layer: Layer, X, x6, acc: bool = False, y: bool = False, q: bool = False,
                           out_scale: float = 1.0, bufs: Optional[dict] = None, lower_for: Optional[Layer] = None,
                           x6_out=None):
@@ -365,6 +389,7 @@ def _outs(shape, device, want_acc, want_y, want_q, out_scale, bufs, lower_for=No
     return o, {"acc": acc, "y": y, "q": q}
 
 
+@_native
 def flexiq_mixed_gemm(layer: Layer, X, acc: bool = False, y: bool = False, q: bool = False,
                       out_scale: float = 1.0, bufs: Optional[dict] = None, lower_for: Optional[Layer] = None,
                       scan_for: Optional[Layer] = None, x4_out=None):
@@ -381,6 +406,7 @@ def flexiq_mixed_gemm(layer: Layer, X, acc: bool = False, y: bool = False, q: bo
     return res
 
 
+@_native
 def flexiq_mixed_conv_implicit(layer: Layer, X, stride: int, pad: int, acc: bool = False, y: bool = False,
                                q: bool = False, out_scale: float = 1.0, bufs: Optional[dict] = None,
                                lower_for: Optional[Layer] = None, scan_for: Optional[Layer] = None):

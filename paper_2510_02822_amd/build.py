@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflexiq.so")
+CALLS = os.path.join(HERE, "_calls.so")   # Python's way into the run-time entry points (csrc/calls.cpp), against this torch
 NUM_TILE_SHAPES = 15
 # (source, object, extra flags): the kernel of every tile shape is a translation unit of its own
 UNITS = [("pack.hip", "pack.o", []), ("gemm.hip", "gemm.o", []), ("fp6_gemm.hip", "fp6_gemm.o", []),
@@ -20,6 +22,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
+def _calls_command():
+    import torch
+    T = os.path.dirname(torch.__file__)
+    inc = [os.path.join(T, "include"), os.path.join(T, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"],
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), os.path.join(ROOT, "include")]
+    return ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *sum((["-isystem", i] for i in inc[:-1]), []), "-I", inc[-1],
+            os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L", os.path.join(T, "lib"), "-lc10", "-ltorch_cpu", "-lc10_hip", "-ltorch_python"]
+
+
 def build(verbose: bool = False, extra=()) -> str:
     objs = []
     procs = []
@@ -28,6 +40,8 @@ def build(verbose: bool = False, extra=()) -> str:
         cmd = ["hipcc", *FLAGS, *defs, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    cmd = _calls_command()
+    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for cmd, pr in procs:
         out, _ = pr.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)

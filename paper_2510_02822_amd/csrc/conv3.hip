@@ -416,8 +416,7 @@ int launch_conv3(const flexiq_layer *L, const int8_t *X, int B, int H, int W, co
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
     void (*fn)(const Params) = units == 2 ? (q_only ? k_conv3<2, true> : k_conv3<2, false>) : (q_only ? k_conv3<4, true> : k_conv3<4, false>);
     if (lowering) fn = units == 2 ? k_conv3<2, true, true> : k_conv3<4, true, true>;
-    hipLaunchKernelGGL(fn, dim3((unsigned)gx64, (unsigned)gy), dim3(64 * (kWaves + 1)), lds, (hipStream_t)stream_, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(fn, dim3((unsigned)gx64, (unsigned)gy), dim3(64 * (kWaves + 1)), lds, stream_, p));
     g_last = 1;
     return FLEXIQ_OK;
 }

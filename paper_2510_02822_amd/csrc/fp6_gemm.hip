@@ -194,7 +194,6 @@ extern "C" int flexiq_mixed_gemm_fp6(const flexiq_layer *L, const int8_t *X, con
     p.tiles_n = (L->N + sh.BN - 1) / sh.BN;
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
     if (tiles > 0x7fffffff) return FLEXIQ_EINVAL;
-    hipLaunchKernelGGL(sh.fn, dim3((unsigned)tiles), dim3(sh.threads), sh.lds, (hipStream_t)stream, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(sh.fn, dim3((unsigned)tiles), dim3(sh.threads), sh.lds, stream, p));
     return FLEXIQ_OK;
 }

@@ -505,8 +505,7 @@ static int launch_any(const flexiq_layer *L, const int8_t *X, int B, int H, int 
     p.wn_log2 = __builtin_ctz(pl.wn); p.wmn_log2 = __builtin_ctz(pl.wm * pl.wn); p.wk = pl.wk;
     p.dBand = div(8 * p.ncb); p.dTail = div(p.tiles % 8 ? p.tiles % 8 : 1);
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
-    hipLaunchKernelGGL(kernel(pl.fr, taps, q_only, lowering), dim3((unsigned)(p.tiles * p.ncb)), dim3(64 * pl.wm * pl.wn * pl.wk), (size_t)c.lds, (hipStream_t)stream_, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(kernel(pl.fr, taps, q_only, lowering), dim3((unsigned)(p.tiles * p.ncb)), dim3(64 * pl.wm * pl.wn * pl.wk), (size_t)c.lds, stream_, p));
     g_last = 1 + c.shape;
     return FLEXIQ_OK;
 }

@@ -811,8 +811,7 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
             case 3: fn = cg == 4 ? k_few_rows_dot<3, 4> : k_few_rows_dot<3, 1>; break;
             default: fn = cg == 4 ? k_few_rows_dot<4, 4> : k_few_rows_dot<4, 1>; break;
             }
-            hipLaunchKernelGGL(fn, dim3((unsigned)((ncg + cg - 1) / cg)), dim3(64 * nw), lds, (hipStream_t)stream, p);
-            FLEXIQ_HIP(hipGetLastError());
+            FLEXIQ_HIP(launch_kernel(fn, dim3((unsigned)((ncg + cg - 1) / cg)), dim3(64 * nw), lds, stream, p));
             *taken = 2;
             g_last_rows = 2;
             return FLEXIQ_OK;
@@ -844,8 +843,7 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     void (*fn)(const RowsParams) =
         mf == 1 ? (p4 ? (coop ? k_few_rows<1, true, false, true> : k_few_rows<1, false, false, true>) : (coop ? k_few_rows<1, true> : k_few_rows<1, false>))
                 : (mf == 2 ? k_few_rows<2, false> : (mf == 3 ? k_few_rows<3, false> : k_few_rows<4, false>));
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * nw), lds, (hipStream_t)stream, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(fn, dim3(blocks), dim3(64 * nw), lds, stream, p));
     *taken = 1;
     g_last_rows = 1;
     g_last_codes = p4;
@@ -882,8 +880,7 @@ int launch_few_rows_fp6(const flexiq_layer *L, const int8_t *X, const uint8_t *X
     const int nw = (int)blocks >= 2 * num_cu ? 4 : (items >= 12 ? 16 : (items >= 6 ? 8 : 4));
     const size_t lds = (size_t)nw * mf * 64 * 16;
     void (*fn)(const RowsParams) = mf == 1 ? k_few_rows<1, false, true> : (mf == 2 ? k_few_rows<2, false, true> : (mf == 3 ? k_few_rows<3, false, true> : k_few_rows<4, false, true>));
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * nw), lds, (hipStream_t)stream, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(fn, dim3(blocks), dim3(64 * nw), lds, stream, p));
     *taken = 1;
     g_last_rows = 3;
     g_last_codes = false;
@@ -950,16 +947,17 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
         if (X6 && lower->x6) { p.nx6 = lower->x6; p.next_K6 = lower->K6; p.next_S = lower->S; }
     }
     const dim3 grid((unsigned)((L->N + tc - 1) / tc), (unsigned)((M + tr - 1) / tr));
+    hipError_t err;
     if (X6) {
         p.X6 = X6; p.W6 = L->d_w6; p.W6S = L->d_w6s;
         p.s6 = K6 / 64;
-        if (shape == 0) hipLaunchKernelGGL((k_tile_splitk<4, 4, 8, 2, true>), grid, dim3(512), lds, (hipStream_t)stream, p);
-        else if (shape == 1) hipLaunchKernelGGL((k_tile_splitk<2, 4, 8, 4, true>), grid, dim3(512), lds / 2, (hipStream_t)stream, p);   // (eight waves: registers)
-        else hipLaunchKernelGGL((k_tile_splitk<2, 2, 16, 4, true>), grid, dim3(1024), lds, (hipStream_t)stream, p);
-    } else if (shape == 0) hipLaunchKernelGGL((k_tile_splitk<4, 4, 8, 2>), grid, dim3(512), lds, (hipStream_t)stream, p);
-    else if (shape == 1) hipLaunchKernelGGL((k_tile_splitk<2, 4, 16, 2>), grid, dim3(1024), lds, (hipStream_t)stream, p);
-    else hipLaunchKernelGGL((k_tile_splitk<2, 2, 16, 4>), grid, dim3(1024), lds, (hipStream_t)stream, p);
-    FLEXIQ_HIP(hipGetLastError());
+        if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2, true>, grid, dim3(512), lds, stream, p);
+        else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 8, 4, true>, grid, dim3(512), lds / 2, stream, p);   // (eight waves: registers)
+        else err = launch_kernel(k_tile_splitk<2, 2, 16, 4, true>, grid, dim3(1024), lds, stream, p);
+    } else if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2>, grid, dim3(512), lds, stream, p);
+    else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 16, 2>, grid, dim3(1024), lds, stream, p);
+    else err = launch_kernel(k_tile_splitk<2, 2, 16, 4>, grid, dim3(1024), lds, stream, p);
+    FLEXIQ_HIP(err);
     *taken = 1 + shape;
     g_last_tile_splitk = 1 + shape;
     g_last_rows = 0;

@@ -635,8 +635,7 @@ int launch_stream(const flexiq_layer *L, const int8_t *X, int64_t M, const flexi
         else if (p.units == 4) fn = nt == 2 ? FQ_R(2, 4) : (nt == 4 ? FQ_R(4, 4) : FQ_R(8, 4));
         else fn = nt == 2 ? FQ_R(2, 8) : (nt == 4 ? FQ_R(4, 8) : FQ_R(8, 8));
 #undef FQ_R
-        hipLaunchKernelGGL(fn, dim3((unsigned)gx64, gy), dim3(64 * rp.waves), lds, (hipStream_t)stream_, p);
-        FLEXIQ_HIP(hipGetLastError());
+        FLEXIQ_HIP(launch_kernel(fn, dim3((unsigned)gx64, gy), dim3(64 * rp.waves), lds, stream_, p));
         *taken = 1;
         g_last = 2;
         return FLEXIQ_OK;
@@ -665,8 +664,7 @@ int launch_stream(const flexiq_layer *L, const int8_t *X, int64_t M, const flexi
     else if (p.units == 4) fn = nt == 2 ? FQ_Q(2, 4, 2) : (nt == 4 ? FQ_Q(4, 4, 2) : FQ_Q(8, 4, 2));
     else fn = nt == 2 ? FQ_Q(2, 8, 2) : (nt == 4 ? FQ_Q(4, 8, 2) : FQ_Q(8, 8, 2));
 #undef FQ_Q
-    hipLaunchKernelGGL(fn, dim3(gx, gy), dim3(256 * cw), lds, (hipStream_t)stream_, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(fn, dim3(gx, gy), dim3(256 * cw), lds, stream_, p));
     *taken = 1;
     g_last = 1;
     return FLEXIQ_OK;

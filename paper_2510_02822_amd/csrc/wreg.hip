@@ -472,8 +472,7 @@ int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
     const Out kind = lowering ? kLowered : (q_only ? kCodes : (out->y && !out->q && !out->acc && (L->N & 3) == 0 ? kFloats : kAny));
     const size_t lds = kTabBytes + (size_t)slots(nu) * stage_bytes(nu);
-    hipLaunchKernelGGL(kernel(nu, kind, p.n_low > 0, p.units == nu), dim3((unsigned)(p.ncb * p.groups)), dim3(64 * kWaves), lds, (hipStream_t)stream_, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(kernel(nu, kind, p.n_low > 0, p.units == nu), dim3((unsigned)(p.ncb * p.groups)), dim3(64 * kWaves), lds, stream_, p));
     *taken = 1;
     g_last = 1;
     return FLEXIQ_OK;

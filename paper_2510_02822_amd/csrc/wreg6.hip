@@ -463,8 +463,7 @@ int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flex
     }
     const Out kind = chain ? kChain : (q_only ? kCodes : (out->y && !out->q && !out->acc && (L->N & 3) == 0 ? kFloats : kAny));
     const size_t lds = kTabBytes + (size_t)slots(ns) * stage_bytes(ns);
-    hipLaunchKernelGGL(kernel(ns, kind), dim3((unsigned)(p.ncb * p.groups)), dim3(64 * kWaves), lds, (hipStream_t)stream, p);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(kernel(ns, kind), dim3((unsigned)(p.ncb * p.groups)), dim3(64 * kWaves), lds, stream, p));
     *taken = 1;
     g_last = 1;
     return FLEXIQ_OK;

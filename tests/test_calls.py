@@ -1,0 +1,102 @@
+"""The native calls of the binding (csrc/calls.cpp) against the functions of binding.py that they stand for: the same results, the same
+refusals."""
+import inspect
+
+import numpy as np
+import pytest
+
+import workloads
+from helpers import both_layers
+
+CALLS = ["flexiq_mixed_gemm", "flexiq_mixed_gemm_fp6", "flexiq_mixed_gemm_packed4", "flexiq_mixed_conv_implicit", "flexiq_lower_fp6", "flexiq_lower_packed4",
+         "flexiq_quantize_act", "flexiq_permute_channels", "flexiq_dynamic_positions"]
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_calls_are_native_and_keep_their_signature(name):
+    import paper_2510_02822_amd as fq
+    f = getattr(fq, name)
+    assert fq.binding._calls is not None and type(f).__name__ == "Call" and f.__name__ == name and f.__doc__ == f.__wrapped__.__doc__
+    assert str(inspect.signature(f)) == str(inspect.signature(f.__wrapped__))
+
+
+def test_what_a_native_call_does_not_serve():
+    import torch
+    import paper_2510_02822_amd as fq
+    fq.load()
+    freed = fq.Layer(0, 4, 64, 1, 1, 32)
+    x = torch.zeros(2, 64, dtype=torch.int8)   # not on a GPU
+    bad = [(fq.flexiq_mixed_gemm, (freed, x), {}, AssertionError), (fq.flexiq_mixed_gemm, (), {}, TypeError), (fq.flexiq_mixed_gemm, (freed, x), {"Q": True}, TypeError),
+           (fq.flexiq_mixed_gemm, (freed, x), {"X": x}, TypeError), (fq.flexiq_mixed_gemm, (freed, "x"), {}, AttributeError), (fq.flexiq_mixed_gemm, (freed,) * 12, {}, TypeError),
+           (fq.flexiq_mixed_gemm_fp6, (freed, x), {}, TypeError), (fq.flexiq_mixed_conv_implicit, (freed, x, 0, 0), {}, AssertionError),
+           (fq.flexiq_quantize_act, (torch.zeros(3), 1.0), {}, AssertionError), (fq.flexiq_permute_channels, (freed, x), {}, AssertionError),
+           (fq.flexiq_dynamic_positions, (freed, x), {}, AssertionError), (fq.flexiq_lower_fp6, (freed, x), {}, AssertionError), (fq.flexiq_lower_packed4, (freed, x), {}, AssertionError)]
+    for f, args, kw, error in bad:
+        for g in (f, f.__wrapped__):
+            with pytest.raises(error):
+                g(*args, **kw)
+
+
+@pytest.mark.gpu
+def test_same_results_as_the_functions_they_stand_for():
+    import torch
+    import paper_2510_02822_amd as fq
+    dev = torch.device("cuda:0")
+    first, second, cv = (workloads.make_linear("calls", 31, 1, 70, 128, 256, 32), workloads.make_linear("calls2", 31, 2, 70, 256, 64, 32),
+                         workloads.make_conv("calls3", 31, 3, 2, 9, 7, 64, 64, 3, 3, 2, 1, 32))
+    _, h2, _ = both_layers(second)
+    x_scale = float(np.abs(first.Xcal).max() / 127)
+    h1 = fq.flexiq_quantize_pack(first.W, np.abs(first.Xcal).max(0), x_scale, 32, bias=first.bias, out_perm=h2.info()["perm"])
+    _, hc, sc = both_layers(cv)
+    for h in (h1, h2, hc):
+        fq.flexiq_set_ratio(h, 0.75)
+    xf = torch.from_numpy(first.X).to(dev)
+    native = {n: getattr(fq, n) for n in CALLS}
+    plain = {n: getattr(fq, n).__wrapped__ for n in CALLS}
+
+    def run(f):
+        got = []
+        q = f["flexiq_quantize_act"](xf, x_scale)
+        own = torch.empty_like(q)
+        assert f["flexiq_quantize_act"](xf, scale=x_scale, out=own) is own and torch.equal(own, q)
+        x = f["flexiq_permute_channels"](h1, q)
+        x6, xlow = f["flexiq_lower_fp6"](h1, x)
+        mine = torch.zeros_like(x6)
+        a, b = f["flexiq_lower_fp6"](h1, x, x6=mine, need_xlow=True)
+        assert a is mine and b is not x and torch.equal(b, xlow)
+        with pytest.raises(fq.FlexiqError):   # (a 4-bit group of 32 is left over: its channels have to be lowered somewhere)
+            f["flexiq_lower_fp6"](h1, x, need_xlow=False)
+        x4 = f["flexiq_lower_packed4"](h1, x)
+        got += [q, x, xlow, x4[:, :32]]   # (of 96 4-bit channels 64 are packed)
+        for kw in ({"acc": True}, {"y": True, "q": True, "out_scale": 0.25}, {"q": True, "out_scale": 0.25, "lower_for": h2},
+                   {"q": True, "out_scale": np.float32(0.5)}, {"acc": 1, "out_scale": 2}):   # (the last two: not served natively)
+            got += list(f["flexiq_mixed_gemm"](h1, x, **kw).values())
+            got += list(f["flexiq_mixed_gemm_fp6"](h1, xlow, x6, **kw).values())
+            got += list(f["flexiq_mixed_gemm_packed4"](h1, x, x4, **kw).values())
+        bufs = {"y": torch.zeros(70, 256, device=dev)}
+        out = f["flexiq_mixed_gemm"](h1, x, False, True, bufs=bufs, out_scale=1.0)
+        assert list(out) == ["acc", "y", "q"] and out["y"] is bufs["y"] and out["acc"] is None and out["q"] is None
+        got.append(out["y"])
+        n6 = torch.zeros(fq.flexiq_fp6_bytes(h2, 70), dtype=torch.uint8, device=dev)
+        n4 = torch.zeros(70, 128, dtype=torch.uint8, device=dev)
+        f["flexiq_mixed_gemm_fp6"](h1, xlow, x6, q=True, out_scale=0.25, lower_for=h2, x6_out=n6)
+        f["flexiq_mixed_gemm"](h1, x, q=True, out_scale=0.25, lower_for=h2, x4_out=n4)
+        f["flexiq_mixed_gemm"](h1, x, q=True, out_scale=0.25, scan_for=h2)
+        fq.flexiq_static_positions(h2)
+        xc = torch.from_numpy(np.ascontiguousarray(np.clip(np.rint(cv.X / sc), -127, 127).astype(np.int8))).to(dev)
+        got += [n6, n4] + list(f["flexiq_mixed_conv_implicit"](hc, xc, 2, 1, q=True, y=True, out_scale=0.25).values())
+        assert f["flexiq_dynamic_positions"](h1, x) is None
+        got.append(torch.from_numpy(fq.flexiq_layer_positions(h1).astype(np.int32)))
+        fq.flexiq_static_positions(h1)
+        for bad in ({"q": True, "out_scale": -1.0}, {}, {"q": True, "lower_for": hc}):   # refused by the library
+            with pytest.raises(fq.FlexiqError):
+                f["flexiq_mixed_gemm"](h1, x, **bad)
+        other = torch.cuda.Stream()
+        other.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(other):
+            z = f["flexiq_mixed_gemm"](h1, x, acc=True)["acc"]
+        torch.cuda.current_stream().wait_stream(other)
+        return got + [z]
+
+    for a, b in zip(run(native), run(plain)):
+        assert (a is None and b is None) or (a.dtype == b.dtype and a.shape == b.shape and a.device == b.device and torch.equal(a, b))
