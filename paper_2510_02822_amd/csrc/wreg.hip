@@ -209,7 +209,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
     const bool q_rows = p.q != nullptr && (p.N & 15) == 0;
     const FragOut fo = {p.acc, p.y, p.q, p.r_out, p.N};
     const int xe = fr * 64 + ((fh ^ swizzle(fr, 4)) << 4), xo = fr * 64 + (((2 + fh) ^ swizzle(fr, 4)) << 4);
-    constexpr bool REGTAB = OUT != kAny && NU <= 32;   // the epilogue's constants stay in registers
+    // The sums of a tile leave between the matrix instructions of the next one: fp32 rows, whose stores then spread over the tile (r = 0.5 / 1:
+    // 6304 x 768 -> 3072 27.0 / 27.5 -> 24.3 / 24.4 us, 12608 x 1024 -> 4096 62.5 / 62.9 -> 53.2 / 55.4), and codes of short layers without lowering (12608 x 512 ->
+    // 2048 at r = 0 17.2 -> 16.2).  Other codes leave at once: beside the lowering they held up the matrix instructions (12608 x 1024 -> 4096 at
+    // r = 1 50.1 -> 52.7), and without it nothing was gained.
+    constexpr bool INTER = NU <= 32 && (OUT == kFloats || (OUT != kAny && NU == 16 && !LOWIN));
+    constexpr bool REGTAB = OUT != kAny && NU <= (INTER && LOWIN ? 24 : 32);   // the epilogue's constants stay in registers
     constexpr int D = NU <= 32 ? 4 : 2;          // units that activation fragments are read ahead
     // the pieces to lower leave one after the other from the third unit of a half on
     constexpr int PSTEP = 2, LASTP = 2 + PSTEP * (NCP - 1);
@@ -247,70 +252,56 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
             wait_tile();
             block_barrier();
         };
+        const int lim_lane = p.N - n_blk - 4 * fh;
+        // ---- epilogue of tile t0 + i: value e of the lane's sixteen (register 4 k + j: column 8 k + 4 fh + j of the wave's), then the rest.
+        // (What is computed here is pinned in its place: as pure data flow the optimiser moves it past the branches, to its use.)
+        uint32_t qrow[4];
+        v4i yq, lt;
+        auto value = [&](const v16i &acc, int i, int e) {
+            const int k = e >> 2, j = e & 3, c = 32 * wave + 8 * k + 4 * fh;
+            if (j == 0) {
+                if constexpr (!REGTAB) {
+                    mul[k] = *reinterpret_cast<const v4i *>(lds + 4 * c);
+                    add[k] = *reinterpret_cast<const v4i *>(lds + 4 * (kCols + c));
+                    asm volatile("" : "+v"(mul[k]), "+v"(add[k]));
+                }
+                if constexpr (LOWER) {
+                    lt = *reinterpret_cast<const v4i *>(lds + 4 * (2 * kCols + c));
+                    asm volatile("" : "+v"(lt));
+                }
+            }
+            float v = __builtin_fmaf((float)acc[e], __int_as_float(mul[k][j]), __int_as_float(add[k][j]));
+            if constexpr (OUT == kFloats) {
+                yq[j] = __float_as_int(v);
+                asm volatile("" : "+v"(yq));
+                const uint32_t at = (uint32_t)(fr * p.N + n_blk + c) * 4u;
+                if (j == 3 && fr < p.M - (t0 + i) * kRows && c - 4 * fh < lim_lane)
+                    *reinterpret_cast<v4i *>(reinterpret_cast<unsigned char *>(p.y + (int64_t)(t0 + i) * kRows * p.N) + at) = yq;
+            } else {
+                if constexpr (LOWER) v = __builtin_amdgcn_fmed3f(v, __int_as_float(lt.x), __int_as_float(lt.y));
+                qrow[k] = __builtin_amdgcn_cvt_pk_u8_f32(v, j, j == 0 ? 0 : qrow[k]);
+                if (j == 3) {
+                    qrow[k] ^= 0x80808080u;
+                    if constexpr (LOWER) qrow[k] &= (uint32_t)lt.z;
+                }
+                asm volatile("" : "+v"(qrow[k]));
+            }
+        };
+        auto finish = [&](int i) {
+            if constexpr (OUT != kFloats) {
+                const FragOut at = {nullptr, nullptr, p.q + (int64_t)(t0 + i) * kRows * p.N, 0.0f, p.N};   // (its rows from this tile on)
+                store_codes(at, qrow, wave, n_blk, fr, fr < p.M - (t0 + i) * kRows, lim_lane, fh);
+            }
+        };
         float *y_lane = p.y + ((int64_t)t0 * kRows + fr) * p.N + n_blk + 32 * wave + 4 * fh;
         int8_t *q_tile = p.q + (int64_t)t0 * kRows * p.N;
-        v16i acc;
-        int after = STAGE;   // slot of the next tile
-        // half of a tile's units, from U0 on; LOW: the wave lowers its part of the tile in `low_slot`
-        // meanwhile; COPY: it asks for a tile (in one go the copies of all waves would hold up each other and the stores)
-        auto half = [&](auto begin, auto low, int low_slot, auto copy_c) {
-            constexpr int U0 = decltype(begin)::value;
-            constexpr bool LOW = decltype(low)::value, COPY = decltype(copy_c)::value;
-            if constexpr (LOW) lower_read(low_slot);
-            __builtin_amdgcn_sched_barrier(0);
+        auto leave = [&](const v16i &acc, int i) {   // all of a tile's sums at once
+            if constexpr (INTER) {
 #pragma unroll
-            for (int u = U0; u < U0 + NU / 2; ++u) {
-                if (EXACT || u <= NU - 8 || u < p.units) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[u], x[u % D], acc, 0, 0, 0);
-                if (u + D == NU) {   // the next tile's fragments (beyond the last tile: whatever the slot holds, not used)
-                    se = ring + xe + after;
-                    so = ring + xo + after;
-                }
-                xload((u + D) % NU);
-                if constexpr (COPY) {
-                    if ((u - U0) % 3 == 1 && (u - U0) / 3 < NCP) copy((u - U0) / 3);
-                }
-                if constexpr (LOW) {
-                    const int k = u - U0 - 2;
-                    if (k >= 0 && k % PSTEP == 0 && k / PSTEP < NCP) lower_write(low_slot, k / PSTEP);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                for (int e = 0; e < 16; ++e) value(acc, i, e);
+                finish(i);
+                return;
             }
-            if constexpr (COPY) copied();
-            if constexpr (LOW) wait_lds<NU / 2 - 1 - LASTP>();   // (the fragment reads behind the last piece may be in flight)
-        };
-        using L = std::integral_constant<bool, LOWIN>;
-        using T = std::integral_constant<bool, true>;
-        using F = std::integral_constant<bool, false>;
-        using H0 = std::integral_constant<int, 0>;
-        using H1 = std::integral_constant<int, NU / 2>;
-        auto tile = [&](int i, auto first) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[e] = 0;
-            // (in the last rounds the barriers and, behind them, copies of nothing go on, and a slot that nobody reads is lowered
-            // again; but a block of two tiles or one does not put them behind its weights)
-            constexpr bool FIRST = decltype(first)::value;
-            if (!LATE) {
-                if (LOWIN && (!FIRST || nt > 1)) {
-                    wait_tile();
-                    half(H0{}, L{}, after, F{});
-                } else {
-                    half(H0{}, F{}, 0, F{});
-                }
-                sync();
-                if (!FIRST || nt > 2) half(H1{}, F{}, 0, T{});
-                else half(H1{}, F{}, 0, F{});
-            } else {
-                if (!FIRST || nt > 2) half(H0{}, F{}, 0, T{});
-                else half(H0{}, F{}, 0, F{});
-                if (LOWIN && (!FIRST || nt > 2)) {
-                    wait_tile();
-                    half(H1{}, L{}, after == (S - 1) * STAGE ? 0 : after + STAGE, F{});
-                } else {
-                    half(H1{}, F{}, 0, F{});
-                }
-                if (i + 1 < nt) sync();
-            }
-            after = after == (S - 1) * STAGE ? 0 : after + STAGE;
             int lim = p.N - n_blk - 4 * fh;
             asm volatile("" : "+v"(lim));
             const int64_t m = (int64_t)(t0 + i) * kRows + fr;
@@ -361,11 +352,100 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
             } else {
                 store_fragment<QONLY, kCols, LOWER>(acc, fo, lds, wave, n_blk, m, m < p.M, lim, fh, pre_scaled, q_rows);
             }
+        };
+        int after = STAGE;   // slot of the next tile
+        // half of a tile's units, from U0 on; LOW: the wave lowers its part of the tile in `low_slot`
+        // meanwhile; COPY: it asks for a tile (in one go the copies of all waves would hold up each other and the stores); PREV: the sums of the
+        // tile before leave
+        auto half = [&](auto begin, auto low, int low_slot, auto copy_c, auto prev_c, int i, v16i &acc, const v16i &prev) {
+            constexpr int U0 = decltype(begin)::value;
+            constexpr bool LOW = decltype(low)::value, COPY = decltype(copy_c)::value, PREV = INTER && decltype(prev_c)::value;
+            if constexpr (LOW) lower_read(low_slot);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = U0; u < U0 + NU / 2; ++u) {
+                if (EXACT || u <= NU - 8 || u < p.units) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[u], x[u % D], INTER && u == 0 ? v16i{} : acc, 0, 0, 0);
+                if constexpr (INTER) asm volatile("" : "+v"(acc));
+                if (u + D == NU) {   // the next tile's fragments (beyond the last tile: whatever the slot holds, not used)
+                    se = ring + xe + after;
+                    so = ring + xo + after;
+                }
+                xload((u + D) % NU);
+                if constexpr (COPY) {
+                    if ((u - U0) % 3 == 1 && (u - U0) / 3 < NCP) copy((u - U0) / 3);
+                }
+                if constexpr (LOW) {
+                    const int k = u - U0 - 2;
+                    if (k >= 0 && k % PSTEP == 0 && k / PSTEP < NCP) lower_write(low_slot, k / PSTEP);
+                }
+                if constexpr (PREV) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (e * (NU - 4) / 16 + 2 == u) value(prev, i - 1, e);
+                    if (u == NU - 1) finish(i - 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (COPY) copied();
+            if constexpr (LOW) wait_lds<NU / 2 - 1 - LASTP>();   // (the fragment reads behind the last piece may be in flight)
+        };
+        using L = std::integral_constant<bool, LOWIN>;
+        using T = std::integral_constant<bool, true>;
+        using F = std::integral_constant<bool, false>;
+        using H0 = std::integral_constant<int, 0>;
+        using H1 = std::integral_constant<int, NU / 2>;
+        auto tile = [&](int i, auto first, v16i &acc, const v16i &prev) {
+            // (in the last rounds the barriers and, behind them, copies of nothing go on, and a slot that nobody reads is lowered
+            // again; but a block of two tiles or one does not put them behind its weights)
+            constexpr bool FIRST = decltype(first)::value;
+            using P = std::integral_constant<bool, !FIRST>;
+            if constexpr (!INTER) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[e] = 0;
+            }
+            if (!LATE) {
+                if (LOWIN && (!FIRST || nt > 1)) {
+                    wait_tile();
+                    half(H0{}, L{}, after, F{}, P{}, i, acc, prev);
+                } else {
+                    half(H0{}, F{}, 0, F{}, P{}, i, acc, prev);
+                }
+                sync();
+                if (!FIRST || nt > 2) half(H1{}, F{}, 0, T{}, P{}, i, acc, prev);
+                else half(H1{}, F{}, 0, F{}, P{}, i, acc, prev);
+            } else {
+                if (!FIRST || nt > 2) half(H0{}, F{}, 0, T{}, P{}, i, acc, prev);
+                else half(H0{}, F{}, 0, F{}, P{}, i, acc, prev);
+                if (LOWIN && (!FIRST || nt > 2)) {
+                    wait_tile();
+                    half(H1{}, L{}, after == (S - 1) * STAGE ? 0 : after + STAGE, F{}, P{}, i, acc, prev);
+                } else {
+                    half(H1{}, F{}, 0, F{}, P{}, i, acc, prev);
+                }
+                if (i + 1 < nt) sync();
+            }
+            after = after == (S - 1) * STAGE ? 0 : after + STAGE;
+            if constexpr (!INTER) leave(acc, i);
             __builtin_amdgcn_sched_barrier(0);
         };
         if (LATE) sync();
-        tile(0, T{});   // (waits for each weight at its first use: a copy of the code that the loop need not carry)
-        for (int i = 1; i < nt; ++i) tile(i, F{});
+        v16i sum0, sum1;
+        tile(0, T{}, sum0, sum0);   // (waits for each weight at its first use: a copy of the code that the loop need not carry)
+        if constexpr (INTER) {
+            int i = 1;
+            for (; i + 1 < nt; i += 2) {
+                tile(i, F{}, sum1, sum0);
+                tile(i + 1, F{}, sum0, sum1);
+            }
+            if (i < nt) {
+                tile(i, F{}, sum1, sum0);
+                leave(sum1, nt - 1);
+            } else {
+                leave(sum0, nt - 1);
+            }
+        } else {
+            for (int i = 1; i < nt; ++i) tile(i, F{}, sum0, sum0);
+        }
         wait_vm<0>();   // nothing of this wave's copies is in flight when the block's LDS is released
     };
     if (wave >= kWaves / 2) walk(std::integral_constant<bool, true>{});
