@@ -266,12 +266,16 @@ __global__ void k_lower_packed4(const int8_t *__restrict__ X, uint8_t *__restric
 // at runtime"): per channel group the highest magnitude bit p of all values (ones' complement for negative ones) is
 // found by OR-ing v ^ (v << 1) over the group; three more bits below the sign can be kept: s = max(0, p - 2).
 // Thread (tx, ty) of a block of 1024 ORs the 16 channels at column piece blockIdx.y*TX + tx over the rows
-// blockIdx.x*TY + ty, + gridDim.x*TY, ...; the block combines its rows in LDS.  PARTIAL: the block then leaves the
+// blockIdx.x*TY + ty, + gridDim.x*TY, ...; its waves combine their rows by shuffles and meet in LDS.  PARTIAL: the block then leaves the
 // masks of its groups in a row of its own (no atomics on shared words: with a hundred blocks those queue up for tens
 // of microseconds) and the block that finishes last ORs the rows.  Otherwise (the variant that lives in G + 1 scan
 // words) it adds what is new to the group's mask (an atomic only if a coherent read shows bits missing).  Either way
 // the last block turns the masks of the scanned groups (the first g4) into positions, copies the calibrated
 // positions of the other groups, and leaves what must be zero for the next call zero.  No block waits for another.
+// Bound by its chain of trips (launch, rows, masks, ticket, masks of all blocks: 2.8 us without any rows) up to a few MB, then by memory.
+// Combining the rows by one thread per column, a loop over LDS, and the blocks' masks by LDS atomics cost up to 11 us where the channels are few
+// (r = 0 13.6 -> 2.85 us; one group of 1576 x 768 9.4 -> 4.4) and 1 to 2.5 us where they are many (12608 x 4096 14.2 -> 11.7, 3000 x 5088 9.6
+// -> 7.3); 1576 x 768 at r = 0.5 4.6 -> 4.4, 6304 x 768 at r = 1 5.9 -> 5.3.
 constexpr int kScanThreads = 1024;
 template <bool PARTIAL>
 __global__ __launch_bounds__(kScanThreads) void k_dyn_positions(const int8_t *__restrict__ X, int64_t rows, int C,
@@ -279,15 +283,18 @@ __global__ __launch_bounds__(kScanThreads) void k_dyn_positions(const int8_t *__
                                                                 uint32_t *scan, const int32_t *__restrict__ ashift_static,
                                                                 int32_t *__restrict__ ashift_dyn)
 {
-    __shared__ uint32_t sh[kScanThreads];
+    __shared__ uint32_t own[kMaxGroups], sum[kMaxGroups];   // masks of this block's groups; PARTIAL: of all blocks
     __shared__ int last;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int TX = 1 << tx_log2, TY = kScanThreads >> tx_log2;
     const int tx = tid & (TX - 1), ty = tid >> tx_log2;
     const int piece = blockIdx.y * TX + tx;
-    const bool active = piece < pieces;
+    const int ppg = gs >> 4, ppg_log2 = gs == 64 ? 2 : 1;   // pieces per group
+    const int first = (int)(blockIdx.y * TX) >> ppg_log2, count = min(TX >> ppg_log2, g4 - first);   // the block's groups
+    for (int g = tid; g < kMaxGroups; g += kScanThreads) own[g] = sum[g] = 0;
+    const int32_t calibrated = tid <= G ? ashift_static[tid] : 0;   // (on its way from the start; there are at most kMaxGroups + 1 of them)
     uint32_t m = 0;
-    if (active) {
+    if (piece < pieces) {
         uint32_t acc = 0;
         const int64_t step = (int64_t)gridDim.x * TY;
         const int8_t *src = X + (int64_t)piece * 16;
@@ -303,85 +310,74 @@ __global__ __launch_bounds__(kScanThreads) void k_dyn_positions(const int8_t *__
 #pragma unroll
             for (int k = 0; k < 8; ++k) acc |= fold(v[k]);
         }
-        for (; r + 1 * step < rows; r += 2 * step) {
-            const uint4 v0 = *reinterpret_cast<const uint4 *>(src + r * C);
-            const uint4 v1 = *reinterpret_cast<const uint4 *>(src + (r + step) * C);
-            acc |= fold(v0) | fold(v1);
+        if (r < rows) {   // the rest, in one trip too
+            uint4 v[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                v[k] = make_uint4(0, 0, 0, 0);
+                if (r + k * step < rows) v[k] = *reinterpret_cast<const uint4 *>(src + (r + k * step) * C);
+            }
+#pragma unroll
+            for (int k = 0; k < 7; ++k) acc |= fold(v[k]);
         }
-        for (; r < rows; r += step) acc |= fold(*reinterpret_cast<const uint4 *>(src + r * C));
         acc |= acc >> 16;
         acc |= acc >> 8;
         m = acc & 0xFEu;
     }
-    sh[tid] = m;
+    // the rows of a wave and the pieces of a group meet in the wave, the waves in LDS
+    for (int d = TX; d < 64; d <<= 1) m |= __shfl_xor(m, d);
+    for (int d = 1; d < ppg; d <<= 1) m |= __shfl_xor(m, d);
     __syncthreads();
-    if (PARTIAL) {
-        // Every block leaves the masks of its groups in a row of its own (device-coherent stores, no atomics on shared
-        // words: with a block per compute unit those queue up for tens of microseconds), draws a ticket once the
-        // stores have completed, and the block that draws the last one ORs the rows together.
-        __shared__ uint32_t gmask[kMaxGroups + 1];
-        const int ppg = gs >> 4;   // pieces per group
-        if (ty == 0) {
-            for (int y = 1; y < TY; ++y) m |= sh[y * TX + tx];
-        }
-        __syncthreads();
-        if (ty == 0) sh[tx] = m;
-        for (int g = tid; g <= kMaxGroups; g += kScanThreads) gmask[g] = 0;
-        __syncthreads();
-        uint32_t *part = scan + kScanHead;
-        if (ty == 0 && active && (tx & (ppg - 1)) == 0) {
-            uint32_t gm = 0;
-            for (int k = 0; k < ppg; ++k) gm |= sh[tx + k];
-            __hip_atomic_store(&part[(int64_t)blockIdx.x * g4 + (piece * 16) / gs], gm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_s_waitcnt(0x0070);
-        __syncthreads();
-        if (tid == 0) last = atomicAdd(&scan[0], 1u) == gridDim.x * gridDim.y - 1;
-        __syncthreads();
-        if (!last) return;
-        const int total = (int)gridDim.x * g4;
-        for (int i = tid; i < total; i += kScanThreads) {
-            const uint32_t v = __hip_atomic_load(&part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (v) atomicOr(&gmask[i % g4], v);
-        }
-        __syncthreads();
-        for (int g = tid; g <= G; g += kScanThreads) {
-            if (g < g4) {
-                const uint32_t mask = gmask[g];
-                const int p = mask ? 31 - __clz((int)mask) : 0;   // bit p of the mask: highest magnitude bit p - 1
-                ashift_dyn[g] = p - 3 > 0 ? p - 3 : 0;
+    if ((lane >> tx_log2) == 0 && (tx & (ppg - 1)) == 0 && m) atomicOr(&own[tx >> ppg_log2], m);
+    __syncthreads();
+    // The first wave passes the block's masks on and draws a ticket when that has completed.  What other blocks need of it is
+    // at the device's coherence point by then (a release fence would also write back the L2, i.e. the whole output of the
+    // kernel before this one).
+    if (tid < 64) {
+        for (int g = lane; g < count; g += 64) {
+            if (PARTIAL) {
+                __hip_atomic_store(&scan[kScanHead + (int64_t)blockIdx.x * g4 + first + g], own[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else {
-                ashift_dyn[g] = ashift_static[g];
+                const uint32_t seen = __hip_atomic_load(&scan[first + g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (own[g] & ~seen) atomicOr(&scan[first + g], own[g]);
             }
         }
-        if (tid == 0) scan[0] = 0;
-        return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) last = atomicAdd(&scan[PARTIAL ? 0 : G], 1u) == gridDim.x * gridDim.y - 1;
     }
-    if (ty == 0 && active) {
-        for (int y = 1; y < TY; ++y) m |= sh[y * TX + tx];
-        uint32_t *dst = &scan[(piece * 16) / gs];
-        const uint32_t seen = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (m & ~seen) atomicOr(dst, m);
-    }
-    // The only results other blocks need are those of the atomics above, which are performed at the device's
-    // coherence point: it is enough that they have completed before this block's ticket is drawn (a full
-    // release fence would also write back the L2, i.e. the whole output of the kernel before this one).
-    __builtin_amdgcn_s_waitcnt(0x0070);
-    __syncthreads();
-    if (tid == 0) last = atomicAdd(&scan[G], 1u) == gridDim.x * gridDim.y - 1;
     __syncthreads();
     if (!last) return;
-    for (int g = tid; g <= G; g += kScanThreads) {
+    if (PARTIAL) {
+        const int wide = g4 > 1 ? 32 - __clz(g4 - 1) : 0;   // 2^wide threads read a row
+        const int g = tid & ((1 << wide) - 1), step = kScanThreads >> wide, blocks = (int)gridDim.x;
+        uint32_t v = 0;
         if (g < g4) {
-            const uint32_t mask = atomicOr(&scan[g], 0u);   // device-scope read of what all blocks added
-            const int p = mask ? 31 - __clz((int)mask) : 0;   // bit p of the mask: highest magnitude bit p - 1
-            ashift_dyn[g] = p - 3 > 0 ? p - 3 : 0;
-            scan[g] = 0;
-        } else {
-            ashift_dyn[g] = ashift_static[g];
+            for (int r = tid >> wide; r < blocks; r += 8 * step) {
+                uint32_t w[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    w[k] = 0;
+                    if (r + k * step < blocks) w[k] = __hip_atomic_load(&scan[kScanHead + (int64_t)(r + k * step) * g4 + g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v |= w[k];
+            }
         }
+        for (int d = 1 << wide; d < 64; d <<= 1) v |= __shfl_xor(v, d);
+        if ((lane >> wide) == 0 && v) atomicOr(&sum[g], v);
+        __syncthreads();
     }
-    if (tid == 0) scan[G] = 0;
+    if (tid <= G) {
+        int32_t s = calibrated;
+        if (tid < g4) {
+            const uint32_t mask = PARTIAL ? sum[tid] : atomicOr(&scan[tid], 0u);   // (a device-scope read of what all blocks added)
+            const int p = mask ? 31 - __clz((int)mask) : 0;   // bit p of the mask: highest magnitude bit p - 1
+            s = p - 3 > 0 ? p - 3 : 0;
+            if (!PARTIAL) scan[tid] = 0;
+        }
+        ashift_dyn[tid] = s;
+    }
+    if (tid == 0) scan[PARTIAL ? 0 : G] = 0;
 }
 
 // Eq. 1 for activations: four values per thread, one packed dword out.

@@ -1,0 +1,35 @@
+"""GPU parity of the scan for run-time extraction positions at the edges of its block layout: a lone row, rows that are not a multiple of a
+thread's trip, one group and all groups, more than 256 pieces of 16 channels (two columns of blocks), against the oracle (whole numbers)."""
+import numpy as np
+import pytest
+
+import workloads
+from helpers import both_layers
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,C,gs", [(1, 64, 64), (1, 768, 32), (77, 5088, 32), (515, 4160, 64), (1576, 96, 32), (4099, 320, 64), (16385, 64, 32)])
+def test_scan_edges(M, C, gs):
+    import torch
+    import oracle
+    import paper_2510_02822_amd as fq
+    fq.load()
+    oracle.build()
+    case = workloads.make_linear("scan", 12, M + C, 8, C, 16, gs, outlier_frac=0.02)
+    ol, hl, x_scale = both_layers(case)
+    rng = np.random.default_rng(M + C)
+    # a small value everywhere, one larger one in every group and a few at the first and the last row
+    X = rng.integers(-3, 4, (M, C), dtype=np.int64).astype(np.int8)
+    for g in range(C // gs):
+        X[rng.integers(M), g * gs + rng.integers(gs)] = rng.integers(-128, 128)
+    X[0, rng.integers(C)] = -128
+    X[M - 1, C - 1] = 127
+    Xd = torch.from_numpy(X).to("cuda")
+    G = C // gs
+    for r in (1.0, 1.0 / G, 0.5, 0.0):
+        g4 = fq.flexiq_set_ratio(hl, r) // gs
+        want = oracle.dynamic_act_shifts(X, gs, g4, ol.a_shift)
+        for _ in range(2):   # (the second call finds the scan words as the first one left them)
+            fq.flexiq_dynamic_positions(hl, Xd)
+            assert np.array_equal(fq.flexiq_layer_positions(hl)[:G], want[:G]), (M, C, gs, r)
