@@ -63,6 +63,7 @@ struct Call {
     PyObject_HEAD
     vectorcallfunc vectorcall;
     PyObject *dict;
+    PyObject *weak;       // list of weak references
     PyObject *fallback;
     const Kind *kind;
 };
@@ -392,6 +393,7 @@ void call_dealloc(PyObject *self)
 {
     Call *c = reinterpret_cast<Call *>(self);
     PyObject_GC_UnTrack(self);
+    if (c->weak) PyObject_ClearWeakRefs(self);
     Py_CLEAR(c->dict);
     Py_CLEAR(c->fallback);
     Py_TYPE(self)->tp_free(self);
@@ -410,7 +412,33 @@ int call_clear(PyObject *self)
     return 0;
 }
 
-PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr, nullptr}};
+
+// ---- what else a program does with a function: it is one for isinstance() and the inspect module (as it is for a program that asks
+// whether something is one before it looks at its defaults or code), binds as a method, and is copied and pickled by its name
+PyObject *call_class(PyObject *, void *)
+{
+    Py_INCREF(&PyFunction_Type);
+    return reinterpret_cast<PyObject *>(&PyFunction_Type);
+}
+PyObject *call_getattro(PyObject *self, PyObject *name)
+{
+    PyObject *v = PyObject_GenericGetAttr(self, name);
+    if (v || !PyErr_ExceptionMatches(PyExc_AttributeError)) return v;
+    PyErr_Clear();
+    return PyObject_GetAttr(reinterpret_cast<Call *>(self)->fallback, name);
+}
+PyObject *call_bind(PyObject *self, PyObject *object, PyObject *)
+{
+    if (object && object != Py_None) return PyMethod_New(self, object);
+    Py_INCREF(self);
+    return self;
+}
+PyObject *call_reduce(PyObject *self, PyObject *) { return PyObject_GetAttrString(self, "__qualname__"); }
+
+PyMethodDef call_methods[] = {{"__reduce__", call_reduce, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr},
+                             {"__class__", call_class, nullptr, nullptr, nullptr},
+                             {nullptr, nullptr, nullptr, nullptr, nullptr}};
 PyTypeObject call_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
 // wrap(function): a Call of the entry point of that name which hands what it does not serve to the function
@@ -430,6 +458,7 @@ PyObject *wrap(PyObject *, PyObject *function)
     if (!c) return nullptr;
     c->vectorcall = call;
     c->dict = nullptr;
+    c->weak = nullptr;
     Py_INCREF(function);
     c->fallback = function;
     c->kind = kind;
@@ -492,11 +521,14 @@ PyMODINIT_FUNC PyInit__calls()
     call_type.tp_vectorcall_offset = offsetof(Call, vectorcall);
     call_type.tp_call = PyVectorcall_Call;
     call_type.tp_dictoffset = offsetof(Call, dict);
+    call_type.tp_weaklistoffset = offsetof(Call, weak);
+    call_type.tp_methods = call_methods;
     call_type.tp_getset = call_getset;
+    call_type.tp_descr_get = call_bind;
     call_type.tp_dealloc = call_dealloc;
     call_type.tp_traverse = call_traverse;
     call_type.tp_clear = call_clear;
-    call_type.tp_getattro = PyObject_GenericGetAttr;
+    call_type.tp_getattro = call_getattro;
     call_type.tp_setattro = PyObject_GenericSetAttr;
     if (PyType_Ready(&handle_type) < 0 || PyType_Ready(&call_type) < 0) return nullptr;
     for (Kind &k : kinds) {

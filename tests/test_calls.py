@@ -1,6 +1,9 @@
 """The native calls of the binding (csrc/calls.cpp) against the functions of binding.py that they stand for: the same results, the same
 refusals."""
+import copy
 import inspect
+import pickle
+import weakref
 
 import numpy as np
 import pytest
@@ -18,6 +21,25 @@ def test_calls_are_native_and_keep_their_signature(name):
     f = getattr(fq, name)
     assert fq.binding._calls is not None and type(f).__name__ == "Call" and f.__name__ == name and f.__doc__ == f.__wrapped__.__doc__
     assert str(inspect.signature(f)) == str(inspect.signature(f.__wrapped__))
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_calls_are_used_like_functions(name):
+    import paper_2510_02822_amd as fq
+    f = getattr(fq, name)
+    assert copy.deepcopy({"call": f})["call"] is f and copy.copy(f) is f and weakref.ref(f)() is f
+    for protocol in range(pickle.HIGHEST_PROTOCOL + 1):
+        assert pickle.loads(pickle.dumps(f, protocol)) is f
+    assert inspect.isfunction(f) and inspect.isroutine(f) and callable(f)
+    for attribute in ("__defaults__", "__kwdefaults__", "__code__", "__closure__", "__globals__"):
+        assert getattr(f, attribute) is getattr(f.__wrapped__, attribute)
+    with pytest.raises(AttributeError):
+        f.no_such_attribute
+    holder = type("Holder", (), {"call": f})
+    bound = holder().call
+    assert holder.call is f and inspect.ismethod(bound) and bound.__func__ is f
+    with pytest.raises((AttributeError, AssertionError)):   # (the holder stands for the first argument)
+        bound(*[None] * (len(inspect.signature(f).parameters) - 1 - len(f.__defaults__ or ())))
 
 
 def test_what_a_native_call_does_not_serve():
