@@ -42,6 +42,17 @@ def test_calls_are_used_like_functions(name):
         bound(*[None] * (len(inspect.signature(f).parameters) - 1 - len(f.__defaults__ or ())))
 
 
+def test_sizes_of_a_layer_are_ordinary_attributes():
+    import paper_2510_02822_amd as fq
+    layer = fq.Layer(0, 4, 64, 3, 1, 32)
+    assert {k: vars(layer)[k] for k in ("N", "C", "R", "S", "group_size")} == {"N": 4, "C": 64, "R": 3, "S": 1, "group_size": 32}
+    for value in (np.int64(8), 8.0, None, 1 << 70):
+        layer.N = value
+        assert layer.N is value
+    del layer.C
+    assert not hasattr(layer, "C")
+
+
 def test_what_a_native_call_does_not_serve():
     import torch
     import paper_2510_02822_amd as fq
