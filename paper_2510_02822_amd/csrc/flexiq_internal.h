@@ -28,11 +28,14 @@ void set_hip_error(hipError_t e, const char *what);
     } while (0)
 
 // A launch of a kernel that takes one structure.  (2.31 us of host time against 2.52 with the launch syntax and hipGetLastError behind
-// it, which pass the configuration through a stack of their own.)
+// it, which pass the configuration through a stack of their own.)  A failed one is returned and taken off the runtime's last error, where
+// the next check of an unrelated call on this thread would find it.
 template <class P> inline hipError_t launch_kernel(void (*fn)(P), dim3 grid, dim3 block, size_t lds, void *stream, const P &p)
 {
     void *args[] = {const_cast<P *>(&p)};
-    return hipLaunchKernel(reinterpret_cast<const void *>(fn), grid, block, args, lds, (hipStream_t)stream);
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(fn), grid, block, args, lds, (hipStream_t)stream);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 // Once per device, when the first layer is packed on it: dynamic-LDS limits and occupancy of every kernel of the
