@@ -32,25 +32,42 @@ def _calls_command():
             os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L", os.path.join(T, "lib"), "-lc10", "-ltorch_cpu", "-lc10_hip", "-ltorch_python"]
 
 
+def _start(cmd):
+    return cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def _finish(job, verbose: bool):
+    """Raises if the command failed."""
+    cmd, pr = job
+    out, _ = pr.communicate()
+    out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
+    if pr.returncode != 0:
+        raise RuntimeError("%s failed: %s\n%s" % (os.path.basename(cmd[0]), " ".join(cmd), out))
+    if verbose and out.strip():
+        print(out)
+
+
 def build(verbose: bool = False, extra=()) -> str:
-    objs = []
-    procs = []
-    for src, o, defs in UNITS:
-        obj = os.path.join(CSRC, o)
-        cmd = ["hipcc", *FLAGS, *defs, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
-        procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        objs.append(obj)
-    cmd = _calls_command()
-    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    for cmd, pr in procs:
-        out, _ = pr.communicate()
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
-        if pr.returncode != 0:
-            raise RuntimeError("hipcc failed: %s\n%s" % (" ".join(cmd), out))
-        if verbose and out.strip():
-            print(out)
-    cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    subprocess.check_call(cmd)
+    """Builds the library, and the native calls where torch's and Python's headers and a C++ compiler are there (the Python functions
+    behind them serve every call without)."""
+    calls, why = None, None
+    try:
+        calls = _start(_calls_command())
+    except (ImportError, OSError) as e:
+        why = e
+    jobs = [_start(["hipcc", *FLAGS, *defs, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(CSRC, o)]) for src, o, defs in UNITS]
+    if calls:
+        try:
+            _finish(calls, verbose)
+        except RuntimeError as e:
+            why = e
+    if why is not None:
+        print("the native calls were not built: %s" % why, file=sys.stderr)
+        if os.path.exists(CALLS):   # (of other sources)
+            os.remove(CALLS)
+    for job in jobs:
+        _finish(job, verbose)
+    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *[os.path.join(CSRC, o) for _, o, _ in UNITS]])
     return LIB
 
 
