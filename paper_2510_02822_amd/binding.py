@@ -8,11 +8,12 @@ from typing import Optional
 
 import numpy as np
 
-import torch   # noqa: F401  (its libraries are what _calls is linked with)
-
 try:
+    import torch   # (its libraries are what _calls is linked with)
     from . import _calls   # the run-time entry points as native calls (csrc/calls.cpp); the functions below serve what it does not
-except ImportError:   # not built for this torch: they serve every call
+    if getattr(_calls, "built_for", None) != torch.__version__:   # (they look into tensors: another torch may lay them out otherwise)
+        _calls = None
+except (ImportError, OSError):   # no torch, or not built for this one or this Python: they serve every call
     _calls = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))

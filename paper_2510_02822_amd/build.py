@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflexiq.so")
-CALLS = os.path.join(HERE, "_calls.so")   # Python's way into the run-time entry points (csrc/calls.cpp), against this torch
+# Python's way into the run-time entry points (csrc/calls.cpp), for this Python and this torch
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 NUM_TILE_SHAPES = 15
 # (source, object, extra flags): the kernel of every tile shape is a translation unit of its own
 UNITS = [("pack.hip", "pack.o", []), ("gemm.hip", "gemm.o", []), ("fp6_gemm.hip", "fp6_gemm.o", []),
@@ -28,6 +29,7 @@ def _calls_command():
     inc = [os.path.join(T, "include"), os.path.join(T, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"],
            os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), os.path.join(ROOT, "include")]
     return ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-DBUILT_FOR=\"%s\"" % torch.__version__,
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *sum((["-isystem", i] for i in inc[:-1]), []), "-I", inc[-1],
             os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L", os.path.join(T, "lib"), "-lc10", "-ltorch_cpu", "-lc10_hip", "-ltorch_python"]
 

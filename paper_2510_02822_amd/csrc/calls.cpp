@@ -558,6 +558,7 @@ PyMODINIT_FUNC PyInit__calls()
     }
     PyObject *m = PyModule_Create(&module);
     if (!m) return nullptr;
+    if (PyModule_AddStringConstant(m, "built_for", BUILT_FOR) < 0) return nullptr;   // torch.__version__
     Py_INCREF(&handle_type);
     if (PyModule_AddObject(m, "Handle", reinterpret_cast<PyObject *>(&handle_type)) < 0) return nullptr;
     return m;

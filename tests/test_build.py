@@ -1,7 +1,12 @@
 """CPU: what the library's build and import do without, shown with a library of one small source."""
 import os
+import subprocess
+import sys
+import sysconfig
 
 import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("missing", ["torch", "compiler", "headers"])
@@ -26,3 +31,27 @@ def test_the_library_is_built_without_the_native_calls(missing, tmp_path, monkey
     (tmp_path / "one.hip").write_text("#error not this\n")
     with pytest.raises(RuntimeError, match="hipcc failed"):
         b.build()
+
+
+@pytest.mark.parametrize("before", ["import sys; sys.modules['torch'] = None", "import torch; torch.__version__ = 'another'",
+                                    "import sys; sys.modules['paper_2510_02822_amd._calls'] = None"])
+def test_imported_without_the_native_calls(before):
+    """No torch, another torch than the native calls were built for, no native calls: the package is there, with Python's functions."""
+    program = before + """
+import types
+import paper_2510_02822_amd as fq
+from paper_2510_02822_amd import build
+assert fq.binding._calls is None and fq.Layer.__mro__ == (fq.Layer, object)
+assert type(fq.flexiq_mixed_gemm) is types.FunctionType and not hasattr(fq.flexiq_mixed_gemm, '__wrapped__')
+if fq.binding.os.path.exists(fq.binding.LIB_PATH):
+    fq.load()
+"""
+    subprocess.check_call([sys.executable, "-c", program], cwd=ROOT)
+
+
+def test_native_calls_are_for_this_python_and_this_torch():
+    import torch
+    import paper_2510_02822_amd as fq
+    from paper_2510_02822_amd import build
+    assert build.CALLS.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and os.path.samefile(fq.binding._calls.__file__, build.CALLS)
+    assert fq.binding._calls.built_for == torch.__version__
