@@ -145,8 +145,10 @@ int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fl
 // (wreg.hip) linear calls of 288 to 1280 channels: the weights of a block resident in registers, row tiles streamed
 // past them; *taken = 0: the call does not qualify
 int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
-// (wreg6.hip) the same for flexiq_mixed_gemm_fp6: 256 to 1280 channels, all of them (K6) on the FP6 matrix path
-int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int *taken, const LowerArgs *lower);
+// (wreg6.hip) the same for flexiq_mixed_gemm_fp6: 256 to 1280 channels, all of them (K6) on the FP6 matrix path; tiled_rows: how many rows
+// one after the other a compute unit would work through in the tiled kernel
+int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int64_t tiled_rows, int *taken,
+                 const LowerArgs *lower);
 }  // namespace flexiq
 
 // Device layouts (all offsets in bytes unless noted), T = R*S filter taps, CUp = C/32 rounded up to

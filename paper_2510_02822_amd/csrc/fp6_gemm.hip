@@ -29,6 +29,27 @@ static std::mutex g_mu;
 static int g_force_shape = -1;
 static int g_last_shape = -1;
 
+// The tile shape with the least modelled time; *rows: how many rows one after the other a compute unit works through.
+static int choose_shape(const Shape *tab, const flexiq_layer *L, int64_t M, int K6, int num_cu, int64_t *rows)
+{
+    const int S = L->C / 64, S6 = K6 / 64;
+    int best = 0;
+    double best_cost = 1e300;
+    for (int i = 0; i < kNumShapes; ++i) {
+        const double tiles = (double)((M + tab[i].BM - 1) / tab[i].BM) * (double)((L->N + tab[i].BN - 1) / tab[i].BN);
+        const double rounds = __builtin_ceil(tiles / num_cu);
+        const double mf = tab[i].BM / 64.0;   // MFMAs per wave and k-half (two waves per SIMD): 2 x BM / 64 ... relative
+        const double step8 = 140.0 + 128.0 * mf, step6 = 140.0 + 64.0 * mf;
+        const double cost = rounds * (3500.0 + S6 * step6 + (S - S6) * step8 + 1400.0 * mf);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = i;
+            *rows = (int64_t)rounds * tab[i].BM;
+        }
+    }
+    return best;
+}
+
 }  // namespace fp6
 
 int prepare_fp6_kernels(int device)
@@ -158,34 +179,18 @@ extern "C" int flexiq_mixed_gemm_fp6(const flexiq_layer *L, const int8_t *X, con
         }
     }
 
+    const DeviceState &ds = g_dev[dev];
+    const Shape *tab = K6 == L->C ? shapes<true>() : shapes<false>();
+    int64_t rows = 0;
+    const int best = g_force_shape >= 0 ? g_force_shape : choose_shape(tab, L, M, K6, ds.num_cu, &rows);
+
     if (g_force_shape < 0) {   // all of at most 1280 channels as FP6: the weights of a block resident in registers (wreg6.hip)
         int taken = 0;
-        const int rc = launch_wreg6(L, X6, M, out, stream, K6, &taken, &la);
+        const int rc = launch_wreg6(L, X6, M, out, stream, K6, rows, &taken, &la);
         if (rc != FLEXIQ_OK) return rc;
         if (taken) {
             g_last_shape = -7;
             return FLEXIQ_OK;
-        }
-    }
-
-    const DeviceState &ds = g_dev[dev];
-    const Shape *tab = K6 == L->C ? shapes<true>() : shapes<false>();
-    int best = 0;
-    if (g_force_shape >= 0) {
-        best = g_force_shape;
-    } else {
-        double best_cost = 1e300;
-        const int S = L->C / 64, S6 = K6 / 64;
-        for (int i = 0; i < kNumShapes; ++i) {
-            const double tiles = (double)((M + tab[i].BM - 1) / tab[i].BM) * (double)((L->N + tab[i].BN - 1) / tab[i].BN);
-            const double rounds = __builtin_ceil(tiles / ds.num_cu);
-            const double mf = tab[i].BM / 64.0;   // MFMAs per wave and k-half (two waves per SIMD): 2 x BM / 64 ... relative
-            const double step8 = 140.0 + 128.0 * mf, step6 = 140.0 + 64.0 * mf;
-            const double cost = rounds * (3500.0 + S6 * step6 + (S - S6) * step8 + 1400.0 * mf);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best = i;
-            }
         }
     }
     g_last_shape = best;

@@ -20,9 +20,9 @@
 // int8 K-steps behind the FP6 ones (a branch per step) needs more registers than there are from 13 K-steps on: 0.4 to 0.9 times the
 // tiled kernel's speed.
 //
-// Measured (us in the tiled kernel and here, r = 1; int8 codes / fp32 / FP6 codes for a consumer): 12608 x 1024 -> 4096 55.2 / 78.9 / 78.9 and
-// 28.0 / 52.1 / 32.2; 12608 x 384 -> 1536 16.7 / 27.0 / 25.9 and 10.9 / 18.5 / 13.2; 3000 x 1024 -> 1024 10.1 / 12.6 / 12.0 and 7.7 / 10.4 / 7.6; 400 x 512 ->
-// 512 7.2 / 8.4 / 9.2 and 6.0 / 6.1 / 6.2.
+// Measured (graph replays, us in the tiled kernel's build without int8 operands and here, r = 1; int8 codes / fp32 / FP6 codes for a consumer): 12608 x 1024 ->
+// 4096 54.0 / 79.3 / 77.2 and 31.9 / 54.5 / 35.6; 12608 x 384 -> 1536 15.0 / 26.1 / 23.9 and 12.1 / 19.7 / 13.1; 400 x 512 -> 512 6.2 / 7.5 / 7.9 and 5.3 / 5.9 /
+// 5.4; two tiles per block, 3000 x 1024 -> 1024, 8.4 / 11.1 / 10.2 and 8.3 / 12.5 / 8.7.
 #include <algorithm>
 
 #include "flexiq_internal.h"
@@ -407,6 +407,32 @@ static Fn kernel(int ns, int out)
     }
 }
 
+// Whether the call is faster here than in the tiled kernel (its build without int8 operands).  Measured on 46800 calls (96 to 25200 rows of 256 to 1280
+// channels, 64 to 65536 columns, on 256 compute units), time here over time there, geometric means of a class by its outputs:
+//   * what leaves for a consumer 0.70 (FP6 codes) and 0.75 (lowered rows), never above 0.97; one tile per block 0.81 to 0.87, never above 1.06.
+//   * two tiles: 0.97 to 1.00 from a used share of the grid of 0.7 on (N not a multiple of 4: 0.8); below that 0.98 for fp32 rows, 1.01 to 1.05 for the
+//     others, 1.06 to 1.12 if N is not a multiple of 4.
+//   * three to seven: 0.88 to 0.98; N not a multiple of 4 0.92 to 0.95 with fewer rows in a block than in one there and 0.99 to 1.05 with as many; 1.00 to
+//     1.08 with more than 224 column blocks, which all bring their weights for few rows.
+//   * eight and more: 0.60 to 1.00 while a block has less than 1.3 times the rows of one there.  Beyond (129 column blocks and more leave a part of the
+//     chip idle) 1.07 to 1.21 if N is not a multiple of 4, 1.04 to 1.11 for int8 rows that are not whole 16-byte pieces, 0.64 to 0.97 else.
+//   * fp32 rows of whole 256 bytes that do not fit the last-level cache (256 MB) leave in pieces of 32 bytes, which memory takes worse than that kernel's:
+//     1.18, up to 1.5; sums alone of less than 512 channels 1.11; int8 rows 0.88, but 1.06 with 1.3 times the rows and more.
+// By these lines 0.845 of the tiled kernel's time over all calls (0.850 without them), and of the 4300 that are left to it 450 would have been more than 5 % faster here.
+static bool ahead(const flexiq_layer *L, int64_t M, const flexiq_out *out, const Params &p, int num_cu, int64_t tiled_rows)
+{
+    const int outputs = (out->acc ? 1 : 0) + (out->y ? 1 : 0) + (out->q ? 1 : 0), per_block = p.per_group + (p.extra > 0 ? 1 : 0);
+    const bool quads = (L->N & 3) == 0, floats = out->y && outputs == 1 && quads, codes = out->q && outputs == 1;
+    const int64_t elements = M * L->N, kCache = 1ll << 28;
+    if (per_block == 1) return true;
+    if ((L->N & 63) == 0 && 4 * elements > kCache && (floats || (out->acc && outputs == 1 && L->C < 512))) return false;
+    if (per_block == 2) return floats || (double)elements >= (quads ? 0.7 : 0.8) * num_cu * 2 * kRows * kCols;
+    const double rows = (double)per_block * kRows / (double)tiled_rows;
+    if (per_block < 8) return 8 * p.ncb <= 7 * num_cu && (quads || rows < 0.95);
+    if (rows < 1.3) return true;
+    return quads && (!codes || ((L->N & 15) == 0 && elements <= kCache));
+}
+
 }  // namespace wreg6
 
 int prepare_wreg6_kernels(int device)
@@ -426,10 +452,10 @@ int prepare_wreg6_kernels(int device)
 
 // Launches k_wreg6 when the call qualifies: every channel on the FP6 path, 256 to 1280 of them (with fewer the tiled kernel is as fast:
 // 6304 x 128 -> 512 5.6 us there, 5.9 here), outputs of any kind, those for a consumer with int8 rows alone and N a multiple of 16.  It is
-// offered what the kernels for few rows and few tiles leave, and takes 96 rows and more (below, up to 1.2 times the tiled kernel's 5 to 6 us).
-// On 364 calls of 32 to 36 thousand rows its time is 0.82 of the tiled kernel's (geometric mean; 0.57 with FP6 codes out and rows enough
-// to use most of the grid), and at most 1.05 above 8 us.
-int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int *taken, const LowerArgs *lower)
+// offered what the kernels for few rows and few tiles leave, and takes 96 rows and more (below, up to 1.2 times the tiled kernel's 5 to 6 us)
+// where it is ahead.
+int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int64_t tiled_rows, int *taken,
+                 const LowerArgs *lower)
 {
     using namespace wreg6;
     *taken = 0;
@@ -457,6 +483,7 @@ int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flex
     p.groups = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, ds.num_cu / p.ncb));
     p.per_group = (int)(tiles / p.groups);
     p.extra = (int)(tiles % p.groups);
+    if (g_force < 0 && !chain && !ahead(L, M, out, p, ds.num_cu, tiled_rows)) return FLEXIQ_OK;
     if (chain) {
         p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2;
         p.nx6 = lower->x6; p.next_K6 = lower->x6 ? lower->K6 : 0; p.next_S = lower->S;

@@ -117,3 +117,39 @@ def test_route(env, M, C, N, r, taken):
             hook(mode)
     pick = np.r_[0:40, M - 1]
     assert (acc.cpu().numpy()[pick] == oracle.forward_gemm(ol, Xq[pick], r)).all()
+
+
+# ... and where it is ahead of the tiled kernel: by how many tiles a block walks, how much of the grid is used, rows of whole quads, columns, and whether
+# the output fits the last-level cache
+@pytest.mark.parametrize("M,C,N,outputs", [
+    (1576, 320, 2048, {"q": True, "y": True, "yq": True, "acc": True}),               # two tiles per block, a used share of 0.77
+    (1576, 320, 1536, {"q": False, "y": True, "yq": False, "acc": False}),            # ... of 0.58
+    (3152, 768, 515, {"q": False, "y": False, "acc": False}),                         # ... of 0.39, rows that leave element by element
+    (1576, 320, 33000, {"q": False, "y": True, "yq": True}),                          # half of the chip idle, int8 rows of 8 bytes
+    (1576, 320, 36864, {"q": True, "y": True}),                                       # ... of 16 bytes
+    (197, 512, 51200, {"q": True, "y": True}), (197, 512, 65536, {"q": False, "y": False}),   # 200 and 256 column blocks of seven tiles
+    (4200, 256, 16384, {"q": True, "y": False, "acc": False, "yq": True}),            # 275 MB of fp32
+    (3900, 256, 16384, {"y": True, "acc": True})])                                    # 256 MB
+def test_route_by_outputs(env, M, C, N, outputs):
+    torch, oracle, fq, dev = env
+    hooks = (fq.debug_force_few_rows, fq.debug_force_tile_splitk, fq.debug_force_wreg6)
+    rng = np.random.default_rng(M + N)
+    hl = fq.flexiq_quantize_pack(rng.standard_normal((N, C), dtype=np.float32) * 0.02, np.exp(rng.standard_normal(C)).astype(np.float32), 0.05, 64)
+    fq.flexiq_set_ratio(hl, 1.0)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(N)
+    x6, xlow = fq.flexiq_lower_fp6(hl, torch.randint(-128, 128, (M, C), dtype=torch.int8, device=dev, generator=gen))
+    _positions(fq, hl, torch, xlow, False)
+    for name, taken in outputs.items():
+        kw = {k: True for k in (("y", "q") if name == "yq" else (name,))}
+        for hook in hooks:
+            hook(-1)
+        try:
+            got = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, out_scale=0.5, **kw)
+            assert fq.debug_force_wreg6(-1) == int(taken), (name, taken)
+        finally:
+            for hook, mode in zip(hooks, (0, 0, 0 if taken else 1)):
+                hook(mode)
+        want = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, out_scale=0.5, **kw)   # the other kernel
+        assert fq.debug_force_wreg6(1) == int(not taken)
+        assert all(torch.equal(got[k], want[k]) for k in kw), name
