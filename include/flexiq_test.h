@@ -80,7 +80,7 @@ int flexiq_debug_halo_plan(const int64_t *call, int64_t *plan);
 /* The kernel that keeps the weights of a block in registers (linear calls of 288 to 1280 channels; last launch: tile shape index -6):
  * 1 = take it whenever the call reaches it and qualifies, 0 = never, -1 = automatic (what the kernels for few rows and short rounds
  * leave, but for calls that leave much of its grid unused).
- * Returns 1 if the last call it was offered ran on it, or 0. */
+ * Returns 1 if the last call it was offered ran on it, 2 if on a build whose fp32 rows leave at once, or 0. */
 int flexiq_debug_force_wreg(int mode);
 
 /* The same for flexiq_mixed_gemm_fp6 (up to 1280 channels): 1 = take it whenever the call reaches it and qualifies, 0 = never,

@@ -72,7 +72,8 @@ template <int N> __device__ __forceinline__ void wait_lds()   // ... LDS operati
 
 // The outputs of a call: any of them; int8 rows and nothing else, N a multiple of 16; those lowered for a consumer; fp32 rows and
 // nothing else, N a multiple of 4.
-enum Out { kAny, kCodes, kLowered, kFloats };
+enum Out { kAny, kCodes, kLowered, kFloats, kFloatsAtOnce };
+constexpr int kOuts = 5;
 
 // NU: units held in registers (C / 32 rounded up to a multiple of eight); EXACT: C = 32 NU.  LOWIN: the kernel lowers the 4-bit
 // channels of its input.
@@ -213,7 +214,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
     // 6304 x 768 -> 3072 27.0 / 27.5 -> 24.3 / 24.4 us, 12608 x 1024 -> 4096 62.5 / 62.9 -> 53.2 / 55.4), and codes of short layers without lowering (12608 x 512 ->
     // 2048 at r = 0 17.2 -> 16.2).  Other codes leave at once: beside the lowering they held up the matrix instructions (12608 x 1024 -> 4096 at
     // r = 1 50.1 -> 52.7), and without it nothing was gained.
-    constexpr bool INTER = NU <= 32 && (OUT == kFloats || (OUT != kAny && NU == 16 && !LOWIN));
+    // (That does not pay where memory itself takes the stores, fp32 rows that do not fit the last-level cache, for all numbers of units: launch_wreg.)
+    constexpr bool FLOATS = OUT == kFloats || OUT == kFloatsAtOnce;
+    constexpr bool INTER = NU <= 32 && (OUT == kFloats || (!FLOATS && OUT != kAny && NU == 16 && !LOWIN));
     constexpr bool REGTAB = OUT != kAny && NU <= (INTER && LOWIN ? 24 : 32);   // the epilogue's constants stay in registers
     constexpr int D = NU <= 32 ? 4 : 2;          // units that activation fragments are read ahead
     // the pieces to lower leave one after the other from the third unit of a half on
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
                 }
             }
             float v = __builtin_fmaf((float)acc[e], __int_as_float(mul[k][j]), __int_as_float(add[k][j]));
-            if constexpr (OUT == kFloats) {
+            if constexpr (FLOATS) {
                 yq[j] = __float_as_int(v);
                 asm volatile("" : "+v"(yq));
                 const uint32_t at = (uint32_t)(fr * p.N + n_blk + c) * 4u;
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
             }
         };
         auto finish = [&](int i) {
-            if constexpr (OUT != kFloats) {
+            if constexpr (!FLOATS) {
                 const FragOut at = {nullptr, nullptr, p.q + (int64_t)(t0 + i) * kRows * p.N, 0.0f, p.N};   // (its rows from this tile on)
                 store_codes(at, qrow, wave, n_blk, fr, fr < p.M - (t0 + i) * kRows, lim_lane, fh);
             }
@@ -305,7 +308,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_wreg(const Params p)
             int lim = p.N - n_blk - 4 * fh;
             asm volatile("" : "+v"(lim));
             const int64_t m = (int64_t)(t0 + i) * kRows + fr;
-            if constexpr (OUT == kFloats) {
+            if constexpr (FLOATS) {
                 if (m < p.M) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
@@ -467,6 +470,7 @@ template <int NU, bool LOWIN, bool EXACT> static Fn pick(int out)
     case kCodes: return k_wreg<NU, kCodes, LOWIN, EXACT>;
     case kLowered: return k_wreg<NU, kLowered, LOWIN, EXACT>;
     case kFloats: return k_wreg<NU, kFloats, LOWIN, EXACT>;
+    case kFloatsAtOnce: return k_wreg<NU, NU <= 32 ? kFloatsAtOnce : kFloats, LOWIN, EXACT>;
     default: return k_wreg<NU, kAny, LOWIN, EXACT>;
     }
 }
@@ -495,8 +499,8 @@ int prepare_wreg_kernels(int device)
     FLEXIQ_HIP(hipGetDeviceProperties(&prop, device));
     g_dev[device].num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     for (int nu = 16; nu <= 40; nu += 8)
-        for (int k = 0; k < 16; ++k)
-            FLEXIQ_HIP(hipFuncSetAttribute((const void *)kernel(nu, k % 4, (k & 4) != 0, (k & 8) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        for (int k = 0; k < 4 * kOuts; ++k)
+            FLEXIQ_HIP(hipFuncSetAttribute((const void *)kernel(nu, k >> 2, (k & 1) != 0, (k & 2) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     g_dev[device].ready = true;
     return FLEXIQ_OK;
 }
@@ -550,11 +554,18 @@ int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_
         if (g_force < 0 && per_block > 1 && used < least) return FLEXIQ_OK;
     }
     if (lowering) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
-    const Out kind = lowering ? kLowered : (q_only ? kCodes : (out->y && !out->q && !out->acc && (L->N & 3) == 0 ? kFloats : kAny));
+    Out kind = lowering ? kLowered : (q_only ? kCodes : (out->y && !out->q && !out->acc && (L->N & 3) == 0 ? kFloats : kAny));
+    // fp32 rows beyond the last-level cache (256 MB): spread over the next tile, time over that of rows that leave at once, 3152 x 36864 (465 MB) / 51200 (646 MB) at
+    // r = 0: 320 channels 0.90 / 0.93, 384 1.04 / 1.11, 512 1.18 / 1.16, 640 1.05 / 1.14, 768 1.33 / 1.38, 896 0.89 / 0.92, 1024 1.12 / 1.11, 448, 576, 704, 832
+    // and 960 0.81 to 0.92; 12608 x 5120 (258 MB) 512 1.00, 768 1.20, 1024 1.10; 12608 x 4096 (207 MB) 0.92 to 1.04.
+    if (kind == kFloats) {
+        const double bytes = 4.0 * (double)M * L->N;
+        if (p.units == nu && nu > 16 ? bytes > 240e6 : (p.units & 3) == 0 && nu < 32 && bytes > 400e6) kind = kFloatsAtOnce;
+    }
     const size_t lds = kTabBytes + (size_t)slots(nu) * stage_bytes(nu);
     FLEXIQ_HIP(launch_kernel(kernel(nu, kind, p.n_low > 0, p.units == nu), dim3((unsigned)(p.ncb * p.groups)), dim3(64 * kWaves), lds, stream_, p));
     *taken = 1;
-    g_last = 1;
+    g_last = kind == kFloatsAtOnce ? 2 : 1;
     return FLEXIQ_OK;
 }
 

@@ -191,3 +191,23 @@ def test_route_by_the_used_share_of_the_grid(env, M, C, N, outs, taken):
         assert (out["q"].cpu().numpy()[pick] == requant_fp32_sequence(ref, ol, 0.5)).all()
     if "y" in outs:
         check_y(out["y"].cpu().numpy()[pick], ref, ol)
+
+
+# fp32 rows beyond the last-level cache leave at once where the number of units asks for it (build 2), the others between the matrix instructions of
+# the next tile (1): below and above 240 MB with all units of 24 and 32 held, below and above 400 MB with 16, 20 of 24 and 28 of 32; ragged rows and columns
+@pytest.mark.parametrize("M,C,N,r,build", [(12607, 768, 4756, 0.0, 1), (12607, 768, 4860, 0.0, 2), (12607, 1024, 4860, 0.5, 2), (12607, 512, 7924, 0.5, 1),
+                                           (12607, 512, 7940, 0.5, 2), (12607, 640, 7940, 0.0, 2), (12607, 384, 7940, 1.0, 2), (12607, 896, 7940, 0.0, 1)])
+def test_fp32_rows_beyond_the_cache(env, M, C, N, r, build):
+    torch, oracle, fq, dev = env
+    rng = np.random.default_rng(C + N)
+    hl = fq.flexiq_quantize_pack(rng.standard_normal((N, C), dtype=np.float32) * 0.02, np.exp(rng.standard_normal(C)).astype(np.float32), 0.05, 32,
+                                 bias=rng.standard_normal(N).astype(np.float32))
+    fq.flexiq_set_ratio(hl, r)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(N)
+    X = torch.randint(-128, 128, (M, C), dtype=torch.int8, device=dev, generator=gen)
+    got = fq.flexiq_mixed_gemm(hl, X, y=True)["y"]
+    assert fq.debug_force_wreg(0) == build
+    want = fq.flexiq_mixed_gemm(hl, X, y=True)["y"]   # the tiled kernel
+    assert fq.debug_force_wreg(1) == 0
+    assert torch.equal(got, want)
