@@ -32,8 +32,9 @@ def _positions(fq, hl, torch, Xd, dynamic):
 
 
 # (M, C, N, gs): every number of K-steps held (4, 8, 12, 16, 20), full and short of one to three; one row, tiles in either half of a
-# block of 64 rows, ragged last tiles; blocks of one, two, three and more tiles than the ring has slots (4 to 6); several column
-# blocks, ragged ones, N not a multiple of 16 and of 4, more column blocks than an XCD's band
+# block of 64 rows, ragged last tiles; blocks of one to four tiles, with 16 and 20 K-steps of more than the ring has slots (the ring in use
+# beyond its slots with every number of K-steps: test_many_tiles_per_block); several column blocks, ragged ones, N not a multiple of 16 and of 4,
+# more column blocks than an XCD's band
 CASES = [(1, 256, 64, 64), (33, 64, 40, 32), (200, 192, 300, 32), (1000, 512, 2048, 64), (700, 320, 515, 32), (97, 448, 6144, 64), (2100, 768, 2049, 64),
          (450, 576, 4112, 32), (3300, 1024, 16384, 64), (830, 832, 16400, 32), (161, 960, 64, 64), (6500, 1280, 4160, 64), (65, 1088, 8200, 32), (4200, 1216, 4864, 64)]
 
@@ -96,7 +97,92 @@ def test_codes_for_a_consumer(env, M, C, N, gs2):
         assert fq.debug_force_wreg6(1) == 1 and torch.equal(rows.to(torch.int32), low), (dynamic, r2)
 
 
-# Which calls it gets: every channel as FP6 and 256 to 1280 of them; (M, C, N, r, kernel: -7 this one, >= 0 the tiled one)
+def _ring(C):
+    """LDS slots for row tiles: six while six of them and the tables fit."""
+    held = -(-C // 256) * 4
+    stage = 1024 * 8 * -(-(3 * held // 2) // 8)
+    return min(6, (160 * 1024 - 2 * 256 * 4) // stage)
+
+
+def _rows_for(torch, C, N, ragged):
+    """Rows that give every block more than twice as many tiles as the ring has slots, and some blocks one more."""
+    groups = torch.cuda.get_device_properties(0).multi_processor_count // -(-N // 256)
+    M = 32 * ((2 * _ring(C) + 1) * groups + 1) - ragged
+    tiles = -(-M // 32)
+    assert groups > 1 and tiles // groups > 2 * _ring(C) and tiles % groups == 1
+    return M
+
+
+# Every number of K-steps held, full and short of one and of three: blocks of more than twice as many tiles as the ring has slots, so that every slot
+# is filled again with rows that are multiplied, and the sums of a tile leave beside the next one many times, some blocks one tile ahead of others
+@pytest.mark.parametrize("C", [256, 192, 64, 512, 448, 320, 768, 704, 576, 1024, 960, 832, 1280, 1216, 1088])
+def test_many_tiles_per_block(env, C):
+    torch, oracle, fq, dev = env
+    N = 64 * torch.cuda.get_device_properties(0).multi_processor_count + 16   # a last column block of 16 columns
+    M = _rows_for(torch, C, N, 11)
+    case = workloads.make_linear("wreg6ring", 22, C, M, C, N, 32)
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[:, ol.perm])
+    Xd = torch.from_numpy(Xq).to(dev)
+    rows = np.r_[0, 31, 32, 32 * _ring(C) + 3, M // 2, M - 33, M - 1]
+    fq.flexiq_set_ratio(hl, 1.0)
+    _positions(fq, hl, torch, Xd, False)
+    x6, xlow = fq.flexiq_lower_fp6(hl, Xd)
+    ref = oracle.forward_gemm(ol, np.ascontiguousarray(Xq[rows]), 1.0)
+    so = float(np.abs(oracle.dequant_f64(ref, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9)
+    fq.debug_force_wreg6(0)   # the tiled kernel: every row
+    want = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, acc=True, y=True, q=True, out_scale=so)
+    assert fq.debug_force_wreg6(1) == 0
+    assert (want["acc"].cpu().numpy()[rows] == ref).all() and (want["q"].cpu().numpy()[rows] == requant_fp32_sequence(ref, ol, so)).all()
+    for kinds in ("q", "y", ("acc", "y", "q")):
+        got = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, out_scale=so, **{k: True for k in kinds})
+        assert fq.debug_force_wreg6(1) == 1
+        for k in kinds:
+            assert torch.equal(got[k], want[k]), (k, len(kinds))
+
+
+# the same for the builds that write a consumer's FP6 codes and lowered rows (of at most 159 channel groups: fewer columns, more rows)
+@pytest.mark.parametrize("C", [256, 64, 512, 320, 768, 576, 1024, 832, 1280, 1088])
+def test_many_tiles_per_block_for_a_consumer(env, C):
+    torch, oracle, fq, dev = env
+    N = 5120
+    M = _rows_for(torch, C, N, 5)
+    first = workloads.make_linear("wreg6ring1", 22, C, M, C, N, 64)
+    second = workloads.make_linear("wreg6ring2", 22, C + 1, 64, N, 64, 32)
+    x_scale = oracle.absmax_scale(first.Xcal)
+    W2, amax2, scale2 = second.W.reshape(64, N), np.abs(second.Xcal).max(0), float(np.abs(second.Xcal).max() / 127)
+    h2 = fq.flexiq_quantize_pack(W2, amax2, scale2, 64)
+    hl = fq.flexiq_quantize_pack(first.W, np.abs(first.Xcal).max(0), x_scale, 64, bias=first.bias, out_perm=h2.info()["perm"])
+    X = torch.from_numpy(np.ascontiguousarray(oracle.quantize(first.X, x_scale)[:, hl.info()["perm"]])).to(dev)
+    fq.flexiq_set_ratio(hl, 1.0)
+    _positions(fq, hl, torch, X, False)
+    x6, xlow = fq.flexiq_lower_fp6(hl, X)
+    so = float(fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, y=True)["y"].abs().max()) / 127
+    plain = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, q=True, out_scale=so)["q"]
+    assert fq.debug_force_wreg6(1) == 1
+    for r2 in (1.0, 0.4):
+        k4 = fq.flexiq_set_ratio(h2, r2)
+        k6 = fq.flexiq_fp6_channels(h2)
+        assert 0 < k6 <= k4
+        x6o = torch.zeros(fq.flexiq_fp6_bytes(h2, M), dtype=torch.uint8, device=dev)
+        got = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, q=True, out_scale=so, lower_for=h2, x6_out=x6o)["q"]
+        assert fq.debug_force_wreg6(1) == 1
+        rows = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, q=True, out_scale=so, lower_for=h2)["q"]
+        assert fq.debug_force_wreg6(0) == 1
+        t6 = torch.zeros_like(x6o)
+        tiled = fq.flexiq_mixed_gemm_fp6(hl, xlow, x6, q=True, out_scale=so, lower_for=h2, x6_out=t6)["q"]
+        assert fq.debug_force_wreg6(1) == 0
+        assert torch.equal(x6o, t6) and torch.equal(got[:, k6:], tiled[:, k6:]), r2
+        # ... and from the definition: the packer's FP6 codes of the plain rows, the consumer's 4-bit channels clamped and cleared
+        want6 = torch.zeros_like(x6o)
+        fq.flexiq_lower_fp6(h2, plain, x6=want6)
+        sh = torch.from_numpy(np.repeat(fq.flexiq_layer_positions(h2).astype(np.int32), 64)[:k4]).to(dev)
+        low = plain.to(torch.int32)
+        low[:, :k4] = ((low[:, :k4] >> sh).clamp(-8, 7)) << sh
+        assert torch.equal(x6o, want6) and torch.equal(rows.to(torch.int32), low), r2
+
+
+# Which calls it gets: every channel as FP6 and 256 to 1280 of them; (M, C, N, r, taken: by this kernel, else by the tiled one)
 @pytest.mark.parametrize("M,C,N,r,taken", [(3000, 1024, 1024, 1.0, True), (3000, 1024, 1024, 0.5, False), (3000, 1344, 1024, 1.0, False), (6000, 192, 1024, 1.0, False),
                                            (6000, 256, 1024, 1.0, True)])
 def test_route(env, M, C, N, r, taken):
