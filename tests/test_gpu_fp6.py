@@ -118,6 +118,17 @@ def test_fp6_gemm_ragged_shapes(env, M, K, N, gs):
     _run_fp6_case(env, case, sorted({0.0, 1.0, 0.5, 1.0 / G, 3.0 / G if G >= 3 else 1.0}))
 
 
+@pytest.mark.parametrize("K", [1024, 1088])
+@pytest.mark.parametrize("groups", [15, 16, 23, 24])
+def test_fp6_gemm_long_prefix_with_int8_steps(env, K, groups):
+    # every tile shape with 7, 8, 11 and 12 FP6 K-steps (all of them but the last few in the loop of constant wait counts), a 4-bit group outside the
+    # prefix where their number is odd, and int8 steps behind; several ragged tiles of every shape
+    case = workloads.make_linear("fp6long", 8, 450 + K + groups, 531, K, 523, 32, outlier_frac=0.02)
+    hl = _run_fp6_case(env, case, ((groups - 0.5) / (K // 32),), scale=2.0)
+    fq = env[2]
+    assert fq.flexiq_fp6_channels(hl) == groups // 2 * 64 and fq.flexiq_set_ratio(hl, (groups - 0.5) / (K // 32)) == groups * 32
+
+
 def test_fp6_gemm_saturating_inputs(env):
     # activations far beyond the calibrated range: the clamp of the lowering is active everywhere
     case = workloads.make_linear("fp6sat", 8, 420, 96, 128, 64, 32)
