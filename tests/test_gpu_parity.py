@@ -105,10 +105,12 @@ def test_permute_channels(env):
 
 
 @pytest.mark.parametrize("C,gs,rows", [(32, 32, 1), (96, 32, 1000), (768, 32, 333), (4096, 64, 37), (4128, 32, 9),
-                                       (8192, 64, 6), (10176, 64, 5), (64, 32, 3000)])
+                                       (8192, 64, 6), (10176, 64, 5), (64, 32, 3000), (768, 32, 5200), (4096, 64, 1030), (4128, 32, 1025), (4128, 32, 1539),
+                                       (5088, 32, 2053), (8192, 64, 1027), (10176, 64, 1026), (10176, 64, 2051)])
 def test_permute_channels_row_lengths(env, C, gs, rows):
-    """Row lengths on every route of the reorder operator: several rows per staged run, one, long rows dealt out over
-    the block (up to the 159 groups of 64 channels a layer may have)."""
+    """Row lengths on every route of the reorder operator: several rows per pass of a block, one, long rows dealt out over
+    the block (up to the 159 groups of 64 channels a layer may have); runs of one pass (few rows), and of two, three and four with a ragged last
+    one (from 1024 passes over all rows on)."""
     torch, oracle, fq, dev = env
     rng = np.random.default_rng(7000 + C)
     W = rng.normal(0, 0.02, size=(8, C)).astype(np.float32)

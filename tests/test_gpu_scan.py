@@ -1,5 +1,6 @@
 """GPU parity of the scan for run-time extraction positions at the edges of its block layout: a lone row, rows that are not a multiple of a
-thread's trip, one group and all groups, more than 256 pieces of 16 channels (two columns of blocks), against the oracle (whole numbers)."""
+thread's trip, one group and all groups, more than 64 groups in a block, more than 256 pieces of 16 channels (several columns of blocks), through both
+entry points, against the oracle (whole numbers)."""
 import numpy as np
 import pytest
 
@@ -32,4 +33,8 @@ def test_scan_edges(M, C, gs):
         want = oracle.dynamic_act_shifts(X, gs, g4, ol.a_shift)
         for _ in range(2):   # (the second call finds the scan words as the first one left them)
             fq.flexiq_dynamic_positions(hl, Xd)
+            assert np.array_equal(fq.flexiq_layer_positions(hl)[:G], want[:G]), (M, C, gs, r)
+        for _ in range(2):   # the scan whose words are shared by all blocks and layers
+            fq.flexiq_static_positions(hl)
+            fq.flexiq_dynamic_positions_static(hl, Xd)
             assert np.array_equal(fq.flexiq_layer_positions(hl)[:G], want[:G]), (M, C, gs, r)
