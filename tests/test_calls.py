@@ -1,5 +1,6 @@
-"""The native calls of the binding (csrc/calls.cpp) against the functions of binding.py that they stand for: the same results, the same
-refusals."""
+"""The native calls of the binding (csrc/calls.cpp) against the functions of binding.py that they stand for.  On the CPU: what they are as objects,
+and the refusal of what is no layer, no GPU tensor or no argument list of theirs.  On the GPU: the same results, the same refusals of GPU tensors that
+do not fit a live layer, and the stream."""
 import copy
 import inspect
 import pickle
@@ -133,3 +134,91 @@ def test_same_results_as_the_functions_they_stand_for():
 
     for a, b in zip(run(native), run(plain)):
         assert (a is None and b is None) or (a.dtype == b.dtype and a.shape == b.shape and a.device == b.device and torch.equal(a, b))
+
+
+def _live(fq, workloads):
+    """A linear layer of 128 channels, one that reads its 256 outputs, and a convolution, all at 3/4 of the channels at 4 bits."""
+    first, second, cv = (workloads.make_linear("calls", 31, 1, 70, 128, 256, 32), workloads.make_linear("calls2", 31, 2, 70, 256, 64, 32),
+                         workloads.make_conv("calls3", 31, 3, 2, 9, 7, 64, 64, 3, 3, 2, 1, 32))
+    layers = [both_layers(c)[1] for c in (first, second, cv)]
+    for h in layers:
+        fq.flexiq_set_ratio(h, 0.75)
+    return layers
+
+
+@pytest.mark.gpu
+def test_tensors_that_do_not_fit_a_live_layer():
+    """What the native checks let through would go to a kernel: type, contiguity, the number of dimensions and the channels."""
+    import torch
+    import paper_2510_02822_amd as fq
+    dev = torch.device("cuda:0")
+    h, _, hc = _live(fq, workloads)
+    rows = torch.zeros(70, 128, dtype=torch.int8, device=dev)
+    image = torch.zeros(2, 9, 7, 64, dtype=torch.int8, device=dev)
+    x6 = torch.zeros(fq.flexiq_fp6_bytes(h, 70), dtype=torch.uint8, device=dev)
+    x4 = torch.zeros(70, 64, dtype=torch.uint8, device=dev)
+    bad_rows = [rows.to(torch.uint8), rows.to(torch.int32), rows.t().contiguous().t(), torch.zeros(70, 256, dtype=torch.int8, device=dev)[:, ::2], rows[:, :64].contiguous(),
+                torch.zeros(70, 256, dtype=torch.int8, device=dev), rows[0], rows.view(7, 10, 128), rows.cpu()]
+    bad_images = [image.to(torch.uint8), image.permute(0, 3, 1, 2), image[:, :, :, :32].contiguous(), torch.zeros(2, 9, 7, 96, dtype=torch.int8, device=dev), image[0], image[None], image.cpu()]
+    calls = [(fq.flexiq_mixed_gemm, lambda x: (h, x, True), bad_rows), (fq.flexiq_mixed_gemm_fp6, lambda x: (h, x, x6, True), bad_rows),
+             (fq.flexiq_mixed_gemm_packed4, lambda x: (h, x, x4, True), bad_rows), (fq.flexiq_lower_fp6, lambda x: (h, x), bad_rows),
+             (fq.flexiq_lower_packed4, lambda x: (h, x), bad_rows), (fq.flexiq_mixed_conv_implicit, lambda x: (hc, x, 2, 1, True), bad_images),
+             (fq.flexiq_dynamic_positions, lambda x: (h, x), bad_rows[:6] + bad_rows[8:]),   # (any number of dimensions)
+             (fq.flexiq_permute_channels, lambda x: (h, x), bad_rows[:4] + bad_rows[8:]),    # (... and whole rows of its own)
+             (fq.flexiq_quantize_act, lambda x: (x, 0.5), [rows, rows.half(), rows.double(), torch.zeros(70, 128, device=dev).t(), torch.zeros(70, 128)])]
+    for f, arguments, bad in calls:
+        for x in bad:
+            for g in (f, f.__wrapped__):
+                with pytest.raises(AssertionError):
+                    g(*arguments(x))
+    assert fq.flexiq_dynamic_positions(h, rows.view(7, 10, 128)) is None   # what is accepted: sizes that are no plain integers too
+    fq.flexiq_static_positions(h)
+    want = fq.flexiq_mixed_gemm(h, rows, True)["acc"]
+    h.N, h.C = np.int64(h.N), np.int64(h.C)
+    assert torch.equal(fq.flexiq_mixed_gemm(h, rows, True)["acc"], want)
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream():
+    """Captured on a stream of their own: work on any other stream would not be in the graph, whose replays write every output again."""
+    import torch
+    import paper_2510_02822_amd as fq
+    dev = torch.device("cuda:0")
+    h, _, hc = _live(fq, workloads)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    x = torch.randint(-128, 128, (70, 128), dtype=torch.int8, device=dev, generator=gen)
+    small = torch.randint(-2, 3, (70, 128), dtype=torch.int8, device=dev, generator=gen)
+    image = torch.randint(-128, 128, (2, 9, 7, 64), dtype=torch.int8, device=dev, generator=gen)
+    xf = torch.randn(70, 128, device=dev, generator=gen)
+    x6, xlow = fq.flexiq_lower_fp6(h, x)
+    x4 = fq.flexiq_lower_packed4(h, x)
+    own = torch.zeros_like(x6)   # (rows of the last 64 and K-steps that the packer does not write stay zero)
+    calls = [lambda: [fq.flexiq_mixed_gemm(h, x, acc=True)["acc"]], lambda: [fq.flexiq_mixed_gemm_fp6(h, xlow, x6, y=True)["y"]],
+             lambda: [fq.flexiq_mixed_gemm_packed4(h, x, x4, q=True, out_scale=0.5)["q"]], lambda: [fq.flexiq_mixed_conv_implicit(hc, image, 2, 1, acc=True)["acc"]],
+             lambda: list(fq.flexiq_lower_fp6(h, x, x6=own, need_xlow=True)), lambda: [fq.flexiq_lower_packed4(h, x)[:, :32]], lambda: [fq.flexiq_quantize_act(xf, 0.02)],
+             lambda: [fq.flexiq_permute_channels(h, x)]]
+    for call in calls:
+        want = [o.clone() for o in call()]
+        assert all(o.any().item() for o in want)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            outs = call()
+        for _ in range(3):
+            for o in outs:
+                o.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(o, w) for o, w in zip(outs, want))
+    fq.flexiq_dynamic_positions(h, x)
+    want = fq.flexiq_layer_positions(h).copy()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fq.flexiq_dynamic_positions(h, x)
+    for _ in range(3):
+        fq.flexiq_dynamic_positions(h, small)
+        assert not np.array_equal(fq.flexiq_layer_positions(h), want)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(fq.flexiq_layer_positions(h), want)
