@@ -174,7 +174,9 @@ def test_tensors_that_do_not_fit_a_live_layer():
     assert fq.flexiq_dynamic_positions(h, rows.view(7, 10, 128)) is None   # what is accepted: sizes that are no plain integers too
     fq.flexiq_static_positions(h)
     want = fq.flexiq_mixed_gemm(h, rows, True)["acc"]
-    h.N, h.C = np.int64(h.N), np.int64(h.C)
+    vars(h)["N"] = 512   # (more than it has: the output is as large as the attribute says at the time of the call)
+    assert fq.flexiq_mixed_gemm(h, rows, True)["acc"].shape == fq.flexiq_mixed_gemm.__wrapped__(h, rows, True)["acc"].shape == (70, 512)
+    h.N, h.C = np.int64(256), np.int64(128)
     assert torch.equal(fq.flexiq_mixed_gemm(h, rows, True)["acc"], want)
 
 
