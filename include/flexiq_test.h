@@ -84,7 +84,7 @@ int flexiq_debug_halo_plan(const int64_t *call, int64_t *plan);
 int flexiq_debug_force_wreg(int mode);
 
 /* The same for flexiq_mixed_gemm_fp6 (up to 1280 channels): 1 = take it whenever the call reaches it and qualifies, 0 = never,
- * -1 = automatic.  Returns 1 if the last call it was offered ran on it, or 0. */
+ * -1 = automatic (where it is ahead of the tiled kernel).  Returns 1 if the last call it was offered ran on it, or 0. */
 int flexiq_debug_force_wreg6(int mode);
 
 /* Force tile shape `index` of the FP6-variant kernel's table (-1 = automatic).  Returns the table size. */

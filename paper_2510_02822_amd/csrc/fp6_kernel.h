@@ -259,8 +259,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_fp6(const Params 
     };
     using std::integral_constant;
 
-    // ---- prologue: tables (scales, biases, consumer positions per column, activation positions per group) and K-steps
-    // 0, 1, 2 on their way, all straight into LDS
+    // ---- prologue: tables (scales, biases, consumer positions per column, activation positions per group) and the first
+    // K-steps on their way (all stages of the ring but one: three, with every channel FP6 five), all straight into LDS
     {
         const __amdgpu_buffer_rsrc_t rcs = __builtin_amdgcn_make_buffer_rsrc((void *)p.cs, 0, 2 * p.Npad * 4, kRsrcFlags);
         const __amdgpu_buffer_rsrc_t ras = __builtin_amdgcn_make_buffer_rsrc((void *)p.ashift, 0, (p.C >> (5 + p.gs_shift)) * 4 + 4, kRsrcFlags);

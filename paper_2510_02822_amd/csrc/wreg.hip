@@ -15,12 +15,13 @@
 //     stores (2060 cycles).
 //   * Each XCD serves few column blocks and many row groups, so that its L2 fetches few of the weights before the first tile can
 //     begin: bands of eight column blocks; with all column blocks on every XCD 6304 x 768 -> 3072 took 18.5 us instead of 16.9.
-// What bounds it now: power.  On zeros the card holds 2.2 GHz and 12608 x 1024 -> 4096 takes 35 us, on activations 1.6 GHz and 44 to
-// 46 us; matrix instructions alone, no LDS reads, copies or epilogue, take 36 us there.
+// What bounds it now: on many tiles the clock.  12608 x 1024 -> 4096 takes 33.1 us on zeros and 40.9 on activations (r = 0.5: 39.0 and 44.1) in the same
+// number of cycles; matrix instructions alone, no LDS reads, copies or epilogue, take 36 us on activations.  Not on few: 6304 x 768 -> 3072, four tiles per
+// block, takes 14.3 and 14.8, 3 us of it the weights' way into registers and the rest launch, tiles and last stores.
 //
 // Measured (graph replays, us in the tiled kernel and here): 6304 x 768 -> 3072, int8 out, r = 0 / 0.5 / 1: 21.7 / 22.5 / 24.2 and 17.8 /
-// 19.1 / 20.8, fp32 out 41.5 and 26.9; 12608 x 1024 -> 4096: 62 / 67 / 68 and 46 / 51 / 53, input lowered by its producer 63 and 45, fp32
-// out 126 and 65; 12608 x 1216 -> 4864 at r = 0 / 1: 80 / 80 and 63 / 75; 1576 x 768 -> 3072 9.6 and 8.2.
+// 19.1 / 20.8, fp32 out (r = 0.5) 42.3 and 25.0; 12608 x 1024 -> 4096: 62 / 67 / 68 and 46 / 51 / 53, input lowered by its producer 63 and 45, fp32
+// out (r = 0.5) 128 and 59; 12608 x 1216 -> 4864 at r = 0 / 1: 80 / 80 and 63 / 75; 1576 x 768 -> 3072 9.6 and 8.2.
 #include <algorithm>
 
 #include "flexiq_internal.h"

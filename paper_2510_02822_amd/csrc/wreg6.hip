@@ -15,9 +15,10 @@
 //   * A consumer's FP6 codes: five operations make a code of a sum (scale, clamp, round, to the consumer's position, floor), one instruction
 //     packs the sixteen of a lane.
 // What bounds it now: reads of LDS (24 bytes a lane per 32 matrix cycles, 1020 + 190 cycles per tile of 16 K-steps with the copies) beside
-// the matrix instructions, power (0.84 us per tile, 0.69 on zeros), and about 8 us of weight loads, launch and last stores.  Four waves of
+// the matrix instructions, the clock (12608 x 1024 -> 4096 28.1 us on activations and 24.3 on zeros, in the same number of cycles), and about 8 us of weight
+// loads, launch and last stores.  Four waves of
 // 64 columns, which read half as much, were no faster (0.86 us): one wave per SIMD issues an instruction in four to five cycles.  A form with
-// int8 K-steps behind the FP6 ones (a branch per step) needs more registers than there are from 13 K-steps on: 0.4 to 0.9 times the
+// int8 K-steps behind the FP6 ones (a branch per step) needs more registers than there are from 13 K-steps on: 0.4 to 0.97 times the
 // tiled kernel's speed.
 //
 // Measured (graph replays, us in the tiled kernel's build without int8 operands and here, r = 1; int8 codes / fp32 / FP6 codes for a consumer): 12608 x 1024 ->
