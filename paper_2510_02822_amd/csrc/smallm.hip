@@ -28,6 +28,8 @@ typedef short v2s __attribute__((ext_vector_type(2)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+constexpr int kRsrcFlags = 0x00020000;
+
 // clamp(v, -(8 << s), (8 << s) - 1) with the low s bits cleared, on the four int8 lanes of a dword: the bit-lowered
 // value L(v, s) put back at its position (Section 4.1)
 __device__ __forceinline__ uint32_t lower4(uint32_t d, int s)
@@ -525,10 +527,18 @@ __global__ __launch_bounds__(512) void k_few_rows_dot(const RowsParams p)
 //
 // The tiled kernel gives such a call a handful of 64 x 64 blocks that each walk the whole reduction, one barrier per
 // K-step: bound by the latency of a step (ViT-L fc2 with 197 rows: 64 steps, 14.6 us at r = 0 and 22.1 us at r = 1 for
-// 0.3 us of matrix work).  Here the eight waves of a block take the K-steps wave, wave + 8, ... of the tile on their own:
-// operands straight from global memory into MFMA registers (every byte of the tile's weights and activations is loaded by
-// exactly one lane of the block), sixteen v_mfma_i32_16x16x64_i8 per K-step and wave, no barrier until the waves' sums
-// meet in LDS.  4-bit units come from the position-expanded weight copy and their activations are lowered in registers.
+// 0.3 us of matrix work).  Here the eight waves of a block take the K-steps wave, wave + 8, ... of the tile on their own
+// (every byte of the tile's weights and activations is loaded by exactly one lane of the block), sixteen v_mfma_i32_16x16x64_i8
+// per K-step and wave, no barrier until the waves' sums meet in LDS.  4-bit units come from the position-expanded weight copy and
+// their activations are lowered in registers.
+// What bounds it is the rate at which a compute unit pulls its operands, and that depends on which lane loads what: a wave load whose
+// neighbouring lanes read neighbouring 16-byte pieces (64 or more bytes of a row) delivers 46 B/clk per compute unit, one in the order of the MFMA operand
+// (neighbouring lanes on sixteen different rows) 15 (128 KB per block, 256 blocks: 2850 and 8560 cycles).  The packed weights lie in operand
+// order; activation rows do not.  They are loaded four lanes to a row and cross the wave's lanes through its own part of LDS (no barrier:
+// LDS serves a wave's accesses in order).  The sums are finished four lanes to a row as well, so the stores are whole 64-byte runs of fp32.
+// int8 out, r = 0 / 0.5 / 1, loaded in operand order and now: 197 x 4096 -> 1024 7.4 / 7.7 / 8.1 and 5.5 / 6.1 / 7.0 us; 512 x 3072 -> 768 7.3 / 7.6 / 7.9
+// and 5.7 / 6.0 / 6.7; 1024 x 4096 -> 1024 13.9 / 14.2 / 14.6 and 11.5 / 12.3 / 14.1; 40 x 832 -> 192 3.75 / 3.9 / 4.1 and 3.1 / 3.3 / 3.4.  (Tried: masking
+// alone where no byte of a wave reaches the clamp: no gain, a wave of 1024 and more activations nearly always holds one.)
 // FR x FC: 16 x 16 fragments of the tile (rows x columns), NW: waves.  A smaller tile means more blocks, i.e. more compute
 // units pulling operands, at more operand bytes per multiply.
 // FP6: the leading s6 K-steps run first on `v_mfma_scale_f32_16x16x128_f8f6f4`, as in the FP6 build of k_few_rows (chunks of
@@ -539,6 +549,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
 {
     constexpr int kTileRows = 16 * FR, kTileCols = 16 * FC, kTileWaves = NW, NF = FR * FC;
     constexpr int E = (NF + NW - 1) / NW;   // fragments a wave finishes: wave, wave + NW, ...
+    constexpr int kStage = NF > FR ? NF : FR;   // KB of LDS per wave: its sums, and before that the activations that cross its lanes
     extern __shared__ __align__(16) unsigned char lds[];   // [waves][fragments][64 lanes] accumulator quads
     v4i *const red = reinterpret_cast<v4i *>(lds);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -548,13 +559,14 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
     const int m0 = blockIdx.y * kTileRows;
 
     // the epilogue's scales and biases travel with the first operands
-    // (fragment id = FC f + g: rows m0 + 16 f + c, columns n0 + 16 g + 4 qd + i)
+    // (fragment id = FC f + g: rows m0 + 16 f + er, columns n0 + 16 g + 4 eq + i: four neighbouring lanes finish 16 columns of a row)
+    const int er = lane >> 2, eq = lane & 3;
     float cs4[E][4], bi4[E][4];
 #pragma unroll
     for (int e = 0; e < E; ++e)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int nn = n0 + 16 * ((wave + NW * e) % FC) + 4 * qd + i;   // < Npad
+            const int nn = n0 + 16 * ((wave + NW * e) % FC) + 4 * eq + i;   // < Npad
             cs4[e][i] = p.cs[nn];
             bi4[e][i] = p.cs[p.Npad + nn];
         }
@@ -563,7 +575,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
     int sn_e[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int nn0 = n0 + 16 * ((wave + NW * e) % FC) + 4 * qd;
+        const int nn0 = n0 + 16 * ((wave + NW * e) % FC) + 4 * eq;
         const bool to6 = FP6 && p.nx6 != nullptr && nn0 < p.next_K6;
         sn_e[e] = p.next_ashift != nullptr && (to6 || nn0 < p.next_K4) ? p.next_ashift[nn0 >> p.next_gs_log2] : 4;
     }
@@ -633,48 +645,80 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
                 acc[f][g] = (v4i){(int)accf[f][g].x, (int)accf[f][g].y, (int)accf[f][g].z, (int)accf[f][g].w};   // exact integers below 2^24
         first = p.s6 + (wave + NW - chunks % NW) % NW;   // the int8 K-steps continue the deal
     }
-    // UN K-steps in flight per wave
-    for (int ks0 = first; ks0 < p.steps; ks0 += kTileWaves * UN) {
+    // ---- the int8 K-steps first, first + NW, ...: UN of them in flight per wave, each slot loaded again as soon as it is used up
+    if (first < p.steps) {
+        unsigned char *const mine = lds + wave * kStage * 1024;
+        const int rows = min(p.M - m0, kTileRows);
+        // (rows beyond M and channels beyond the last row read as zero; the pad unit of an odd unit count has zero weights)
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)(p.X + (int64_t)m0 * p.C), 0, rows * p.C, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.W8, 0, 2 * p.w4x_delta, kRsrcFlags);
+        const int xr = lane >> 2, xp = lane & 3;   // row of a fragment and 16-byte piece of the K-step that this lane loads
+        const int xoff = xr * p.C + 16 * xp;
+        unsigned char *const put = mine + xr * 64 + 16 * (xp ^ (xr >> 2));
+        const unsigned char *const get = mine + c * 64 + 16 * (qd ^ (c >> 2));
+        const int woff = (qd * p.Npad + n0 + c) * 16;
         v4i w8[UN][FC], x[UN][FR];
-        int sa[UN];
-        bool low[UN];
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            const int ks = ks0 + k * kTileWaves;
-            const int u = 2 * ks + (qd >> 1), h = qd & 1;   // this lane's unit and k-half
-            const bool valid = ks < p.steps && u < p.units;
-            low[k] = valid && u < p.units4;
-            sa[k] = low[k] && !p.x_pre ? p.ashift[u >> p.gs_shift] : 0;
-#pragma unroll
-            for (int g = 0; g < FC; ++g)
-                w8[k][g] = valid ? *reinterpret_cast<const v4i *>(p.W8 + (low[k] ? p.w4x_delta : 0) + (((int64_t)u * 2 + h) * p.Npad + n0 + 16 * g + c) * 16)
-                                 : (v4i){0, 0, 0, 0};
-#pragma unroll
-            for (int f = 0; f < FR; ++f) {
-                const int m = m0 + 16 * f + c;
-                x[k][f] = valid && m < p.M ? *reinterpret_cast<const v4i *>(p.X + (int64_t)m * p.C + u * 32 + 16 * h) : (v4i){0, 0, 0, 0};
+        int sa0[UN], sa1[UN];
+        auto load = [&](int k, int ks) {
+            if constexpr (!FP6) {   // (scalar, and ahead of its use: a vector load would wait for all of the operands in flight; the table has an entry for the pad unit)
+                sa0[k] = p.ashift[2 * ks >> p.gs_shift];
+                sa1[k] = p.ashift[(2 * ks + 1) >> p.gs_shift];
             }
-        }
+            const int wo = woff + (2 * ks + (qd >> 1) < p.units4 ? p.w4x_delta : 0);
 #pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            if (low[k] && !p.x_pre) {
+            for (int f = 0; f < FR; ++f) x[k][f] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, xoff + 16 * f * p.C + 64 * ks, 0, 0));
+#pragma unroll
+            for (int g = 0; g < FC; ++g) w8[k][g] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, wo + 256 * g, ks * 64 * p.Npad, 0));
+        };
+        auto use = [&](int k, int ks) {
+            const int u = 2 * ks + (xp >> 1);
+            if (!FP6 && !p.x_pre && 2 * ks < p.units4) {   // (lowered before it crosses the lanes: fewer registers live)
+                const bool mine4 = u < p.units4;   // (false: a unit read at 8 bits)
+                const int sa = xp >> 1 ? sa1[k] : sa0[k];
 #pragma unroll
                 for (int f = 0; f < FR; ++f)
-                    x[k][f] = (v4i){(int)lower4((uint32_t)x[k][f].x, sa[k]), (int)lower4((uint32_t)x[k][f].y, sa[k]),
-                                    (int)lower4((uint32_t)x[k][f].z, sa[k]), (int)lower4((uint32_t)x[k][f].w, sa[k])};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[k][f][i] = mine4 ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
             }
+#pragma unroll
+            for (int f = 0; f < FR; ++f) *reinterpret_cast<v4i *>(put + 1024 * f) = x[k][f];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            v4i b[FR];
+#pragma unroll
+            for (int f = 0; f < FR; ++f) b[f] = *reinterpret_cast<const v4i *>(get + 1024 * f);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int f = 0; f < FR; ++f)
 #pragma unroll
-                for (int g = 0; g < FC; ++g) acc[f][g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k][g], x[k][f], acc[f][g], 0, 0, 0);
+                for (int g = 0; g < FC; ++g) acc[f][g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k][g], b[f], acc[f][g], 0, 0, 0);
+        };
+        int left = (p.steps - first + NW - 1) / NW, ks = first;
+#pragma unroll
+        for (int k = 0; k < UN; ++k)
+            if (k < left) load(k, ks + k * NW);
+        for (; left >= 2 * UN; left -= UN, ks += NW * UN) {
+#pragma unroll
+            for (int k = 0; k < UN; ++k) {
+                use(k, ks + k * NW);
+                load(k, ks + (k + UN) * NW);
+            }
         }
+#pragma unroll
+        for (int k = 0; k < 2 * UN - 1; ++k)
+            if (k < left) {
+                use(k % UN, ks + k * NW);
+                if (k + UN < left) load(k % UN, ks + (k + UN) * NW);
+            }
     }
 
     // ---- the waves' sums meet in LDS; wave w adds up and finishes fragments w, w + NW, ...
+    const int slot = 16 * qd + (c ^ (4 * qd));   // (the quads of a row are read by four neighbouring lanes below: no bank twice in either pattern)
 #pragma unroll
     for (int f = 0; f < FR; ++f)
 #pragma unroll
-        for (int g = 0; g < FC; ++g) red[(wave * NF + FC * f + g) * 64 + lane] = acc[f][g];
+        for (int g = 0; g < FC; ++g) red[(wave * NF + FC * f + g) * 64 + slot] = acc[f][g];
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -682,8 +726,8 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
         if (id >= NF) break;
         v4i s = {0, 0, 0, 0};
 #pragma unroll
-        for (int w = 0; w < kTileWaves; ++w) s += red[(w * NF + id) * 64 + lane];
-        const int m = m0 + 16 * f + c, nn0 = n0 + 16 * g + 4 * qd;
+        for (int w = 0; w < kTileWaves; ++w) s += red[(w * NF + id) * 64 + 16 * eq + (er ^ (4 * eq))];
+        const int m = m0 + 16 * f + er, nn0 = n0 + 16 * g + 4 * eq;
         if (m >= p.M || nn0 >= p.N) continue;
         const int64_t o = (int64_t)m * p.N + nn0;
         float yv[4];

@@ -182,6 +182,28 @@ def test_tile_splitk_kernel(env, M, K, N, gs, shape):
         fq.debug_force_tile_splitk(-1)
 
 
+# fewer K-steps of a wave than it has in flight, between once and twice as many, more; a last K-step of one unit; rows that end in a tile
+@pytest.mark.parametrize("units,gs", [(2 * 15, 32), (2 * 17 - 1, 32), (2 * 33, 32), (2 * 50 - 1, 32), (2 * 65, 32), (2 * 129, 64)])
+@pytest.mark.parametrize("shape", [2, 3, 4])
+def test_tile_splitk_reductions(env, units, gs, shape):
+    torch, oracle, fq, dev = env
+    M, K, N = 71, 32 * units, 40
+    case = workloads.make_linear("tilered", 8, 1100 + units, M, K, N, gs, outlier_frac=0.02)
+    case.X *= 2.0
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[:, ol.perm])
+    Xd = torch.from_numpy(Xq).to(dev)
+    fq.debug_force_tile_splitk(shape)
+    try:
+        for r in (0.0, 96.0 / K, 0.5, 1.0):   # (an odd number of 4-bit groups: a K-step of both kinds)
+            fq.flexiq_set_ratio(hl, r)
+            got = fq.flexiq_mixed_gemm(hl, Xd, acc=True)["acc"]
+            assert fq.debug_last_launch()["tile"] == -5
+            assert (got.cpu().numpy() == oracle.forward_gemm(ol, Xq, r)).all(), r
+    finally:
+        fq.debug_force_tile_splitk(-1)
+
+
 @pytest.mark.parametrize("M,K1,N1,N2,gs2", [(100, 1024, 520, 128, 32), (197, 256, 136, 64, 32), (33, 2048, 256, 24, 64)])
 @pytest.mark.parametrize("shape", [2, 3, 4])
 def test_tile_splitk_lower_for_consumer(env, M, K1, N1, N2, gs2, shape):
