@@ -54,6 +54,11 @@ __device__ __forceinline__ uint32_t lower4(uint32_t d, int s)
 // n0 + lane % 16 resp. activation row 16 f + lane % 16, channels 16 (lane / 16) ... of the K-step) and leaves its
 // accumulators in LDS; waves 0 .. MF-1 add them up and run the epilogue of one 16-row fragment each.  One trip to memory
 // for the operands and one for the outputs; nothing to zero, nothing to hand in.
+// What bounds it, where the weights do not come from memory, is the rate at which a compute unit pulls its operands: a wave load in operand order
+// touches sixteen rows of activations with neighbouring lanes, 15 B/clk per compute unit, and every block reads all rows.  They are loaded four lanes to
+// a row instead (46 B/clk) and cross the wave's lanes through LDS, and the K-steps in flight are a ring, each slot loaded again as soon as it is used up.
+// int8 out, r = 0 / 0.5 / 1, before and now: 16384 x 4096 weights, 16 rows 14.5 / 13.6 / 15.1 and 12.6 / 11.7 / 12.1 us, 8 rows 12.7 / 13.1 / 14.1 and 12.7 / 11.5 / 11.7;
+// 1024 x 4096, 16 rows 4.4 / 4.6 / 4.8 and 3.65 / 4.1 / 4.7, 32 rows 6.3 / 6.5 / 6.8 and 4.4 / 5.05 / 6.05.
 struct RowsParams {
     const int8_t *X;        // int8 [M][C], stored channel order
     const int8_t *W8;       // [U][2][Npad][16]
@@ -104,7 +109,7 @@ constexpr int kRowCols = 16;   // output columns per block
 template <int MF, bool COOP, bool FP6 = false, bool P4 = false>
 __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
 {
-    static_assert(!P4 || (MF == 1 && !FP6), "packed codes: up to 16 rows");
+    static_assert(!P4 || (MF == 1 && !FP6 && !COOP), "packed codes: up to 16 rows, lowered by every wave");
     static_assert(!COOP || MF == 1, "the cooperative pass is for calls of a few rows");
     static_assert(!(COOP && FP6), "FP6 calls bring lowered activations");
     extern __shared__ __align__(16) unsigned char lds[];   // [waves][MF][64 lanes] accumulator quads, then (COOP) the lowered rows
@@ -134,44 +139,6 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
 #pragma unroll
     for (int f = 0; f < MF; ++f) acc[f] = (v4i){0, 0, 0, 0};
 
-    constexpr int UN = MF <= 3 ? 4 : 3;   // K-steps in flight per wave (four with four fragments spill)
-    v4i w8[UN], x[UN][MF];
-    int sa[UN];
-    bool low[UN], valid[UN];
-    // weight fragments (and activation positions) of the K-steps ks0, ks0 + nw, ...: loads only.  4-bit units come from the
-    // position-expanded copy (code << w_shift as int8, 16 bytes per lane like an 8-bit unit): measured against the packed codes
-    // expanded in registers (8 bytes and a position byte per lane, 22 vector-ALU operations per 16 codes) it is faster at every
-    // size (ViT-L fc2, 16 rows, r = 1: 5.2 against 6.1 us; 16384 x 4096 weights, 8 rows: 16.1 against 18.7 us): what the packed
-    // codes save in bytes that expansion costs in instructions.  One and two rows, where bytes decide, go to k_few_rows_dot;
-    // the P4 builds have a cheaper expansion.
-    auto issue_w = [&](int ks0) {
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            const int ks = ks0 + k * nw;
-            const int u = 2 * ks + (qd >> 1), h = qd & 1;   // this lane's unit and k-half
-            valid[k] = ks < p.steps && u < p.units;
-            low[k] = valid[k] && u < p.units4;
-            w8[k] = (v4i){0, 0, 0, 0};
-            sa[k] = 0;
-            if (valid[k]) w8[k] = *reinterpret_cast<const v4i *>(p.W8 + (low[k] ? p.w4x_delta : 0) + (((int64_t)u * 2 + h) * p.Npad + n) * 16);
-            if (low[k] && !COOP && !p.x_pre) sa[k] = p.ashift[u >> p.gs_shift];
-        }
-    };
-    // activation fragments of the same K-steps: from memory, or (COOP, 4-bit units) lowered already from LDS
-    auto issue_x = [&](int ks0) {
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            const int u = 2 * (ks0 + k * nw) + (qd >> 1), h = qd & 1;
-#pragma unroll
-            for (int f = 0; f < MF; ++f) {
-                const int m = 16 * f + c;
-                if (COOP && low[k])
-                    x[k][f] = m < p.M ? *reinterpret_cast<const v4i *>(xl + m * xl_stride + u * 32 + 16 * h) : (v4i){0, 0, 0, 0};
-                else
-                    x[k][f] = valid[k] && m < p.M ? *reinterpret_cast<const v4i *>(p.X + (int64_t)m * p.C + u * 32 + 16 * h) : (v4i){0, 0, 0, 0};
-            }
-        }
-    };
     int ks0 = wave;
     if constexpr (FP6) {
         // chunks of two FP6 K-steps (128 channels), dealt to the waves in turn; the int8 K-steps after them continue the deal
@@ -222,26 +189,130 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
             acc[f] = (v4i){(int)accf[f].x, (int)accf[f].y, (int)accf[f].z, (int)accf[f].w};   // exact integers below 2^24
         ks0 = p.s6 + (wave + nw - chunks % nw) % nw;
     }
-    // packed K-steps wave, wave + nw, ... of the leading s4: loads of a batch of them
+    // ---- activations of a K-step: loaded four lanes to a row (neighbouring lanes on neighbouring pieces; rows beyond M read as zero), they cross
+    // the wave's lanes through its own part of LDS (no barrier: LDS serves a wave's accesses in order).  The pad unit of an odd unit count
+    // has zero weights.
+    unsigned char *const mine = lds + wave * MF * 1024;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)p.X, 0, p.M * p.C, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.W8, 0, 2 * p.w4x_delta, kRsrcFlags);
+    const int xr = lane >> 2, xp = lane & 3;   // row of a fragment and 16-byte piece of the K-step that this lane loads
+    const int xoff = xr * p.C + 16 * xp;
+    unsigned char *const put = mine + xr * 64 + 16 * (xp ^ (xr >> 2));
+    const unsigned char *const get = mine + c * 64 + 16 * (qd ^ (c >> 2));
+    const unsigned char *const own = xl + min(c, p.M - 1) * xl_stride + 16 * qd;   // (COOP: rows beyond M are computed from the last one and not stored)
+    const int woff = (qd * p.Npad + n) * 16;
+    auto load_x = [&](v4i &x, int f, int ks) { x = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rx, xoff + 16 * f * p.C + 64 * ks, 0, 0)); };
+    auto cross = [&](const v4i (&x)[MF], v4i (&b)[MF]) {
+#pragma unroll
+        for (int f = 0; f < MF; ++f) *reinterpret_cast<v4i *>(put + 1024 * f) = x[f];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int f = 0; f < MF; ++f) b[f] = *reinterpret_cast<const v4i *>(get + 1024 * f);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // weight fragments.  4-bit units come from the position-expanded copy (code << w_shift as int8, 16 bytes per lane like an 8-bit unit):
+    // measured against the packed codes expanded in registers (8 bytes and a position byte per lane, 22 vector-ALU operations per 16 codes)
+    // it is faster at every size (ViT-L fc2, 16 rows, r = 1: 5.2 against 6.1 us; 16384 x 4096 weights, 8 rows: 16.1 against 18.7 us): what the
+    // packed codes save in bytes that expansion costs in instructions.  One and two rows, where bytes decide, go to k_few_rows_dot;
+    // the P4 builds have a cheaper expansion.
+    constexpr int UN = MF <= 3 ? 4 : 3;   // K-steps in flight per wave, each slot loaded again as soon as it is used up
+    v4i w8[UN], x[UN][MF];
+    int sa0[UN], sa1[UN];
+    auto load8 = [&](int k, int ks) {
+        if (!COOP && !FP6 && !p.x_pre) {   // (scalar, and ahead of its use; the table has an entry for the pad unit)
+            sa0[k] = p.ashift[2 * ks >> p.gs_shift];
+            sa1[k] = p.ashift[(2 * ks + 1) >> p.gs_shift];
+        }
+        w8[k] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, woff + (2 * ks + (qd >> 1) < p.units4 ? p.w4x_delta : 0), ks * 64 * p.Npad, 0));
+        if (!COOP || 2 * ks + 1 >= p.units4) {   // (COOP: a K-step all of 4-bit units is in LDS, lowered)
+#pragma unroll
+            for (int f = 0; f < MF; ++f) load_x(x[k][f], f, ks);
+        }
+    };
+    auto use8 = [&](int k, int ks) {
+        if (!COOP && !FP6 && !p.x_pre && 2 * ks < p.units4) {
+            const bool low = 2 * ks + (xp >> 1) < p.units4;   // (false: a unit read at 8 bits)
+            const int sa = xp >> 1 ? sa1[k] : sa0[k];
+#pragma unroll
+            for (int f = 0; f < MF; ++f)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[k][f][i] = low ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
+        }
+        v4i b[MF];
+        if (COOP && 2 * ks + 1 < p.units4) {
+            b[0] = *reinterpret_cast<const v4i *>(own + 64 * ks);
+        } else {
+            cross(x[k], b);
+            if (COOP && 2 * ks < p.units4 && qd < 2) b[0] = *reinterpret_cast<const v4i *>(own + 64 * ks);
+        }
+#pragma unroll
+        for (int f = 0; f < MF; ++f) acc[f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k], b[f], acc[f], 0, 0, 0);
+    };
+    // packed K-steps wave, wave + nw, ... of the leading s4
     constexpr int U4 = 4;   // (eight in flight: more code to fetch, slower at every size)
     v2i w4[P4 ? U4 : 1];
     uint32_t ws4[P4 ? U4 : 1];
+    v4i x4[P4 ? U4 : 1][MF];
     int sa4[P4 ? U4 : 1];
-    auto issue_w4 = [&](int first) {
-#pragma unroll
-        for (int k = 0; k < U4; ++k) {
-            const int ks = first + k * nw;
-            if (ks >= p.s4) continue;
-            const int u = 2 * ks + (qd >> 1), h = qd & 1;
-            w4[k] = *reinterpret_cast<const v2i *>(p.W4 + ((int64_t)u * p.Npad + n) * 16 + 8 * h);
-            ws4[k] = *reinterpret_cast<const uint32_t *>(p.wshift + (int64_t)ks * p.Npad + n0 + 4 * qd);   // (the K-step is a group)
-            if (!COOP && !p.x_pre) sa4[k] = p.ashift[ks];
-        }
+    auto load4 = [&](int k, int ks) {
+        const int u = 2 * ks + (qd >> 1), h = qd & 1;
+        w4[k] = *reinterpret_cast<const v2i *>(p.W4 + ((int64_t)u * p.Npad + n) * 16 + 8 * h);
+        ws4[k] = *reinterpret_cast<const uint32_t *>(p.wshift + (int64_t)ks * p.Npad + n0 + 4 * qd);   // (the K-step is a group)
+        if (!p.x_pre) sa4[k] = p.ashift[ks];
+        load_x(x4[k][0], 0, ks);
     };
-    if constexpr (P4) issue_w4(wave);
-    else issue_w(ks0);   // (a wave beyond the last K-step loads nothing)
+    auto use4 = [&](int k, int ks) {
+        if (!p.x_pre) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x4[k][0][i] = (int)lower4((uint32_t)x4[k][0][i], sa4[k]);
+        }
+        v4i b[MF];
+        cross(x4[k], b);
+        const v4i a = {(w4[k].x << 4) & (int)0xf0f0f0f0, w4[k].x & (int)0xf0f0f0f0, (w4[k].y << 4) & (int)0xf0f0f0f0, w4[k].y & (int)0xf0f0f0f0};
+        const v4i t = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b[0], (v4i){0, 0, 0, 0}, 0, 0, 0);
+        const uint32_t down = 0x04040404u - ws4[k];   // (positions are 0 .. 4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[0][i] += t[i] >> ((down >> (8 * i)) & 31u);
+    };
+    // the wave's steps first, first + nw, ...: `left` of them, D in flight; `begun`: the first D are on their way
+    auto begin = [&](auto load, auto depth, int first, int left) {
+        constexpr int D = decltype(depth)::value;
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (k < left) load(k, first + k * nw);
+    };
+    auto run = [&](auto load, auto use, auto depth, int first, int left) {
+        constexpr int D = decltype(depth)::value;
+        int ks = first;
+        for (; left >= 2 * D; left -= D, ks += nw * D) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                use(k, ks + k * nw);
+                load(k, ks + (k + D) * nw);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 2 * D - 1; ++k)
+            if (k < left) {
+                use(k % D, ks + k * nw);
+                if (k + D < left) load(k % D, ks + (k + D) * nw);
+            }
+    };
+    using D8 = std::integral_constant<int, UN>;
+    using D4 = std::integral_constant<int, U4>;
+    auto count = [&](int first, int end) { return first < end ? (end - first + nw - 1) / nw : 0; };
+    int left4 = 0;
+    if constexpr (P4) {
+        left4 = count(wave, p.s4);
+        begin(load4, D4{}, wave, left4);
+        ks0 = p.s4 + (wave + nw - p.s4 % nw) % nw;   // (the deal goes on with the other K-steps)
+    }
+    const int left8 = count(ks0, p.steps);
+    if constexpr (!P4) begin(load8, D8{}, ks0, left8);   // (a wave beyond the last K-step loads nothing)
     if constexpr (COOP) {
-        // few rows: in the fragment layout most lanes hold no row, and lowering there would cost every wave the full
+        // few rows: in the fragment layout most lanes would hold no row, and lowering there would cost every wave the full
         // instruction count for a handful of values.  The block lowers the 4-bit channels of its rows once, every lane a
         // 16-byte piece, into LDS, while the first weight fragments are on their way.
         const int per_row = 2 * p.units4;   // pieces per row
@@ -255,49 +326,10 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
         __syncthreads();
     }
     if constexpr (P4) {
-        for (int first = wave; first < p.s4; first += nw * U4) {
-            if (first != wave) issue_w4(first);
-            v4i x4[U4];
-#pragma unroll
-            for (int k = 0; k < U4; ++k) {
-                const int ks = first + k * nw;
-                if (ks >= p.s4) continue;
-                if (COOP) x4[k] = c < p.M ? *reinterpret_cast<const v4i *>(xl + c * xl_stride + 64 * ks + 16 * qd) : (v4i){0, 0, 0, 0};
-                else x4[k] = c < p.M ? *reinterpret_cast<const v4i *>(p.X + (int64_t)c * p.C + 64 * ks + 16 * qd) : (v4i){0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int k = 0; k < U4; ++k) {
-                if (first + k * nw >= p.s4) continue;
-                v4i b = x4[k];
-                if (!COOP && !p.x_pre)
-                    b = (v4i){(int)lower4((uint32_t)b.x, sa4[k]), (int)lower4((uint32_t)b.y, sa4[k]), (int)lower4((uint32_t)b.z, sa4[k]), (int)lower4((uint32_t)b.w, sa4[k])};
-                const v4i a = {(w4[k].x << 4) & (int)0xf0f0f0f0, w4[k].x & (int)0xf0f0f0f0, (w4[k].y << 4) & (int)0xf0f0f0f0, w4[k].y & (int)0xf0f0f0f0};
-                const v4i t = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, (v4i){0, 0, 0, 0}, 0, 0, 0);
-                const uint32_t down = 0x04040404u - ws4[k];   // (positions are 0 .. 4)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[0][i] += t[i] >> ((down >> (8 * i)) & 31u);
-            }
-        }
-        ks0 = p.s4 + (wave + nw - p.s4 % nw) % nw;   // (the deal goes on with the other K-steps)
-        issue_w(ks0);
+        run(load4, use4, D4{}, wave, left4);
+        begin(load8, D8{}, ks0, left8);
     }
-    if (ks0 < p.steps) for (;;) {   // (a wave beyond the last K-step has nothing to multiply)
-        issue_x(ks0);
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-            if (low[k] && !COOP && !p.x_pre) {
-#pragma unroll
-                for (int f = 0; f < MF; ++f)
-                    x[k][f] = (v4i){(int)lower4((uint32_t)x[k][f].x, sa[k]), (int)lower4((uint32_t)x[k][f].y, sa[k]),
-                                    (int)lower4((uint32_t)x[k][f].z, sa[k]), (int)lower4((uint32_t)x[k][f].w, sa[k])};
-            }
-#pragma unroll
-            for (int f = 0; f < MF; ++f) acc[f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k], x[k][f], acc[f], 0, 0, 0);
-        }
-        ks0 += nw * UN;
-        if (ks0 >= p.steps) break;
-        issue_w(ks0);
-    }
+    run(load8, use8, D8{}, ks0, left8);
 
     // ---- the waves' sums meet in LDS
 #pragma unroll
@@ -870,22 +902,21 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     // one block's meeting in LDS and epilogue hide behind the others' loads (16384 x 4096 weights, 8 rows: 13.4 against 17.2 us)
     const int nw = (int)blocks >= 2 * num_cu ? 4 : (p.steps >= 12 ? 16 : (p.steps >= 6 ? 8 : 4));
     size_t lds = (size_t)nw * mf * 64 * 16;
-    // few rows whose 4-bit channels the kernel lowers: once per block, through LDS
-    const size_t rows_bytes = (size_t)M * (32 * (size_t)p.units4 + 16);
-    const bool coop = M <= 8 && !p.x_pre && p.units4 > 0 && lds + rows_bytes <= 64 * 1024;
-    if (coop) lds += rows_bytes;
-    // Packed codes where the weight bytes decide (us with the expanded copies and with the codes, weights from HBM, r = 0.25 / 0.5 / 1).
-    // Up to eight rows, which the block lowers once, from 40 MiB of 8-bit weights on: 16384 x 4096, 5 rows 17.0 / 16.9 / 17.0 and 15.9 / 14.5 /
-    // 14.2; 8192 x 5120 (40 MiB), 8 rows 12.4 / 12.4 / 13.4 and 12.5 / 12.5 / 12.1, kept in cache 6 to 25 % faster.  (At 32 MiB, 8192 x 4096, the codes are
-    // ahead from HBM, 9.9 / 10.2 against 10.4 / 11.4 with 8 rows at r = 0.5 / 1, but not for every shape kept in cache; at 16 MiB, 4096 x 4096, r >= 0.5, they gain
-    // 3 to 6 % from HBM and lose 17 to 30 % in cache.)  More rows are lowered in every wave, which takes more than 40 MiB and half of the channels at 4 bits to pay
-    // for: 16384 x 4096, 16 rows 18.5 / 18.5 / 19.2 and 18.0 / 16.9 / 16.4; 11008 x 4096 (43 MiB), 12 rows 13.0 / 13.0 / 13.6 and 13.2 / 12.6 / 12.5; 8192 x
-    // 5120, 12 rows 11.9 / 11.9 / 12.2 and 12.4 / 12.6 / 12.3.
+    // Packed codes where the weight bytes decide: up to eight rows from 40 MiB of 8-bit weights on, more from above 41 MiB and half of the channels
+    // at 4 bits on.  Weights from HBM, the expanded copies and the codes, r = 0.5 / 1, when the lines were drawn (operands loaded in another order, about
+    // 1 to 2 us slower on both sides): 8192 x 5120 (40 MiB), 8 rows 12.4 / 13.4 and 12.5 / 12.1, kept in cache 6 to 25 % faster; 8192 x 4096 (32 MiB),
+    // ahead from HBM but not for every shape kept in cache; 4096 x 4096 17 to 30 % slower in cache; 11008 x 4096 (43 MiB), 12 rows 13.0 / 13.6 and 12.6 / 12.5;
+    // 8192 x 5120, 12 rows 11.9 / 12.2 and 12.6 / 12.3.
     p.s4 = p.units4 / 2;
     const bool p4 = mf == 1 && L->group_size == 64 && p.s4 > 0 && (g_force_rows == 3 || (g_force_rows < 0 && (M <= 8 ? (int64_t)L->N * L->C >= (40 << 20)
                                                                                                                      : (int64_t)L->N * L->C > (41 << 20) && 2 * L->max_4bit_ch >= L->C)));
+    // few rows whose 4-bit channels the kernel lowers: once per block, through LDS (4096 x 4096, 4 rows, r = 0.5 / 1: 3.85 / 4.0 us, by every wave 4.25 / 4.8; the
+    // packed codes leave every wave the time: 16384 x 4096, 8 rows 12.65 / 13.2 with a block's pass and 11.45 / 11.65 without)
+    const size_t rows_bytes = (size_t)M * (32 * (size_t)p.units4 + 16);
+    const bool coop = !p4 && M <= 8 && !p.x_pre && p.units4 > 0 && lds + rows_bytes <= 64 * 1024;
+    if (coop) lds += rows_bytes;
     void (*fn)(const RowsParams) =
-        mf == 1 ? (p4 ? (coop ? k_few_rows<1, true, false, true> : k_few_rows<1, false, false, true>) : (coop ? k_few_rows<1, true> : k_few_rows<1, false>))
+        mf == 1 ? (p4 ? k_few_rows<1, false, false, true> : (coop ? k_few_rows<1, true> : k_few_rows<1, false>))
                 : (mf == 2 ? k_few_rows<2, false> : (mf == 3 ? k_few_rows<3, false> : k_few_rows<4, false>));
     FLEXIQ_HIP(launch_kernel(fn, dim3(blocks), dim3(64 * nw), lds, stream, p));
     *taken = 1;

@@ -182,6 +182,28 @@ def test_tile_splitk_kernel(env, M, K, N, gs, shape):
         fq.debug_force_tile_splitk(-1)
 
 
+# a wave with no, fewer, as many, between once and twice and more K-steps than it has in flight; a last K-step of one unit; one, some and all rows of a fragment
+@pytest.mark.parametrize("units", [1, 2 * 13 - 1, 2 * 16, 2 * 61, 2 * 66, 2 * 129 - 1])
+@pytest.mark.parametrize("M", [3, 8, 9, 16, 17, 47, 64])
+def test_few_rows_reductions(env, units, M):
+    torch, oracle, fq, dev = env
+    K, N = 32 * units, 40
+    case = workloads.make_linear("fewred", 8, 1300 + units + M, M, K, N, 32, outlier_frac=0.02)
+    case.X *= 2.0
+    ol, hl, x_scale = both_layers(case)
+    Xq = np.ascontiguousarray(oracle.quantize(case.X, x_scale)[:, ol.perm])
+    Xd = torch.from_numpy(Xq).to(dev)
+    fq.debug_force_few_rows(1)
+    try:
+        for r in (0.0, 32.0 / K, 0.5, 1.0):   # (32 channels: a K-step of both kinds)
+            fq.flexiq_set_ratio(hl, r)
+            got = fq.flexiq_mixed_gemm(hl, Xd, acc=True)["acc"]
+            assert fq.debug_last_launch()["tile"] == -4
+            assert (got.cpu().numpy() == oracle.forward_gemm(ol, Xq, r)).all(), r
+    finally:
+        fq.debug_force_few_rows(-1)
+
+
 # fewer K-steps of a wave than it has in flight, between once and twice as many, more; a last K-step of one unit; rows that end in a tile
 @pytest.mark.parametrize("units,gs", [(2 * 15, 32), (2 * 17 - 1, 32), (2 * 33, 32), (2 * 50 - 1, 32), (2 * 65, 32), (2 * 129, 64)])
 @pytest.mark.parametrize("shape", [2, 3, 4])
