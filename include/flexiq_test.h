@@ -87,6 +87,10 @@ int flexiq_debug_force_wreg(int mode);
  * -1 = automatic (where it is ahead of the tiled kernel).  Returns 1 if the last call it was offered ran on it, or 0. */
 int flexiq_debug_force_wreg6(int mode);
 
+/* Kernel with activations in LDS chunk by chunk (linear calls; last launch: tile shape index -7): k >= 1 = with the k-th block shape of its
+ * table whenever the call qualifies, 0 = never, -1 = automatic.  Returns the block shape of the last call it was offered (0: another kernel). */
+int flexiq_debug_force_chunk(int mode);
+
 /* Force tile shape `index` of the FP6-variant kernel's table (-1 = automatic).  Returns the table size. */
 int flexiq_debug_force_fp6_tile(int index);
 

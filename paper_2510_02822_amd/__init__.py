@@ -11,7 +11,7 @@ from .binding import (FlexiqError, Layer, flexiq_bitlower, flexiq_dynamic_positi
                       flexiq_mixed_gemm_fp6, debug_force_fp6_tile,
                       flexiq_packed4_channels, flexiq_packed4_bytes, flexiq_lower_packed4, flexiq_mixed_gemm_packed4,
                       debug_force_stream, debug_force_conv3, debug_force_few_rows, debug_force_tile_splitk, debug_force_halo,
-                      debug_force_wreg, debug_force_wreg6)
+                      debug_force_wreg, debug_force_wreg6, debug_force_chunk)
 
 __all__ = ["FlexiqError", "Layer", "flexiq_bitlower", "flexiq_dynamic_positions", "flexiq_dynamic_positions_static", "flexiq_static_positions",
            "flexiq_layer_positions", "flexiq_input_prelowered", "flexiq_layer_dump", "flexiq_mixed_conv_implicit",
@@ -20,4 +20,4 @@ __all__ = ["FlexiqError", "Layer", "flexiq_bitlower", "flexiq_dynamic_positions"
            "flexiq_mixed_gemm_fp6", "debug_force_fp6_tile",
            "flexiq_packed4_channels", "flexiq_packed4_bytes", "flexiq_lower_packed4", "flexiq_mixed_gemm_packed4",
            "debug_force_stream", "debug_force_conv3", "debug_force_few_rows", "debug_force_tile_splitk", "debug_force_halo", "debug_force_wreg",
-           "debug_force_wreg6"]
+           "debug_force_wreg6", "debug_force_chunk"]

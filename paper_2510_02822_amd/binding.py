@@ -93,6 +93,7 @@ def load():
     L.flexiq_debug_force_halo.argtypes = [C.c_int]
     L.flexiq_debug_force_wreg.argtypes = [C.c_int]
     L.flexiq_debug_force_wreg6.argtypes = [C.c_int]
+    L.flexiq_debug_force_chunk.argtypes = [C.c_int]
     L.flexiq_debug_force_tile.argtypes = [C.c_int]
     L.flexiq_debug_force_packed4.argtypes = [C.c_int]
     L.flexiq_debug_max_blocks.argtypes = [C.c_int]
@@ -471,6 +472,15 @@ def debug_force_wreg(mode: int) -> int:
     """Kernel with the weights resident in registers: 1 = whenever the call reaches it and qualifies, 0 = never, -1 = automatic.
     Returns whether the last call it was offered ran on it."""
     rc = load().flexiq_debug_force_wreg(int(mode))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def debug_force_chunk(mode: int) -> int:
+    """Kernel with activations in LDS chunk by chunk: k >= 1 = with the k-th block shape of its table whenever the call qualifies,
+    0 = never, -1 = automatic.  Returns the block shape of the last call it was offered (0: another kernel)."""
+    rc = load().flexiq_debug_force_chunk(int(mode))
     if rc < 0:
         _check(rc)
     return rc

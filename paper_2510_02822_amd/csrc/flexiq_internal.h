@@ -46,6 +46,7 @@ int prepare_stream_kernels(int device);
 int prepare_conv3_kernels(int device);
 int prepare_halo_kernels(int device);
 int prepare_wreg_kernels(int device);
+int prepare_chunk_kernels(int device);
 int prepare_wreg6_kernels(int device);
 int prepare_tile_splitk_kernels(int device);
 
@@ -145,6 +146,14 @@ int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fl
 // (wreg.hip) linear calls of 288 to 1280 channels: the weights of a block resident in registers, row tiles streamed
 // past them; *taken = 0: the call does not qualify
 int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
+// (chunk.hip) linear calls of a long reduction: activations in LDS chunk by chunk, weights straight into registers; *taken = 0: the call
+// does not qualify or another kernel is ahead.  us: its modelled time; one_round: every block is resident from the start
+struct ChunkChoice {
+    int shape = -1;
+    double us = 0;
+    bool one_round = false;
+};
+int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
 // (wreg6.hip) the same for flexiq_mixed_gemm_fp6: 256 to 1280 channels, all of them (K6) on the FP6 matrix path; tiled_rows: how many rows
 // one after the other a compute unit would work through in the tiled kernel
 int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int64_t tiled_rows, int *taken,

@@ -614,6 +614,7 @@ extern "C" int flexiq_quantize_pack(const flexiq_pack_desc *d, flexiq_layer **ou
         if (rc == FLEXIQ_OK) rc = prepare_conv3_kernels(L->device);
         if (rc == FLEXIQ_OK) rc = prepare_halo_kernels(L->device);
         if (rc == FLEXIQ_OK) rc = prepare_wreg_kernels(L->device);
+        if (rc == FLEXIQ_OK) rc = prepare_chunk_kernels(L->device);
         if (rc == FLEXIQ_OK) rc = prepare_wreg6_kernels(L->device);
         if (rc == FLEXIQ_OK) rc = prepare_tile_splitk_kernels(L->device);
         if (rc != FLEXIQ_OK) return rc;
