@@ -44,6 +44,17 @@ __device__ __forceinline__ uint32_t lower4(uint32_t d, int s)
     return r & (0x01010101u * ((0xFFu << s) & 0xFFu));
 }
 
+// Eight packed activation codes (a dword: channels 0 .. 3 in the low halves of its bytes, 4 .. 7 in the high halves) put back at position s as int8
+// values, code << s: hi = the dword with the wanted halves on top.
+__device__ __forceinline__ uint32_t expand4(uint32_t hi, int s)
+{
+    v2s o = __builtin_bit_cast(v2s, hi);
+    v2s e = o << (short)8;
+    o = o >> (short)(4 - s);   // (sign-extends; what comes from the other half of the byte is cleared below)
+    e = e >> (short)(4 - s);
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, o), __builtin_bit_cast(uint32_t, e), 0x07030501u) & (0x01010101u * ((0xFFu << s) & 0xFFu));
+}
+
 // ---- A block owns 16 output columns and the whole reduction.
 //
 // Splitting the reduction across blocks makes the slices meet in memory (store, ticket, re-read: three dependent trips;
@@ -90,8 +101,10 @@ struct RowsParams {
     int32_t next_K4, next_gs_log2;
     uint8_t *nx6;           // optional (k_tile_splitk, FP6 calls): the consumer's FP6 activation buffer; its leading next_K6 channels
     int32_t next_K6, next_S;   //   leave as FP6 codes as well (next_S = its C / 64)
-    const uint8_t *X4;      // optional (k_few_rows_dot): packed activation codes [M][C / 2] of the leading pieces_p pieces of a row
+    const uint8_t *X4;      // optional (k_few_rows_dot, k_tile_splitk): packed activation codes [M][C / 2] of the leading pieces_p pieces of a row
     int32_t pieces_p;       // 16-channel pieces whose codes come from X4 (a multiple of 4: whole K-steps)
+    uint8_t *nx4;           // optional (k_tile_splitk): the consumer's packed activation buffer [M][N / 2]; its leading next_K4P channels
+    int32_t next_K4P;       //   leave as codes there instead of in q (a multiple of 64)
 };
 
 constexpr int kRowCols = 16;   // output columns per block
@@ -576,7 +589,8 @@ __global__ __launch_bounds__(512) void k_few_rows_dot(const RowsParams p)
 // FP6: the leading s6 K-steps run first on `v_mfma_scale_f32_16x16x128_f8f6f4`, as in the FP6 build of k_few_rows (chunks of
 // two K-steps dealt to the waves in turn; a lane holds the 32 codes of one unit and its block scale), every other K-step as
 // usual with activations that arrive lowered.
-template <int FR, int FC, int NW, int UN, bool FP6 = false>
+// XP: the leading K-steps of activations are read from packed codes.
+template <int FR, int FC, int NW, int UN, bool FP6 = false, bool XP = false>
 __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
 {
     constexpr int kTileRows = 16 * FR, kTileCols = 16 * FC, kTileWaves = NW, NF = FR * FC;
@@ -702,18 +716,9 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
 #pragma unroll
             for (int g = 0; g < FC; ++g) w8[k][g] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, wo + 256 * g, ks * 64 * p.Npad, 0));
         };
-        auto use = [&](int k, int ks) {
-            const int u = 2 * ks + (xp >> 1);
-            if (!FP6 && !p.x_pre && 2 * ks < p.units4) {   // (lowered before it crosses the lanes: fewer registers live)
-                const bool mine4 = u < p.units4;   // (false: a unit read at 8 bits)
-                const int sa = xp >> 1 ? sa1[k] : sa0[k];
+        auto multiply = [&](int k, const v4i (&v)[FR]) {
 #pragma unroll
-                for (int f = 0; f < FR; ++f)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) x[k][f][i] = mine4 ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
-            }
-#pragma unroll
-            for (int f = 0; f < FR; ++f) *reinterpret_cast<v4i *>(put + 1024 * f) = x[k][f];
+            for (int f = 0; f < FR; ++f) *reinterpret_cast<v4i *>(put + 1024 * f) = v[f];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             v4i b[FR];
@@ -726,23 +731,64 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
 #pragma unroll
                 for (int g = 0; g < FC; ++g) acc[f][g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k][g], b[f], acc[f][g], 0, 0, 0);
         };
-        int left = (p.steps - first + NW - 1) / NW, ks = first;
+        auto use = [&](int k, int ks) {
+            const int u = 2 * ks + (xp >> 1);
+            if (!FP6 && !p.x_pre && 2 * ks < p.units4) {   // (lowered before it crosses the lanes: fewer registers live)
+                const bool mine4 = u < p.units4;   // (false: a unit read at 8 bits)
+                const int sa = xp >> 1 ? sa1[k] : sa0[k];
 #pragma unroll
-        for (int k = 0; k < UN; ++k)
-            if (k < left) load(k, ks + k * NW);
-        for (; left >= 2 * UN; left -= UN, ks += NW * UN) {
+                for (int f = 0; f < FR; ++f)
 #pragma unroll
-            for (int k = 0; k < UN; ++k) {
-                use(k, ks + k * NW);
-                load(k, ks + (k + UN) * NW);
+                    for (int i = 0; i < 4; ++i) x[k][f][i] = mine4 ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
             }
+            multiply(k, x[k]);
+        };
+        auto run = [&](auto load, auto use, int ks, int left) {
+#pragma unroll
+            for (int k = 0; k < UN; ++k)
+                if (k < left) load(k, ks + k * NW);
+            for (; left >= 2 * UN; left -= UN, ks += NW * UN) {
+#pragma unroll
+                for (int k = 0; k < UN; ++k) {
+                    use(k, ks + k * NW);
+                    load(k, ks + (k + UN) * NW);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2 * UN - 1; ++k)
+                if (k < left) {
+                    use(k % UN, ks + k * NW);
+                    if (k + UN < left) load(k % UN, ks + (k + UN) * NW);
+                }
+        };
+        auto count = [&](int first, int end) { return first < end ? (end - first + NW - 1) / NW : 0; };
+        if constexpr (XP) {
+            // the K-steps of packed codes first, 8 bytes per lane and fragment
+            const int s4 = p.pieces_p >> 2;
+            const __amdgpu_buffer_rsrc_t rx4 = __builtin_amdgcn_make_buffer_rsrc((void *)(p.X4 + (int64_t)m0 * (p.C >> 1)), 0, rows * (p.C >> 1), kRsrcFlags);
+            v2i x4[UN][FR];
+            auto load4 = [&](int k, int ks) {
+                sa0[k] = p.ashift[2 * ks >> p.gs_shift];
+                sa1[k] = p.ashift[(2 * ks + 1) >> p.gs_shift];
+#pragma unroll
+                for (int f = 0; f < FR; ++f) x4[k][f] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(rx4, (xoff >> 1) + 8 * f * p.C + 32 * ks, 0, 0));
+#pragma unroll
+                for (int g = 0; g < FC; ++g) w8[k][g] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, woff + p.w4x_delta + 256 * g, ks * 64 * p.Npad, 0));
+            };
+            auto use4 = [&](int k, int) {
+                const int sa = xp >> 1 ? sa1[k] : sa0[k];
+                v4i e[FR];
+#pragma unroll
+                for (int f = 0; f < FR; ++f) {
+                    const uint32_t lo = (uint32_t)x4[k][f].x, hi = (uint32_t)x4[k][f].y;
+                    e[f] = (v4i){(int)expand4(lo << 4, sa), (int)expand4(lo, sa), (int)expand4(hi << 4, sa), (int)expand4(hi, sa)};
+                }
+                multiply(k, e);
+            };
+            run(load4, use4, wave, count(wave, s4));
+            first = s4 + (wave + NW - s4 % NW) % NW;   // (the deal goes on with the other K-steps)
         }
-#pragma unroll
-        for (int k = 0; k < 2 * UN - 1; ++k)
-            if (k < left) {
-                use(k % UN, ks + k * NW);
-                if (k + UN < left) load(k % UN, ks + (k + UN) * NW);
-            }
+        run(load, use, first, count(first, p.steps));
     }
 
     // ---- the waves' sums meet in LDS; wave w adds up and finishes fragments w, w + NW, ...
@@ -798,10 +844,16 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
         }
         qw ^= 0x80808080u;
         if (lower) qw &= 0x01010101u * ((0xFFu << sn) & 0xFFu);
+        const bool to4 = !FP6 && p.nx4 != nullptr && nn0 < p.next_K4P;
+        if (to4) {
+            // channels 8 e .. 8 e + 3 of the consumer lie in the low halves of a dword's bytes, 8 e + 4 .. 8 e + 7, the neighbouring lane's, in the high ones
+            const uint32_t codes = (qw >> sn) & 0x0F0F0F0Fu, next = (uint32_t)__shfl_xor((int)codes, 1);
+            if (!(eq & 1)) *reinterpret_cast<uint32_t *>(p.nx4 + (int64_t)m * (p.N >> 1) + (nn0 >> 1)) = codes | (next << 4);
+        }
         if ((p.N & 3) == 0) {
             if (p.acc) *reinterpret_cast<v4i *>(p.acc + o) = s;
             if (p.y) *reinterpret_cast<float4 *>(p.y + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
-            if (p.q) *reinterpret_cast<uint32_t *>(p.q + o) = qw;
+            if (p.q && !to4) *reinterpret_cast<uint32_t *>(p.q + o) = qw;
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -975,29 +1027,37 @@ int prepare_tile_splitk_kernels(int device)
     FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<4, 4, 8, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
     FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<2, 4, 8, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<2, 2, 16, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
+    FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<4, 4, 8, 2, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+    FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<2, 4, 16, 2, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+    FLEXIQ_HIP(hipFuncSetAttribute((const void *)k_tile_splitk<2, 2, 16, 4, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     g_tile_splitk_ready[device] = true;
     return FLEXIQ_OK;
 }
 
-static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t *X6, int K6, int64_t M, const flexiq_out *out, void *stream,
-                           int num_cu, int *taken, const LowerArgs *lower)
+static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t *X6, int K6, const uint8_t *X4, int64_t M, const flexiq_out *out,
+                           void *stream, int num_cu, int *taken, const LowerArgs *lower)
 {
     using namespace smallm;
     *taken = 0;
     g_last_tile_splitk = 0;
     // FP6 calls that lower for a consumer have no few-row kernel to go to: this one takes them at any row count
-    const bool only_here = X6 && out->lower_for;
+    const bool only_here = (X6 && out->lower_for) || (out->x4 && !X4);
+    // Calls that read or write packed codes have the tiled kernel alone else, whose few blocks each walk the reduction with a barrier per K-step: they
+    // come here from 17 rows on, producers at any row count, and with shorter reductions.  us there and here, r = 0.5 / 1, reading: 100 x 384 -> 1536 5.8 / 6.2
+    // and 4.0 / 4.0; 20 x 832 -> 576 8.45 / 7.7 and 4.1 / 4.1; 200 x 3072 -> 768 14.9 / 16.8 and 5.5 / 5.8; 200 x 2880 -> 2784 15.7 / 16.2 and 8.6 / 8.9; writing: 6 x 768 ->
+    // 3072 7.1 / 7.8 and 4.0 / 4.15, 1000 x 1024 -> 1024 8.4 / 9.1 and 6.4 / 7.0.  Beyond one tile per compute unit it is behind: 1000 x 768 -> 3072 10.2 there, 11.7 here.
+    const bool packed = X4 || out->x4;
     if (g_force_tile_splitk == 0 || M < 1 || (M <= 16 && !only_here) || M > 0x7fffffff / 2) return FLEXIQ_OK;
     // (calls of at most 64 rows: the few-row hook, in any forced state, keeps this kernel out of its comparisons)
-    if (M <= 64 && (g_force_rows >= 0 || (g_force_tile_splitk < 0 && M <= kTileMinRows && !only_here))) return FLEXIQ_OK;
-    if (out->scan_for || out->x4 || (out->lower_for && !lower)) return FLEXIQ_OK;
+    if (M <= 64 && (g_force_rows >= 0 || (g_force_tile_splitk < 0 && M <= kTileMinRows && !only_here && !packed))) return FLEXIQ_OK;
+    if (out->scan_for || (out->lower_for && !lower) || (out->x4 && !(lower && lower->x4 == out->x4 && (L->N & 31) == 0))) return FLEXIQ_OK;
     if (out->x6 && !(X6 && lower && lower->x6 == out->x6 && (L->N & 63) == 0 && (lower->K6 & 63) == 0)) return FLEXIQ_OK;   // FP6 output: FP6 calls only
     if ((reinterpret_cast<uintptr_t>(X) & 15u) || (L->C & 15) || L->device < 0 || L->device >= 64) return FLEXIQ_OK;
     const int steps = (L->C / kUnit + 1) / 2;
     auto tiles_of = [&](int tr, int tc) { return ((M + tr - 1) / tr) * (int64_t)((L->N + tc - 1) / tc); };
     // Where it measures faster than the tiled kernel: at most about one 64 x 64 tile per compute unit and a reduction of at
     // least 12 K-steps for the waves to split.  The tile shrinks while the blocks would leave half the compute units idle.
-    if (g_force_tile_splitk < 0 && (tiles_of(64, 64) > (int64_t)num_cu || steps < 12)) return FLEXIQ_OK;
+    if (g_force_tile_splitk < 0 && (tiles_of(64, 64) > (int64_t)num_cu || steps < (packed ? 6 : 12))) return FLEXIQ_OK;
     int shape = g_force_tile_splitk >= 2 ? g_force_tile_splitk - 2 : tiles_of(64, 64) * 2 > num_cu ? 0 : tiles_of(32, 64) * 2 > num_cu ? 1 : 2;
     if (shape > 2) return FLEXIQ_EINVAL;
     const int tr = shape == 0 ? 64 : 32, tc = shape == 2 ? 32 : 64;
@@ -1019,6 +1079,7 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
     p.w4x_delta = L->U * 32 * L->Npad;
     if (lower && lower->ashift) {
         p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2;
+        if (out->x4) { p.nx4 = lower->x4; p.next_K4P = lower->K4P; }
         if (X6 && lower->x6) { p.nx6 = lower->x6; p.next_K6 = lower->K6; p.next_S = lower->S; }
     }
     const dim3 grid((unsigned)((L->N + tc - 1) / tc), (unsigned)((M + tr - 1) / tr));
@@ -1029,6 +1090,12 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
         if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2, true>, grid, dim3(512), lds, stream, p);
         else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 8, 4, true>, grid, dim3(512), lds / 2, stream, p);   // (eight waves: registers)
         else err = launch_kernel(k_tile_splitk<2, 2, 16, 4, true>, grid, dim3(1024), lds, stream, p);
+    } else if (X4) {
+        p.X4 = X4;
+        p.pieces_p = (L->max_4bit_ch / 64) * 4;
+        if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2, false, true>, grid, dim3(512), lds, stream, p);
+        else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 16, 2, false, true>, grid, dim3(1024), lds, stream, p);
+        else err = launch_kernel(k_tile_splitk<2, 2, 16, 4, false, true>, grid, dim3(1024), lds, stream, p);
     } else if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2>, grid, dim3(512), lds, stream, p);
     else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 16, 2>, grid, dim3(1024), lds, stream, p);
     else err = launch_kernel(k_tile_splitk<2, 2, 16, 4>, grid, dim3(1024), lds, stream, p);
@@ -1042,9 +1109,9 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
 // Launches k_tile_splitk for a linear call of more than 32 rows whose output tiles leave most compute units idle on a long
 // reduction; *taken = 0: the call was left to the other kernels, else 1 / 2 / 3: tiles of 64 x 64 / 32 x 64 / 32 x 32.
 int launch_tile_splitk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int num_cu, int *taken,
-                       const LowerArgs *lower)
+                       const LowerArgs *lower, const uint8_t *X4)
 {
-    return launch_tile_any(L, X, nullptr, 0, M, out, stream, num_cu, taken, lower);
+    return launch_tile_any(L, X, nullptr, 0, X4, M, out, stream, num_cu, taken, lower);
 }
 
 // The same for the FP6 variant of the 4-bit phase: X holds the lowered activations, X6 the FP6 codes of the leading K6 channels.
@@ -1053,7 +1120,7 @@ int launch_tile_splitk_fp6(const flexiq_layer *L, const int8_t *X, const uint8_t
 {
     *taken = 0;
     if (!X6 || K6 < 0 || (K6 & 63)) return FLEXIQ_OK;
-    return launch_tile_any(L, X, X6, K6, M, out, stream, num_cu, taken, lower);
+    return launch_tile_any(L, X, X6, K6, nullptr, M, out, stream, num_cu, taken, lower);
 }
 
 }  // namespace flexiq

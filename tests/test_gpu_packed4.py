@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import workloads
-from helpers import both_layers, calib, check_q, requant_fp32_sequence
+from helpers import both_layers, calib, check_q, check_y, requant_fp32_sequence
 
 pytestmark = pytest.mark.gpu
 
@@ -244,3 +244,68 @@ def test_few_row_dot_kernel_reads_packed_codes(env, K, N, gs):
         assert (out["acc"].cpu().numpy() == np.repeat(oracle.forward_gemm(ol, Xq, 1.0), 3, axis=0)).all()
     finally:
         fq.debug_force_few_rows(-1)
+
+
+@pytest.mark.parametrize("M,K,N,gs", [(17, 768, 96, 32), (33, 1056, 300, 32), (130, 1472, 257, 64), (200, 384, 64, 64)])
+def test_tile_per_block_kernel_reads_packed_codes(env, M, K, N, gs):
+    """Every tile of the kernel whose waves split the reduction: K-steps of packed codes before none, some and all of the others, a trailing 4-bit group
+    of 32 lowered from X, an odd number of units, rows and columns that do not fill the last tile."""
+    torch, oracle, fq, dev = env
+    case = workloads.make_linear("p4tile", 11, M + K + N, M, K, N, gs, outlier_frac=0.02)
+    case.X *= 2.0   # some values saturate under the calibrated positions
+    ol, hl, x_scale = both_layers(case)
+    Xq = oracle.quantize(case.X, x_scale)[:, ol.perm]
+    try:
+        for r in sorted({1.0, 0.5, 3 * gs / K, 0.0}):
+            fq.flexiq_set_ratio(hl, r)
+            k4p = fq.flexiq_packed4_channels(hl)
+            ref = oracle.forward_gemm(ol, Xq, r)
+            so = float(np.abs(oracle.dequant_f64(ref, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9) or 1.0
+            x4 = fq.flexiq_lower_packed4(hl, _dev(torch, Xq, dev))
+            Xp = Xq.copy()
+            Xp[:, :k4p] = 77   # the packed columns of X are not read
+            for shape in (1, 2, 3, 4):   # the automatic tile and the three
+                fq.debug_force_tile_splitk(shape)
+                out = fq.flexiq_mixed_gemm_packed4(hl, _dev(torch, Xp, dev), x4, acc=True, y=True, q=True, out_scale=so)
+                assert fq.debug_last_launch()["tile"] == -5
+                assert (out["acc"].cpu().numpy() == ref).all(), (r, shape)
+                check_y(out["y"].cpu().numpy(), ref, ol)
+                assert (out["q"].cpu().numpy() == requant_fp32_sequence(ref, ol, so)).all(), (r, shape)
+    finally:
+        fq.debug_force_tile_splitk(-1)
+
+
+@pytest.mark.parametrize("M", [1, 9, 50, 150, 300])
+@pytest.mark.parametrize("pre", [False, True])
+def test_tile_per_block_kernel_packs_for_a_consumer(env, M, pre):
+    """Codes, the int8 columns beside them and what is left alone equal the tiled kernel's, by the automatic route and for every tile; a consumer whose
+    activations arrive lowered takes no codes."""
+    torch, oracle, fq, dev = env
+    K, N = 800, 416
+    first = workloads.make_linear("p4out1", 11, M, M, K, N, 32)
+    second = workloads.make_linear("p4out2", 11, M + 1, 64, N, 64, 32)
+    x_scale = oracle.absmax_scale(first.Xcal)
+    o2, h2, _ = both_layers(second)
+    hl = fq.flexiq_quantize_pack(first.W, np.abs(first.Xcal).max(0), x_scale, 32, bias=first.bias, out_perm=o2.perm)
+    X = _dev(torch, oracle.quantize(first.X, x_scale)[:, hl.info()["perm"]], dev)
+    fq.flexiq_input_prelowered(h2, pre)
+    def call():
+        x4 = torch.full((M, N // 2), 0x5A, dtype=torch.uint8, device=dev)
+        q = torch.full((M, N), 99, dtype=torch.int8, device=dev)
+        out = fq.flexiq_mixed_gemm(hl, X, q=True, y=True, out_scale=0.5, bufs={"q": q}, lower_for=h2, x4_out=x4)
+        return x4, q, out["y"]
+    try:
+        for r1, r2 in ((0.0, 1.0), (0.5, 0.5), (1.0, 0.0)):
+            fq.flexiq_set_ratio(hl, r1)
+            fq.flexiq_set_ratio(h2, r2)
+            fq.debug_force_tile_splitk(0)
+            want = call()
+            assert 0 <= fq.debug_last_launch()["tile"] < fq.debug_force_tile(-1)
+            for shape in (-1, 2, 3, 4):
+                fq.debug_force_tile_splitk(shape)
+                got = call()
+                assert fq.debug_last_launch()["tile"] == -5, (r1, r2, shape)
+                for g, w in zip(got, want):
+                    assert torch.equal(g, w), (r1, r2, shape)
+    finally:
+        fq.debug_force_tile_splitk(-1)
