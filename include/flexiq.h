@@ -170,11 +170,12 @@ int flexiq_permute_channels(const flexiq_layer *layer, const int8_t *src, int8_t
  *               stored channel order (compared by hash).  NULL: plain int8 codes
  *   scan_for  : optional, not together with lower_for.  The layer that will consume q (same conditions).  The
  *               run-time scan of flexiq_dynamic_positions (Section 4.1; Section 9 "Finding extraction positions at
- *               runtime") is done on q in the same pass: every block ORs the magnitude bits of the codes it writes
- *               per channel group of the consumer, and the block that finishes last leaves the consumer's run-time
- *               positions for its 4-bit groups (its ratio when this call is made) and switches it to them, exactly
- *               as flexiq_dynamic_positions(consumer, q, M) would, without a second kernel.  Uses the consumer's scan
- *               scratch, which the kernel leaves clean (safe to replay from a captured graph): calls that scan for
+ *               runtime") is done on q in the same call, by the producing kernel (every block ORs the magnitude bits of the codes it
+ *               writes per channel group of the consumer, the block that finishes last leaves the positions) or, where the
+ *               product is small, by a kernel behind it: the consumer's run-time positions for its 4-bit groups (its ratio
+ *               when this call is made) are left in place and it is switched to them, exactly as
+ *               flexiq_dynamic_positions(consumer, q, M) would.  Uses the consumer's scan
+ *               scratch, which the call leaves clean (safe to replay from a captured graph): calls that scan for
  *               the same consumer must not overlap, nor overlap its flexiq_dynamic_positions.  A call with M == 0
  *               launches nothing and leaves the positions as they were.  NULL: no scan
  *   x6        : optional, only with lower_for and only for flexiq_mixed_gemm_fp6 (FLEXIQ_EINVAL elsewhere): the

@@ -96,8 +96,7 @@ def test_lowered_for_a_consumer_prelowered_and_positions_found_at_run_time(env, 
     fq.debug_force_chunk(-1)
 
 
-# Calls of more than 1280 channels whose blocks are one round go to this kernel, in every form it accepts; of 1280 and fewer, none; what it does
-# not write (a scan for the consumer, packed codes) stays where it was
+# Calls of more than 1280 channels whose blocks are one round go to this kernel, in every form it accepts; of 1280 and fewer, none
 def test_route(env):
     torch, oracle, fq, dev = env
     for hook in (fq.debug_force_few_rows, fq.debug_force_tile_splitk, fq.debug_force_stream):
@@ -119,5 +118,10 @@ def test_route(env):
                 for name in call:
                     assert torch.equal(got[name], want[name])
             fq.debug_force_chunk(-1)
-            fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0, scan_for=nx)
-            assert fq.debug_last_launch()["tile"] >= 0
+            want = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0)["q"]
+            fq.flexiq_dynamic_positions(nx, want)
+            positions = fq.flexiq_layer_positions(nx)
+            fq.flexiq_static_positions(nx)
+            got = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0, scan_for=nx)["q"]   # (a scan for the consumer follows as a kernel of its own)
+            assert (fq.debug_last_launch()["tile"] == -7) == taken and torch.equal(got, want)
+            assert (np.asarray(fq.flexiq_layer_positions(nx)) == np.asarray(positions)).all()
