@@ -350,15 +350,16 @@ static ChunkChoice choose(const flexiq_layer *L, int64_t M, int out_bytes, int n
 }
 
 // Launches k_chunk when the call qualifies: plain outputs or int8 rows lowered for a consumer.  It is offered what the kernels for few rows and few
-// tiles leave, and takes calls of more than 1280 channels (up to there k_halo and k_wreg are there) whose blocks are all resident at once.  Time here over
+// tiles leave, and takes calls of more than 1280 channels (up to there k_wreg is level) whose blocks are all resident at once.  Time here over
 // time in the tiled kernel on 310 such calls, geometric means: one round, r = 0 / 0.25 / 0.5 / 0.75 / 1: 0.89 / 0.79 / 0.82 / 0.74 / 0.73 (the worst 1.10), fp32 out
-// 0.91 at r = 0 and 0.79 at r = 1; two rounds and more 0.80 to 1.07, up to 1.20: the tiled kernel's blocks walk several tiles without a new prologue.
+// 0.91 at r = 0 and 0.79 at r = 1.  Of 576 to 1024 channels it takes what k_halo would: time here over time there on 212 calls, 576 to 672 / 704 to 800 / 832 to 1024
+// channels 0.93 / 0.94 / 0.88, fp32 out 0.96 / 0.96 / 0.99 (the worst 1.05; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).  Two rounds and more 0.80 to 1.07, up to 1.20: the tiled kernel's blocks walk several tiles without a new prologue.
 int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
 {
     using namespace chunk;
     *taken = 0;
     g_last = 0;
-    if (g_force == 0 || (g_force < 0 && L->C <= 1280)) return FLEXIQ_OK;
+    if (g_force == 0) return FLEXIQ_OK;
     if (g_force < 0 && (few_rows_forced() || stream_forced() || halo_forced())) return FLEXIQ_OK;   // (those hooks compare with the tiled kernel)
     if (out->scan_for || out->x4 || out->x6) return FLEXIQ_OK;
     const bool q_only = out->q && !out->acc && !out->y && (L->N & 15) == 0;
@@ -366,6 +367,7 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
     if (lowering && !q_only) return FLEXIQ_OK;      // (the lowering build writes int8 only)
     const DeviceState &ds = g_dev[L->device];
     if (!ds.ready) return FLEXIQ_OK;
+    if (g_force < 0 && L->C <= 1280 && (L->C < 576 || halo_rows_choice(L, M, out, lower).shape < 0)) return FLEXIQ_OK;
     if (M > (1 << 24) || (int64_t)32 * 8 * L->C >= kFar) return FLEXIQ_OK;   // (row indices and the window of a tile)
     const ChunkChoice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, g_force > 0 ? g_force - 1 : -1);
     if (c.shape < 0 || (g_force < 0 && !c.one_round)) return FLEXIQ_OK;

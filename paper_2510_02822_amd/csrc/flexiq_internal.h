@@ -144,6 +144,7 @@ struct HaloChoice {
 HaloChoice halo_choice(const flexiq_layer *L, int B, int H, int W, int stride, int pad, const flexiq_out *out, const LowerArgs *lower);
 int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream,
                 const HaloChoice &c, const LowerArgs *lower);
+HaloChoice halo_rows_choice(const flexiq_layer *L, int64_t M, const flexiq_out *out, const LowerArgs *lower);
 int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken,
                      const LowerArgs *lower = nullptr);
 // (wreg.hip) linear calls of 288 to 1280 channels: the weights of a block resident in registers, row tiles streamed

@@ -1,6 +1,6 @@
 // Convolutions whose input tile stays in LDS while the weights stream past it: 3x3 filters at stride 1 or 2 and any padding with
 // any multiple of 32 input channels, and strided (2) or padded 1x1 filters (ResNet stages 2-4, downsampling layers, small
-// batches).  Which calls it gets beyond one round of blocks: conv_route() in gemm.hip.  Linear layers of up to 1024 channels are served as well where a call is one short round of blocks.
+// batches).  Which calls it gets beyond one round of blocks: conv_route() in gemm.hip.  Linear layers of up to 544 channels are served as well where a call is one short round of blocks (up to 1024 channels such calls are k_chunk's, which it tells from the choice here).
 //
 // What bounded these calls in the tiled implicit-GEMM kernel (k_mixed) was not matrix work: a K-step there is 64 channels of
 // one filter tap, whose activations are fetched (and, for 4-bit groups, bit-lowered) again for each of the nine taps through
@@ -523,24 +523,29 @@ int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int
 
 bool halo_forced() { return halo::g_force >= 0; }
 
-// The same for a linear call of M rows of at most 1024 channels (the rows of a tile are all there is to its image): *taken = 0 also
+// The same for a linear call of M rows of at most 1024 channels (the rows of a tile are all there is to its image): shape < 0 also
 // where the tiled kernel is ahead.
-int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
+HaloChoice halo_rows_choice(const flexiq_layer *L, int64_t M, const flexiq_out *out, const LowerArgs *lower)
 {
-    *taken = 0;
     halo::g_last = 0;
-    if (M > (1 << 20) || M * L->C >= (1 << 30)) return FLEXIQ_OK;   // (row indices times the tile's rows, and the window of the input)
+    if (M > (1 << 20) || M * L->C >= (1 << 30)) return HaloChoice();   // (row indices times the tile's rows, and the window of the input)
     if (halo::g_force < 0) {
-        if (L->N & (out->q ? 15 : 3)) return FLEXIQ_OK;   // (ragged output rows leave element by element here)
-        if (few_rows_forced() || stream_forced()) return FLEXIQ_OK;   // (those hooks compare with the tiled kernel)
+        if (L->N & (out->q ? 15 : 3)) return HaloChoice();   // (ragged output rows leave element by element here)
+        if (few_rows_forced() || stream_forced()) return HaloChoice();   // (those hooks compare with the tiled kernel)
     }
     const HaloChoice c = choice_any(L, 1, 1, (int)M, 1, 0, true, out, lower);
-    if (c.shape < 0) return FLEXIQ_OK;
     // Linear calls of more than one short round stay with the tiled kernel: its blocks keep several tiles' loads in flight, where
     // a block here copies, multiplies and stores one after the other (us there and here: 1576 x 768 -> 3072 10.2 and 11.2; 6304 x
     // 768 -> 3072 22.7 and 26.1; below the line, 1576 x 1024 -> 1024 8.7 and 7.2; 177 x 448 -> 1856 6.4 and 4.9; 1234 x 704 -> 128 7.2
     // and 5.4: 11 % on average over 131 such calls, the worst 5 % behind).
-    if (halo::g_force < 0 && c.cost > 10000.0) return FLEXIQ_OK;
+    return halo::g_force < 0 && c.cost > 10000.0 ? HaloChoice() : c;
+}
+
+int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
+{
+    *taken = 0;
+    const HaloChoice c = halo_rows_choice(L, M, out, lower);
+    if (c.shape < 0) return FLEXIQ_OK;
     const int rc = launch_any(L, X, 1, 1, (int)M, 1, 0, true, out, stream_, c, lower);
     if (rc == FLEXIQ_OK) *taken = 1 + c.shape;
     return rc;

@@ -96,20 +96,21 @@ def test_lowered_for_a_consumer_prelowered_and_positions_found_at_run_time(env, 
     fq.debug_force_chunk(-1)
 
 
-# Calls of more than 1280 channels whose blocks are one round go to this kernel, in every form it accepts; of 1280 and fewer, none
+# Calls of more than 1280 channels whose blocks are one round go to this kernel, in every form it accepts, and from 576 channels on those that would be one
+# short round of the kernel with a resident input tile; no other of at most 1280
 def test_route(env):
     torch, oracle, fq, dev = env
     for hook in (fq.debug_force_few_rows, fq.debug_force_tile_splitk, fq.debug_force_stream):
         hook(-1)
     gen = np.random.default_rng(5)
-    for C, taken in ((1280, False), (1312, True)):
+    for C, M, taken in ((1280, 3000, False), (1312, 3000, True), (1024, 1500, True), (1024, 9000, False), (576, 1500, True), (544, 1500, False)):
         nx = fq.flexiq_quantize_pack(0.02 * gen.standard_normal((64, 768), dtype=np.float32), np.ones(768, np.float32), 0.03, 32)
         hl = fq.flexiq_quantize_pack(0.02 * gen.standard_normal((768, C), dtype=np.float32), np.ones(C, np.float32), 0.03, 32, out_perm=nx.info()["perm"])
-        X = torch.randint(-128, 128, (3000, C), dtype=torch.int8, device=dev)
+        X = torch.randint(-128, 128, (M, C), dtype=torch.int8, device=dev)
         for r in (0.0, 0.5):
             fq.flexiq_set_ratio(hl, r)
             fq.flexiq_set_ratio(nx, 0.5)
-            for call in (dict(q=True), dict(y=True), dict(acc=True, q=True)):
+            for call in (dict(q=True), dict(y=True), dict(acc=True, q=True))[: 3 if C > 1280 else 1]:   # (whether a round is short depends on what is written)
                 fq.debug_force_chunk(-1)
                 got = fq.flexiq_mixed_gemm(hl, X, out_scale=1.0, **call)
                 assert (fq.debug_last_launch()["tile"] == -7) == taken
@@ -123,5 +124,5 @@ def test_route(env):
             positions = fq.flexiq_layer_positions(nx)
             fq.flexiq_static_positions(nx)
             got = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0, scan_for=nx)["q"]   # (a scan for the consumer follows as a kernel of its own)
-            assert (fq.debug_last_launch()["tile"] == -7) == taken and torch.equal(got, want)
+            assert (fq.debug_last_launch()["tile"] == -7) == (C > 1280) and torch.equal(got, want)
             assert (np.asarray(fq.flexiq_layer_positions(nx)) == np.asarray(positions)).all()
