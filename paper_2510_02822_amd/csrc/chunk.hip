@@ -352,7 +352,8 @@ static ChunkChoice choose(const flexiq_layer *L, int64_t M, int out_bytes, int n
 // Launches k_chunk when the call qualifies: plain outputs or int8 rows lowered for a consumer.  It is offered what the kernels for few rows and few
 // tiles leave, and takes calls of more than 1280 channels (up to there k_wreg is level) whose blocks are all resident at once.  Time here over
 // time in the tiled kernel on 310 such calls, geometric means: one round, r = 0 / 0.25 / 0.5 / 0.75 / 1: 0.89 / 0.79 / 0.82 / 0.74 / 0.73 (the worst 1.10), fp32 out
-// 0.91 at r = 0 and 0.79 at r = 1.  Of 576 to 1024 channels it takes what k_halo would: time here over time there on 212 calls, 576 to 672 / 704 to 800 / 832 to 1024
+// 0.91 at r = 0 and 0.79 at r = 1.  Not tiles of 192 rows and more by 256 columns whose activations need no lowering: there the tiled kernel keeps its
+// matrix cores busy as well (int8 out, r = 0 0.99 to 1.04, 12608 x 4096 -> 1024 level to 2 % behind; fp32 out 0.90 to 0.96; with lowering 0.78 to 1.03).  Of 576 to 1024 channels it takes what k_halo would: time here over time there on 212 calls, 576 to 672 / 704 to 800 / 832 to 1024
 // channels 0.93 / 0.94 / 0.88, fp32 out 0.96 / 0.96 / 0.99 (the worst 1.05; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).  Two rounds and more 0.80 to 1.07, up to 1.20: the tiled kernel's blocks walk several tiles without a new prologue.
 int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
 {
@@ -373,6 +374,7 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
     if (c.shape < 0 || (g_force < 0 && !c.one_round)) return FLEXIQ_OK;
     const Shape &s = kShapes[c.shape];
     const int P = 32 * s.fr, BN = 32 * kWaves / s.wk;
+    if (g_force < 0 && s.fr >= 6 && s.wk == 1 && !out->y && (L->x_prelowered || L->max_4bit_ch == 0)) return FLEXIQ_OK;   // (as said above)
     Params p = {};
     p.units = L->C / kUnit;
     p.X = X; p.W8 = L->d_w8; p.ashift = L->dynamic ? L->d_ashift_dyn : L->d_ashift; p.cs = L->d_cs;
