@@ -867,10 +867,9 @@ extern "C" int flexiq_dynamic_positions(flexiq_layer *L, const int8_t *X, int64_
     if (rows > 0 && !X) return FLEXIQ_EINVAL;
     if (rows > 0 && !aligned16(X)) return FLEXIQ_EALIGN;
     const ScanLaunch sl = scan_launch(L, rows, kScanRowBlocks);
-    k_dyn_positions<true><<<dim3(sl.gx, sl.gy), kScanThreads, 0, (hipStream_t)stream>>>(
-        X, sl.pieces > 0 ? rows : 0, L->C, sl.pieces, sl.tx_log2, L->group_size, L->G, sl.g4, L->d_scan + standalone_scan_offset(L->G), L->d_ashift,
-        L->d_ashift_dyn);
-    FLEXIQ_HIP(hipGetLastError());
+    // (launched like the product that it may stand behind, flexiq_out.scan_for: what another call left behind is not its to report)
+    FLEXIQ_HIP(launch_kernel(k_dyn_positions<true>, dim3(sl.gx, sl.gy), dim3(kScanThreads), 0, stream, X, sl.pieces > 0 ? rows : 0, L->C, sl.pieces,
+                             sl.tx_log2, L->group_size, L->G, sl.g4, L->d_scan + standalone_scan_offset(L->G), L->d_ashift, L->d_ashift_dyn));
     L->dynamic = true;
     return FLEXIQ_OK;
 }
@@ -906,10 +905,8 @@ extern "C" int flexiq_dynamic_positions_static(flexiq_layer *L, const int8_t *X,
     // The array is zero when the library is loaded and every scan leaves the words it touched at zero again (its
     // last block clears masks and counter), so nothing is cleared here.
     const ScanLaunch sl = scan_launch(L, rows, 128);
-    k_dyn_positions<false><<<dim3(sl.gx, sl.gy), kScanThreads, 0, (hipStream_t)stream>>>(X, sl.pieces > 0 ? rows : 0, L->C, sl.pieces,
-                                                                                           sl.tx_log2, L->group_size, L->G, sl.g4, words,
-                                                                                           L->d_ashift, L->d_ashift_dyn);
-    FLEXIQ_HIP(hipGetLastError());
+    FLEXIQ_HIP(launch_kernel(k_dyn_positions<false>, dim3(sl.gx, sl.gy), dim3(kScanThreads), 0, stream, X, sl.pieces > 0 ? rows : 0, L->C, sl.pieces,
+                             sl.tx_log2, L->group_size, L->G, sl.g4, words, L->d_ashift, L->d_ashift_dyn));
     L->dynamic = true;
     return FLEXIQ_OK;
 }

@@ -38,3 +38,42 @@ def test_scan_edges(M, C, gs):
             fq.flexiq_static_positions(hl)
             fq.flexiq_dynamic_positions_static(hl, Xd)
             assert np.array_equal(fq.flexiq_layer_positions(hl)[:G], want[:G]), (M, C, gs, r)
+
+
+def _runtime():
+    """The HIP runtime that this process runs on."""
+    import ctypes
+    paths = {line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line}
+    assert len(paths) == 1, paths
+    lib = ctypes.CDLL(paths.pop())
+    return lib.hipSetDevice, lib.hipGetLastError
+
+
+@pytest.mark.parametrize("M,C", [(3, 1024), (200, 1024), (600, 1600), (200, 128)])
+def test_a_scan_reports_only_its_own_errors(M, C):
+    """An error that another call of the thread has left behind (here: a device that does not exist) is neither reported by a product that scans
+    for its consumer, on whichever kernels it runs, nor by the scan alone, nor taken away."""
+    import torch
+    import paper_2510_02822_amd as fq
+    fq.load()
+    gen = np.random.default_rng(7)
+    N = 512
+    nx = fq.flexiq_quantize_pack(0.02 * gen.standard_normal((64, N), dtype=np.float32), np.ones(N, np.float32), 0.03, 32)
+    hl = fq.flexiq_quantize_pack(0.02 * gen.standard_normal((N, C), dtype=np.float32), np.ones(C, np.float32), 0.03, 32, out_perm=nx.info()["perm"])
+    fq.flexiq_set_ratio(nx, 1.0)
+    X = torch.randint(-128, 128, (M, C), dtype=torch.int8, device="cuda")
+    q = torch.empty(M, N, dtype=torch.int8, device="cuda")
+    def product():
+        fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0, bufs={"q": q}, scan_for=nx)
+    product()
+    torch.cuda.synchronize()
+    set_device, last_error = _runtime()
+    for call in (product, lambda: fq.flexiq_dynamic_positions(nx, q), lambda: fq.flexiq_dynamic_positions_static(nx, q)):
+        last_error()
+        assert set_device(1 << 20) != 0
+        try:
+            call()
+        finally:
+            left = last_error()
+        assert left != 0
+    torch.cuda.synchronize()
