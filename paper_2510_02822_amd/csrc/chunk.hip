@@ -12,6 +12,7 @@
 //   * the sums of the WK shares meet in LDS.
 // Same int8 MFMA, int32 sums and epilogue arithmetic as the other kernels: bit-identical outputs.
 #include <algorithm>
+#include <cmath>
 
 #include "flexiq_internal.h"
 #include "flexiq_test.h"
@@ -320,13 +321,23 @@ int prepare_chunk_kernels(int device)
     return FLEXIQ_OK;
 }
 
-// The block shape for a call of M rows: the least modelled time, 0.6 us and per round of blocks 3.4 us, the chunks, and 39 fs per output byte.  Fitted
-// to 7400 timed calls (102 layers of 1056 to 4096 channels, 64 to 5472 columns, 100 to 12608 rows), a tenth off (root mean square); the shape it picks is
-// within 0.8 % of the best (geometric mean; at worst a third, where two blocks share a compute unit).
-static ChunkChoice choose(const flexiq_layer *L, int64_t M, int out_bytes, int num_cu, int only)
+// The block shape for a call of M rows, by the least modelled time: 0.6 us and per round of blocks 4.2 us, 32 fs per output byte, and the longer of the
+// chunks and the weights' way from the last-level cache (the fourth root of the sum of their fourth powers).  A block reads the weights of its columns once, straight
+// into registers, and shares them with no block but those of its XCD that work on the same columns of other row tiles: the weights cross once per row tile,
+// up to eight times (XCDs), at 7.1 to 7.4 TB/s at most.  (Up to 1280 channels they are on their way before a block's other trips to memory end: counted,
+// they made 560 such calls 2 % slower, up to 1.38 times; not counted.)  Fitted to 58900 times (7700 calls of 1344 to 8192 channels, 64 to 16384 columns, 65 to 64000
+// rows, every shape whose blocks are one round), 6.8 % off (root mean square; 15.8 % without the weights, which took 2.7 times the modelled time where they are
+// the most: 157 x 4992 -> 12144 34.7 us in the tiled kernel, 44.7 here, modelled at 18).
+struct Choice {
+    int shape = -1;
+    double us = 0;
+    double weights = 0;      // the weights' share of it
+    bool one_round = false;  // every block is resident from the start
+};
+static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, int num_cu, int only)
 {
     using namespace chunk;
-    ChunkChoice c;
+    Choice c;
     const int units = L->C / kUnit;
     const double low = L->x_prelowered ? 0.0 : (double)L->max_4bit_ch / L->C;
     for (int i = 0; i < kNumShapes; ++i) {
@@ -337,12 +348,14 @@ static ChunkChoice choose(const flexiq_layer *L, int64_t M, int out_bytes, int n
         if (blocks * 8 * ncb >= (1ll << 32) || blocks > 0x3fffffff) continue;   // (the division of the block index)
         const bool two = s.step2 > 0 && blocks > num_cu;
         const int64_t side = two ? 2 : 1, rounds = (blocks + side * num_cu - 1) / (side * num_cu);
-        const int chunks = (units + kUnits * s.wk - 1) / (kUnits * s.wk);
-        const double step = two ? s.step2 + low * s.low2 : s.step + low * s.low;
-        const double us = 0.6 + (double)rounds * (3.4 + 1e-3 * chunks * step + 39e-6 * (double)(side * P * BN) * out_bytes);
+        const double chunks = 1e-3 * ((units + kUnits * s.wk - 1) / (kUnits * s.wk)) * (two ? s.step2 + low * s.low2 : s.step + low * s.low);
+        const double weights = L->C > 1280 ? (double)std::min<int64_t>(tiles, 8) * (double)(ncb * BN) * L->C / 7.4e6 : 0.0;
+        const double c2 = chunks * chunks, w2 = weights / rounds * (weights / rounds);
+        const double us = 0.6 + (double)rounds * (4.2 + std::sqrt(std::sqrt(c2 * c2 + w2 * w2)) + 32e-6 * (double)(side * P * BN) * out_bytes);
         if (c.shape < 0 || us < c.us) {
             c.shape = i;
             c.us = us;
+            c.weights = weights / us;
             c.one_round = rounds == 1;
         }
     }
@@ -350,11 +363,19 @@ static ChunkChoice choose(const flexiq_layer *L, int64_t M, int out_bytes, int n
 }
 
 // Launches k_chunk when the call qualifies: plain outputs or int8 rows lowered for a consumer.  It is offered what the kernels for few rows and few
-// tiles leave, and takes calls of more than 1280 channels (up to there k_wreg is level) whose blocks are all resident at once.  Time here over
-// time in the tiled kernel on 310 such calls, geometric means: one round, r = 0 / 0.25 / 0.5 / 0.75 / 1: 0.89 / 0.79 / 0.82 / 0.74 / 0.73 (the worst 1.10), fp32 out
-// 0.91 at r = 0 and 0.79 at r = 1.  Not tiles of 192 rows and more by 256 columns whose activations need no lowering: there the tiled kernel keeps its
-// matrix cores busy as well (int8 out, r = 0 0.99 to 1.04, 12608 x 4096 -> 1024 level to 2 % behind; fp32 out 0.90 to 0.96; with lowering 0.78 to 1.03).  Of 576 to 1024 channels it takes what k_halo would: time here over time there on 212 calls, 576 to 672 / 704 to 800 / 832 to 1024
-// channels 0.93 / 0.94 / 0.88, fp32 out 0.96 / 0.96 / 0.99 (the worst 1.05; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).  Two rounds and more 0.80 to 1.07, up to 1.20: the tiled kernel's blocks walk several tiles without a new prologue.
+// tiles leave, and takes calls of more than 1280 channels (up to there k_wreg is level) whose blocks are all resident at once.
+// Times here over times in the tiled kernel on 1800 such calls of 544 to 8192 channels, 64 to 16384 columns and 65 to 40000 rows, geometric mean 0.79, 3 % of
+// them more than 3 % behind (the worst 1.27, 826 x 4704 -> 8048 at r = 0.5).  Not, by 7700 calls timed in every shape:
+//   * tiles of 192 rows and more by 256 columns whose activations need no lowering, int8 out: there the tiled kernel keeps its matrix cores busy as well (0.99
+//     to 1.04; 12608 x 4096 -> 1024 level to 2 % behind; fp32 out 0.90 to 0.96, with lowering 0.78 to 1.03);
+//   * 128 rows and more per tile where a layer has at most 128 columns: the block computes up to four times as many (1.00 to 1.24 by shape, up to 1.48; smaller
+//     tiles 0.68 to 0.91);
+//   * 128 rows and more per tile, or two blocks on a compute unit, where the weights take more than 0.4 of the time, unless at least three channels in ten are at 4
+//     bits: both kernels then wait for the same weights (0.93 to 1.02, up to 1.72: 450 x 2176 -> 8096 15.0 us there, 24.2 here; smaller tiles 0.77 to 0.93);
+//   * two rounds and more: 0.80 to 1.07, up to 1.20 at r = 0 with int8 out; fp32 out with lowering 0.62 to 1 (the tiled kernel's blocks walk several tiles without a
+//     new prologue).
+// Of 576 to 1024 channels it takes what k_halo would where a block has at most seven fragments of rows times shares and a compute unit to itself: 635 calls
+// 0.90 (the worst 1.04; larger ones 1.04 to 1.14; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).
 int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
 {
     using namespace chunk;
@@ -370,11 +391,18 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
     if (!ds.ready) return FLEXIQ_OK;
     if (g_force < 0 && L->C <= 1280 && (L->C < 576 || halo_rows_choice(L, M, out, lower).shape < 0)) return FLEXIQ_OK;
     if (M > (1 << 24) || (int64_t)32 * 8 * L->C >= kFar) return FLEXIQ_OK;   // (row indices and the window of a tile)
-    const ChunkChoice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, g_force > 0 ? g_force - 1 : -1);
+    const Choice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, g_force > 0 ? g_force - 1 : -1);
     if (c.shape < 0 || (g_force < 0 && !c.one_round)) return FLEXIQ_OK;
     const Shape &s = kShapes[c.shape];
     const int P = 32 * s.fr, BN = 32 * kWaves / s.wk;
-    if (g_force < 0 && s.fr >= 6 && s.wk == 1 && !out->y && (L->x_prelowered || L->max_4bit_ch == 0)) return FLEXIQ_OK;   // (as said above)
+    const int64_t blocks = ((M + P - 1) / P) * ((L->N + BN - 1) / BN);
+    if (g_force < 0) {   // (as said above)
+        const int low = L->x_prelowered ? 0 : L->max_4bit_ch;
+        if (s.fr >= 6 && s.wk == 1 && !out->y && low == 0) return FLEXIQ_OK;
+        if (s.fr >= 4 && L->N <= 128) return FLEXIQ_OK;
+        if (L->C <= 1280 && (s.fr * s.wk >= 8 || blocks > ds.num_cu)) return FLEXIQ_OK;
+        if (c.weights > 0.4 && ((s.fr >= 4 && 10 * low < 3 * L->C) || blocks > ds.num_cu)) return FLEXIQ_OK;
+    }
     Params p = {};
     p.units = L->C / kUnit;
     p.X = X; p.W8 = L->d_w8; p.ashift = L->dynamic ? L->d_ashift_dyn : L->d_ashift; p.cs = L->d_cs;

@@ -154,12 +154,7 @@ int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fl
 // past them; *taken = 0: the call does not qualify
 int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
 // (chunk.hip) linear calls of a long reduction: activations in LDS chunk by chunk, weights straight into registers; *taken = 0: the call
-// does not qualify or another kernel is ahead.  us: its modelled time; one_round: every block is resident from the start
-struct ChunkChoice {
-    int shape = -1;
-    double us = 0;
-    bool one_round = false;
-};
+// does not qualify or another kernel is ahead
 int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
 // (wreg6.hip) the same for flexiq_mixed_gemm_fp6: 256 to 1280 channels, all of them (K6) on the FP6 matrix path; tiled_rows: how many rows
 // one after the other a compute unit would work through in the tiled kernel

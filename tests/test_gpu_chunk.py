@@ -126,3 +126,24 @@ def test_route(env):
             got = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=1.0, scan_for=nx)["q"]   # (a scan for the consumer follows as a kernel of its own)
             assert (fq.debug_last_launch()["tile"] == -7) == (C > 1280) and torch.equal(got, want)
             assert (np.asarray(fq.flexiq_layer_positions(nx)) == np.asarray(positions)).all()
+
+
+# What bounds a call decides: not where the weights of a wide layer cross once per row tile, nor where most of a tall block's columns are padding
+@pytest.mark.parametrize("M,C,N,r,out,taken", [
+    (140, 1920, 11696, 0.0, "q", True), (450, 2176, 8096, 0.0, "q", False), (204, 4480, 8864, 0.0, "q", False), (695, 3200, 10976, 0.0, "q", False),
+    (695, 3200, 10976, 1.0, "q", True), (414, 4992, 7712, 0.0, "y", False), (17, 3392, 7408, 0.5, "q", True), (51125, 1600, 80, 0.25, "q", False),
+    (20000, 1344, 64, 0.5, "q", True), (1314, 1728, 5968, 0.25, "q", False)])
+def test_route_by_what_bounds_the_call(env, M, C, N, r, out, taken):
+    torch, oracle, fq, dev = env
+    for hook in (fq.debug_force_few_rows, fq.debug_force_tile_splitk, fq.debug_force_stream, fq.debug_force_chunk):
+        hook(-1)
+    hl = fq.flexiq_quantize_pack(0.02 * np.random.default_rng(6).standard_normal((N, C), dtype=np.float32), np.ones(C, np.float32), 0.03, 32)
+    fq.flexiq_set_ratio(hl, r)
+    X = torch.randint(-128, 128, (M, C), dtype=torch.int8, device=dev)
+    got = fq.flexiq_mixed_gemm(hl, X, out_scale=1.0, **{out: True})[out]
+    tile = fq.debug_last_launch()["tile"]
+    fq.debug_force_chunk(0)
+    want = fq.flexiq_mixed_gemm(hl, X, out_scale=1.0, **{out: True})[out]
+    fq.debug_force_chunk(-1)
+    assert torch.equal(got, want)
+    assert (tile == -7) == taken
