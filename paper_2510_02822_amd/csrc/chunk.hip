@@ -376,7 +376,7 @@ static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, int num_cu
 //     new prologue).
 // Of 576 to 1024 channels it takes what k_halo would where a block has at most seven fragments of rows times shares and a compute unit to itself: 635 calls
 // 0.90 (the worst 1.04; larger ones 1.04 to 1.14; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).
-int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
+int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, bool halo, int *taken, const LowerArgs *lower)
 {
     using namespace chunk;
     *taken = 0;
@@ -389,7 +389,7 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
     if (lowering && !q_only) return FLEXIQ_OK;      // (the lowering build writes int8 only)
     const DeviceState &ds = g_dev[L->device];
     if (!ds.ready) return FLEXIQ_OK;
-    if (g_force < 0 && L->C <= 1280 && (L->C < 576 || halo_rows_choice(L, M, out, lower).shape < 0)) return FLEXIQ_OK;
+    if (g_force < 0 && L->C <= 1280 && (L->C < 576 || !halo)) return FLEXIQ_OK;
     if (M > (1 << 24) || (int64_t)32 * 8 * L->C >= kFar) return FLEXIQ_OK;   // (row indices and the window of a tile)
     const Choice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, g_force > 0 ? g_force - 1 : -1);
     if (c.shape < 0 || (g_force < 0 && !c.one_round)) return FLEXIQ_OK;

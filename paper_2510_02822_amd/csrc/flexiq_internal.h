@@ -148,14 +148,13 @@ HaloChoice halo_choice(const flexiq_layer *L, int B, int H, int W, int stride, i
 int launch_halo(const flexiq_layer *L, const int8_t *X, int B, int H, int W, int stride, int pad, const flexiq_out *out, void *stream,
                 const HaloChoice &c, const LowerArgs *lower);
 HaloChoice halo_rows_choice(const flexiq_layer *L, int64_t M, const flexiq_out *out, const LowerArgs *lower);
-int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken,
-                     const LowerArgs *lower = nullptr);
+int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, const HaloChoice &c, const LowerArgs *lower);
 // (wreg.hip) linear calls of 288 to 1280 channels: the weights of a block resident in registers, row tiles streamed
 // past them; *taken = 0: the call does not qualify
 int launch_wreg(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
 // (chunk.hip) linear calls of a long reduction: activations in LDS chunk by chunk, weights straight into registers; *taken = 0: the call
-// does not qualify or another kernel is ahead
-int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int *taken, const LowerArgs *lower);
+// does not qualify or another kernel is ahead.  halo: halo_rows_choice() has a shape for the call
+int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, bool halo, int *taken, const LowerArgs *lower);
 // (wreg6.hip) the same for flexiq_mixed_gemm_fp6: 256 to 1280 channels, all of them (K6) on the FP6 matrix path; tiled_rows: how many rows
 // one after the other a compute unit would work through in the tiled kernel
 int launch_wreg6(const flexiq_layer *L, const uint8_t *X6, int64_t M, const flexiq_out *out, void *stream, int K6, int64_t tiled_rows, int *taken,

@@ -541,14 +541,9 @@ HaloChoice halo_rows_choice(const flexiq_layer *L, int64_t M, const flexiq_out *
     return halo::g_force < 0 && c.cost > 10000.0 ? HaloChoice() : c;
 }
 
-int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, int *taken, const LowerArgs *lower)
+int launch_halo_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, const HaloChoice &c, const LowerArgs *lower)
 {
-    *taken = 0;
-    const HaloChoice c = halo_rows_choice(L, M, out, lower);
-    if (c.shape < 0) return FLEXIQ_OK;
-    const int rc = launch_any(L, X, 1, 1, (int)M, 1, 0, true, out, stream_, c, lower);
-    if (rc == FLEXIQ_OK) *taken = 1 + c.shape;
-    return rc;
+    return launch_any(L, X, 1, 1, (int)M, 1, 0, true, out, stream_, c, lower);
 }
 
 }  // namespace flexiq
