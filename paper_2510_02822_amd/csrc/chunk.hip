@@ -278,11 +278,6 @@ __global__ __launch_bounds__(kThreads) void k_chunk(const Params p)
     }
 }
 
-struct DeviceState {
-    bool ready = false;
-    int num_cu = 0;
-};
-static DeviceState g_dev[64];
 static int g_force = -1;   // test hook: >= 1: take this kernel with shape g_force - 1 whenever the call qualifies, 0 = never, -1 = automatic
 static int g_last = 0;
 
@@ -305,6 +300,13 @@ constexpr Shape kShapes[] = {{2, 1, pick<2, 1>, 366, 75, 768, 21}, {3, 1, pick<3
                              {1, 4, pick<1, 4>, 379, 205, 837, 123}, {2, 4, pick<2, 4>, 767, 290, 0, 0}, {3, 4, pick<3, 4>, 1158, 433, 0, 0}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
+struct DeviceState {
+    bool ready = false;
+    int num_cu = 0;
+    bool two[kNumShapes] = {};   // two blocks share a compute unit, whatever the outputs
+};
+static DeviceState g_dev[64];
+
 }  // namespace chunk
 
 int prepare_chunk_kernels(int device)
@@ -315,8 +317,16 @@ int prepare_chunk_kernels(int device)
     hipDeviceProp_t prop;
     FLEXIQ_HIP(hipGetDeviceProperties(&prop, device));
     g_dev[device].num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    for (const Shape &s : kShapes)
-        for (int out = 0; out < 3; ++out) FLEXIQ_HIP(hipFuncSetAttribute((const void *)s.fn(out), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(s.fr, s.wk)));
+    for (int i = 0; i < kNumShapes; ++i) {
+        const Shape &s = kShapes[i];
+        g_dev[device].two[i] = s.step2 > 0;   // (measured; and what was compiled still fits)
+        for (int out = 0; out < 3; ++out) {
+            int resident = 0;
+            FLEXIQ_HIP(hipFuncSetAttribute((const void *)s.fn(out), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(s.fr, s.wk)));
+            FLEXIQ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, (const void *)s.fn(out), kThreads, lds_bytes(s.fr, s.wk)));
+            if (resident < 2) g_dev[device].two[i] = false;
+        }
+    }
     g_dev[device].ready = true;
     return FLEXIQ_OK;
 }
@@ -334,10 +344,11 @@ struct Choice {
     double weights = 0;      // the weights' share of it
     bool one_round = false;  // every block is resident from the start
 };
-static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, int num_cu, int only)
+static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, const chunk::DeviceState &ds, int only)
 {
     using namespace chunk;
     Choice c;
+    const int num_cu = ds.num_cu;
     const int units = L->C / kUnit;
     const double low = L->x_prelowered ? 0.0 : (double)L->max_4bit_ch / L->C;
     for (int i = 0; i < kNumShapes; ++i) {
@@ -346,7 +357,7 @@ static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, int num_cu
         const int P = 32 * s.fr, BN = 32 * kWaves / s.wk;
         const int64_t ncb = (L->N + BN - 1) / BN, tiles = (M + P - 1) / P, blocks = ncb * tiles;
         if (blocks * 8 * ncb >= (1ll << 32) || blocks > 0x3fffffff) continue;   // (the division of the block index)
-        const bool two = s.step2 > 0 && blocks > num_cu;
+        const bool two = ds.two[i] && blocks > num_cu;
         const int64_t side = two ? 2 : 1, rounds = (blocks + side * num_cu - 1) / (side * num_cu);
         const double chunks = 1e-3 * ((units + kUnits * s.wk - 1) / (kUnits * s.wk)) * (two ? s.step2 + low * s.low2 : s.step + low * s.low);
         const double weights = L->C > 1280 ? (double)std::min<int64_t>(tiles, 8) * (double)(ncb * BN) * L->C / 7.4e6 : 0.0;
@@ -391,7 +402,7 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
     if (!ds.ready) return FLEXIQ_OK;
     if (g_force < 0 && L->C <= 1280 && (L->C < 576 || !halo)) return FLEXIQ_OK;
     if (M > (1 << 24) || (int64_t)32 * 8 * L->C >= kFar) return FLEXIQ_OK;   // (row indices and the window of a tile)
-    const Choice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds.num_cu, g_force > 0 ? g_force - 1 : -1);
+    const Choice c = choose(L, M, (out->q ? 1 : 0) + (out->y ? 4 : 0) + (out->acc ? 4 : 0), ds, g_force > 0 ? g_force - 1 : -1);
     if (c.shape < 0 || (g_force < 0 && !c.one_round)) return FLEXIQ_OK;
     const Shape &s = kShapes[c.shape];
     const int P = 32 * s.fr, BN = 32 * kWaves / s.wk;
