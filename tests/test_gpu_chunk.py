@@ -96,6 +96,37 @@ def test_lowered_for_a_consumer_prelowered_and_positions_found_at_run_time(env, 
     fq.debug_force_chunk(-1)
 
 
+@pytest.mark.parametrize("C,N,gs2", [(1376, 1056, 32), (992, 352, 32), (1344, 320, 64)])
+def test_lowered_for_a_consumer_whose_channels_end_inside_a_block(env, C, N, gs2):
+    """Columns that end 32 (or 64) into the last block of every width, 4-bit channels of the consumer that end inside a block, groups of 32 and 64."""
+    torch, oracle, fq, dev = env
+    M = 300
+    first = workloads.make_linear("chunk3", 23, C, M, C, N, 32, outlier_frac=0.02)
+    second = workloads.make_linear("chunk4", 23, C + 1, 64, N, 64, gs2)
+    x_scale = oracle.absmax_scale(first.Xcal)
+    amax = np.abs(first.Xcal).max(0)
+    o2, h2, _ = both_layers(second)
+    ol = oracle.prepare_layer(first.W, amax, x_scale, 32, bias=first.bias)
+    hl = fq.flexiq_quantize_pack(first.W, amax, x_scale, 32, bias=first.bias, out_perm=o2.perm)
+    Xq = np.ascontiguousarray(oracle.quantize(first.X, x_scale)[:, ol.perm])
+    X = torch.from_numpy(Xq).to(dev)
+    for r1, r2 in ((0.0, 0.5), (0.5, 1.0), (1.0, 3 * gs2 / N)):
+        fq.flexiq_set_ratio(hl, r1)
+        k4 = fq.flexiq_set_ratio(h2, r2)
+        acc = oracle.forward_gemm(ol, Xq, r1)
+        so = float(np.abs(oracle.dequant_f64(acc, x_scale, ol.w_scale, ol.bias)).max() / 127 * 0.9)
+        want = requant_fp32_sequence(acc, ol, so)[:, o2.perm].astype(np.int32)
+        for c in range(k4):   # (Section 4.1: cut to four bits at the position and put back there)
+            s = int(o2.a_shift[c // gs2])
+            want[:, c] = np.clip(want[:, c] >> s, -8, 7) << s
+        for k in range(1, len(SHAPES) + 1):
+            fq.debug_force_chunk(k)
+            got = fq.flexiq_mixed_gemm(hl, X, q=True, out_scale=so, lower_for=h2)["q"]
+            assert fq.debug_force_chunk(k) == k
+            assert (got.cpu().numpy() == want).all(), (r1, r2, k)
+    fq.debug_force_chunk(-1)
+
+
 # Calls of more than 1280 channels whose blocks are one round go to this kernel, in every form it accepts, and from 576 channels on those that would be one
 # short round of the kernel with a resident input tile; no other of at most 1280
 def test_route(env):
