@@ -30,19 +30,30 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kRsrcFlags = 0x00020000;
 
-// clamp(v, -(8 << s), (8 << s) - 1) with the low s bits cleared, on the four int8 lanes of a dword: the bit-lowered
-// value L(v, s) put back at its position (Section 4.1)
-__device__ __forceinline__ uint32_t lower4(uint32_t d, int s)
-{
-    const short lo = (short)((-(8 << s)) << 8), hi = (short)((((8 << s) - 1) << 8) | 0xFF);
-    const v2s lo2 = {lo, lo}, hi2 = {hi, hi};
-    v2s o = __builtin_bit_cast(v2s, d);   // odd bytes sit on top of the 16-bit halves
-    v2s e = o << (short)8;                // even bytes moved up
-    o = __builtin_elementwise_min(__builtin_elementwise_max(o, lo2), hi2);
-    e = __builtin_elementwise_min(__builtin_elementwise_max(e, lo2), hi2);
-    const uint32_t r = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, o), __builtin_bit_cast(uint32_t, e), 0x07030501u);
-    return r & (0x01010101u * ((0xFFu << s) & 0xFFu));
-}
+// What lowers the four int8 lanes of a dword at position s: clamp(v, -(8 << s), (8 << s) - 1) with the low s bits cleared, the bit-lowered
+// value L(v, s) put back at its position (Section 4.1); or what leaves them as they are (no select per dword: it is the vector ALU that
+// bounds the lowering).
+struct Lowering {
+    v2s lo, hi;      // the bounds in the upper byte of both 16-bit halves
+    uint32_t mask;
+    __device__ __forceinline__ Lowering(int s, bool low = true)
+    {
+        const short l = low ? (short)((-(8 << s)) << 8) : (short)0x8000, h = low ? (short)((((8 << s) - 1) << 8) | 0xFF) : (short)0x7FFF;
+        lo = (v2s){l, l};
+        hi = (v2s){h, h};
+        mask = low ? 0x01010101u * ((0xFFu << s) & 0xFFu) : 0xFFFFFFFFu;
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t d) const
+    {
+        v2s o = __builtin_bit_cast(v2s, d);   // odd bytes sit on top of the 16-bit halves
+        v2s e = o << (short)8;                // even bytes moved up
+        o = __builtin_elementwise_min(__builtin_elementwise_max(o, lo), hi);
+        e = __builtin_elementwise_min(__builtin_elementwise_max(e, lo), hi);
+        const uint32_t r = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, o), __builtin_bit_cast(uint32_t, e), 0x07030501u);
+        return r & mask;
+    }
+};
+__device__ __forceinline__ uint32_t lower4(uint32_t d, int s) { return Lowering(s)(d); }
 
 // Eight packed activation codes (a dword: channels 0 .. 3 in the low halves of its bytes, 4 .. 7 in the high halves) put back at position s as int8
 // values, code << s: hi = the dword with the wanted halves on top.
@@ -246,12 +257,11 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
     };
     auto use8 = [&](int k, int ks) {
         if (!COOP && !FP6 && !p.x_pre && 2 * ks < p.units4) {
-            const bool low = 2 * ks + (xp >> 1) < p.units4;   // (false: a unit read at 8 bits)
-            const int sa = xp >> 1 ? sa1[k] : sa0[k];
+            const Lowering lower(xp >> 1 ? sa1[k] : sa0[k], 2 * ks + (xp >> 1) < p.units4);   // (... or a unit read at 8 bits)
 #pragma unroll
             for (int f = 0; f < MF; ++f)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[k][f][i] = low ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
+                for (int i = 0; i < 4; ++i) x[k][f][i] = (int)lower((uint32_t)x[k][f][i]);
         }
         v4i b[MF];
         if (COOP && 2 * ks + 1 < p.units4) {
@@ -732,14 +742,12 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
                 for (int g = 0; g < FC; ++g) acc[f][g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w8[k][g], b[f], acc[f][g], 0, 0, 0);
         };
         auto use = [&](int k, int ks) {
-            const int u = 2 * ks + (xp >> 1);
             if (!FP6 && !p.x_pre && 2 * ks < p.units4) {   // (lowered before it crosses the lanes: fewer registers live)
-                const bool mine4 = u < p.units4;   // (false: a unit read at 8 bits)
-                const int sa = xp >> 1 ? sa1[k] : sa0[k];
+                const Lowering lower(xp >> 1 ? sa1[k] : sa0[k], 2 * ks + (xp >> 1) < p.units4);   // (... or a unit read at 8 bits)
 #pragma unroll
                 for (int f = 0; f < FR; ++f)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) x[k][f][i] = mine4 ? (int)lower4((uint32_t)x[k][f][i], sa) : x[k][f][i];
+                    for (int i = 0; i < 4; ++i) x[k][f][i] = (int)lower((uint32_t)x[k][f][i]);
             }
             multiply(k, x[k]);
         };
