@@ -386,7 +386,8 @@ static Choice choose(const flexiq_layer *L, int64_t M, int out_bytes, const chun
 //   * two rounds and more: 0.80 to 1.07, up to 1.20 at r = 0 with int8 out; fp32 out with lowering 0.62 to 1 (the tiled kernel's blocks walk several tiles without a
 //     new prologue).
 // Of 576 to 1024 channels it takes what k_halo would where a block has at most seven fragments of rows times shares and a compute unit to itself: 635 calls
-// 0.90 (the worst 1.04; larger ones 1.04 to 1.14; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28).
+// 0.90 (the worst 1.04; larger ones 1.04 to 1.14; 512 and 544 channels 0.95, up to 1.13, fp32 out 1.01, up to 1.28), and at most five of them where a layer has at most
+// 64 columns, of the 128 that such a block computes (96 rows in two shares 1.04 to 1.09: 22799 x 768 -> 64 at r = 1 7.4 us there, 8.0 here; fewer rows 0.90 to 1.01).
 int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream_, bool halo, int *taken, const LowerArgs *lower)
 {
     using namespace chunk;
@@ -411,7 +412,7 @@ int launch_chunk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq
         const int low = L->x_prelowered ? 0 : L->max_4bit_ch;
         if (s.fr >= 6 && s.wk == 1 && !out->y && low == 0) return FLEXIQ_OK;
         if (s.fr >= 4 && L->N <= 128) return FLEXIQ_OK;
-        if (L->C <= 1280 && (s.fr * s.wk >= 8 || blocks > ds.num_cu)) return FLEXIQ_OK;
+        if (L->C <= 1280 && (s.fr * s.wk >= (L->N <= 64 ? 6 : 8) || blocks > ds.num_cu)) return FLEXIQ_OK;
         if (c.weights > 0.4 && ((s.fr >= 4 && 10 * low < 3 * L->C) || blocks > ds.num_cu)) return FLEXIQ_OK;
     }
     Params p = {};

@@ -164,6 +164,7 @@ def test_route(env):
     (140, 1920, 11696, 0.0, "q", True), (450, 2176, 8096, 0.0, "q", False), (204, 4480, 8864, 0.0, "q", False), (695, 3200, 10976, 0.0, "q", False),
     (695, 3200, 10976, 1.0, "q", True), (414, 4992, 7712, 0.0, "y", False), (17, 3392, 7408, 0.5, "q", True), (51125, 1600, 80, 0.25, "q", False),
     (20000, 1344, 64, 0.5, "q", True), (1314, 1728, 5968, 0.25, "q", False),
+    (22799, 768, 64, 1.0, "q", False), (19097, 768, 32, 0.5, "q", False), (14170, 640, 48, 0.5, "q", True), (23447, 704, 128, 1.0, "q", True),
     (32371, 2176, 64, 0.5, "q", True)])   # (506 blocks: one round only if two of them share a compute unit)
 def test_route_by_what_bounds_the_call(env, M, C, N, r, out, taken):
     torch, oracle, fq, dev = env
