@@ -66,6 +66,42 @@ __device__ __forceinline__ uint32_t expand4(uint32_t hi, int s)
     return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, o), __builtin_bit_cast(uint32_t, e), 0x07030501u) & (0x01010101u * ((0xFFu << s) & 0xFFu));
 }
 
+// A wave's K-steps ks, ks + stride, ...: `left` of them, D in flight, each slot loaded again as soon as it is used up.  BEGUN: the first D are on their way.
+// EXACT: D steps have a path of their own, on which the compiler knows how many loads are in flight; behind loads that depend on `left` the first step waits for all
+// of them, and the steps' ways through LDS follow one by one.  r = 0, us with loads in operand order, without that path and with it: 3 x 3520 -> 128 3.25 / 3.53 /
+// 3.48, 4 x 864 -> 10912 3.26 / 3.6 / 3.46, 4 x 3936 -> 480 3.5 / 3.75 / 3.6.  (Where registers are short it costs more: FP6 builds of few rows up to 1.07 times slower with
+// it, those of a tile per block spill.  Tried: one step's way through LDS ahead of the multiplication: no gain; loads masked to the rows there are: few rows 1.01, tiles of FP6 calls
+// of few rows 0.95, of others 1.01.)
+template <int D, bool BEGUN, bool EXACT, class Load, class Use>
+__device__ __forceinline__ void wave_steps(const Load &load, const Use &use, int ks, int left, int stride)
+{
+    if (EXACT && !BEGUN && left == D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) load(k, ks + k * stride);
+#pragma unroll
+        for (int k = 0; k < D; ++k) use(k, ks + k * stride);
+        return;
+    }
+    if constexpr (!BEGUN) {
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (k < left) load(k, ks + k * stride);
+    }
+    for (; left >= 2 * D; left -= D, ks += stride * D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            use(k, ks + k * stride);
+            load(k, ks + (k + D) * stride);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * D - 1; ++k)
+        if (k < left) {
+            use(k % D, ks + k * stride);
+            if (k + D < left) load(k % D, ks + (k + D) * stride);
+        }
+}
+
 // ---- A block owns 16 output columns and the whole reduction.
 //
 // Splitting the reduction across blocks makes the slices meet in memory (store, ticket, re-read: three dependent trips;
@@ -299,42 +335,16 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[0][i] += t[i] >> ((down >> (8 * i)) & 31u);
     };
-    // the wave's steps first, first + nw, ...: `left` of them, D in flight; `begun`: the first D are on their way
-    auto begin = [&](auto load, auto depth, int first, int left) {
-        constexpr int D = decltype(depth)::value;
-#pragma unroll
-        for (int k = 0; k < D; ++k)
-            if (k < left) load(k, first + k * nw);
-    };
-    auto run = [&](auto load, auto use, auto depth, int first, int left) {
-        constexpr int D = decltype(depth)::value;
-        int ks = first;
-        for (; left >= 2 * D; left -= D, ks += nw * D) {
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                use(k, ks + k * nw);
-                load(k, ks + (k + D) * nw);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 2 * D - 1; ++k)
-            if (k < left) {
-                use(k % D, ks + k * nw);
-                if (k + D < left) load(k % D, ks + (k + D) * nw);
-            }
-    };
-    using D8 = std::integral_constant<int, UN>;
-    using D4 = std::integral_constant<int, U4>;
     auto count = [&](int first, int end) { return first < end ? (end - first + nw - 1) / nw : 0; };
-    int left4 = 0;
     if constexpr (P4) {
-        left4 = count(wave, p.s4);
-        begin(load4, D4{}, wave, left4);
+        wave_steps<U4, false, true>(load4, use4, wave, count(wave, p.s4), nw);
         ks0 = p.s4 + (wave + nw - p.s4 % nw) % nw;   // (the deal goes on with the other K-steps)
     }
     const int left8 = count(ks0, p.steps);
-    if constexpr (!P4) begin(load8, D8{}, ks0, left8);   // (a wave beyond the last K-step loads nothing)
     if constexpr (COOP) {
+#pragma unroll
+        for (int k = 0; k < UN; ++k)
+            if (k < left8) load8(k, ks0 + k * nw);   // (a wave beyond the last K-step loads nothing)
         // few rows: in the fragment layout most lanes would hold no row, and lowering there would cost every wave the full
         // instruction count for a handful of values.  The block lowers the 4-bit channels of its rows once, every lane a
         // 16-byte piece, into LDS, while the first weight fragments are on their way.
@@ -348,11 +358,7 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
         }
         __syncthreads();
     }
-    if constexpr (P4) {
-        run(load4, use4, D4{}, wave, left4);
-        begin(load8, D8{}, ks0, left8);
-    }
-    run(load8, use8, D8{}, ks0, left8);
+    wave_steps<UN, COOP, !FP6>(load8, use8, ks0, left8, nw);
 
     // ---- the waves' sums meet in LDS
 #pragma unroll
@@ -751,24 +757,6 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
             }
             multiply(k, x[k]);
         };
-        auto run = [&](auto load, auto use, int ks, int left) {
-#pragma unroll
-            for (int k = 0; k < UN; ++k)
-                if (k < left) load(k, ks + k * NW);
-            for (; left >= 2 * UN; left -= UN, ks += NW * UN) {
-#pragma unroll
-                for (int k = 0; k < UN; ++k) {
-                    use(k, ks + k * NW);
-                    load(k, ks + (k + UN) * NW);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 2 * UN - 1; ++k)
-                if (k < left) {
-                    use(k % UN, ks + k * NW);
-                    if (k + UN < left) load(k % UN, ks + (k + UN) * NW);
-                }
-        };
         auto count = [&](int first, int end) { return first < end ? (end - first + NW - 1) / NW : 0; };
         if constexpr (XP) {
             // the K-steps of packed codes first, 8 bytes per lane and fragment
@@ -793,10 +781,10 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
                 }
                 multiply(k, e);
             };
-            run(load4, use4, wave, count(wave, s4));
+            wave_steps<UN, false, false>(load4, use4, wave, count(wave, s4), NW);
             first = s4 + (wave + NW - s4 % NW) % NW;   // (the deal goes on with the other K-steps)
         }
-        run(load, use, first, count(first, p.steps));
+        wave_steps<UN, false, false>(load, use, first, count(first, p.steps), NW);
     }
 
     // ---- the waves' sums meet in LDS; wave w adds up and finishes fragments w, w + NW, ...
@@ -1114,7 +1102,7 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
     return FLEXIQ_OK;
 }
 
-// Launches k_tile_splitk for a linear call of more than 32 rows whose output tiles leave most compute units idle on a long
+// Launches k_tile_splitk for a linear call of more than 32 rows (packed codes: fewer) whose output tiles leave most compute units idle on a long
 // reduction; *taken = 0: the call was left to the other kernels, else 1 / 2 / 3: tiles of 64 x 64 / 32 x 64 / 32 x 32.
 int launch_tile_splitk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int num_cu, int *taken,
                        const LowerArgs *lower, const uint8_t *X4)
