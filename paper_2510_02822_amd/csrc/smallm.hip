@@ -1085,6 +1085,9 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
         p.s6 = K6 / 64;
         if (shape == 0) err = launch_kernel(k_tile_splitk<4, 4, 8, 2, true>, grid, dim3(512), lds, stream, p);
         else if (shape == 1) err = launch_kernel(k_tile_splitk<2, 4, 8, 4, true>, grid, dim3(512), lds / 2, stream, p);   // (eight waves: registers)
+        // (one row fragment where the call has no more; the second is a load, a way through LDS and two multiplications of nothing in every step of the chain.  r = 0.25 / 0.5 / 1,
+        // two fragments and one: 2 x 4992 -> 3904 5.75 / 5.7 / 5.5 and 5.0 / 5.25 / 5.4 us, 8 x 1088 -> 64 3.2 / 3.25 / 3.4 and 2.95 / 3.0 / 3.2)
+        else if (M <= 16) err = launch_kernel(k_tile_splitk<1, 2, 16, 4, true>, grid, dim3(1024), lds / 2, stream, p);
         else err = launch_kernel(k_tile_splitk<2, 2, 16, 4, true>, grid, dim3(1024), lds, stream, p);
     } else if (X4) {
         p.X4 = X4;

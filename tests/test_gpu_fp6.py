@@ -356,3 +356,31 @@ def test_fp6_chain_few_rows(env, M):
         assert (codes == np.clip(X2[:, :k6].astype(np.int32) >> sh[:, :k6], -8, 7)).all(), (M, r2)
         got = fq.flexiq_mixed_gemm_fp6(h2, mid, x6_2, acc=True)["acc"].cpu().numpy()
         assert (got == oracle.forward_gemm(o2, X2, r2)).all(), (M, r2)
+
+
+@pytest.mark.parametrize("M", [1, 15, 16, 17])
+@pytest.mark.parametrize("K,N", [(832, 96), (2112, 64), (4160, 160)])
+def test_fp6_lowers_for_a_consumer_on_one_fragment_of_rows(env, M, K, N):
+    """Up to 16 rows a tile per block has one row fragment: waves with no, some and many int8 steps behind the FP6 ones, rows that end in it and just beyond."""
+    torch, oracle, fq, dev = env
+    c1 = workloads.make_linear("fp6one1", 8, 451 + M, M, K, N, 64, outlier_frac=0.02)
+    c2 = workloads.make_linear("fp6one2", 8, 452, 32, N, 24, 32)
+    xs, am = calib(c1)
+    am2 = np.abs(c2.Xcal).max(0)
+    o2 = oracle.prepare_layer(c2.W, am2, oracle.absmax_scale(c2.Xcal), 32)
+    h2 = fq.flexiq_quantize_pack(c2.W, am2, oracle.absmax_scale(c2.Xcal), 32)
+    o1 = oracle.prepare_layer(c1.W, am, xs, 64, bias=c1.bias)
+    h1 = fq.flexiq_quantize_pack(c1.W, am, xs, 64, bias=c1.bias, out_perm=o2.perm)
+    Xq = np.ascontiguousarray(oracle.quantize(c1.X, xs)[:, o1.perm])
+    sh = np.repeat(o2.a_shift.astype(np.int32), 32)[None, :]
+    k4 = fq.flexiq_set_ratio(h2, 0.5)
+    for r in (0.25, 0.5, 1.0):
+        fq.flexiq_set_ratio(h1, r)
+        acc = oracle.forward_gemm(o1, Xq, r)
+        so = float(np.abs(oracle.dequant_f64(acc, xs, o1.w_scale, o1.bias)).max() / 127.0 * 0.9) or 1.0
+        want = requant_fp32_sequence(acc, o1, so)[:, o2.perm].astype(np.int32)
+        want[:, :k4] = np.clip(want[:, :k4] >> sh[:, :k4], -8, 7) << sh[:, :k4]
+        x6, xlow = fq.flexiq_lower_fp6(h1, _dev(torch, Xq, dev))
+        got = fq.flexiq_mixed_gemm_fp6(h1, xlow, x6, q=True, out_scale=so, lower_for=h2)["q"].cpu().numpy()
+        assert fq.debug_force_tile_splitk(-1) == 3, (M, r)
+        assert (got == want).all(), (M, r)
