@@ -442,12 +442,13 @@ def measure_shapes(torch, fq, workloads, dev, resnet=True):
             us = _median_graph_us(torch, lambda: one_pass(fn), 1, repeats=5, settle_s=0.04)
             n_tiled = fq.debug_force_tile(-1)
             # which kernel every call of the pass ran on (eager pass after the timing; the route depends on the ratio)
-            routes = {"tiled": 0, "row-streaming": 0, "weights in registers": 0, "3x3, resident weights": 0, "resident input tile": 0}
+            routes = {"tiled": 0, "row-streaming": 0, "weights in registers": 0, "activations chunk by chunk": 0, "3x3, resident weights": 0, "resident input tile": 0}
             for c, (L, j) in enumerate(calls):
                 fq.flexiq_set_ratio(L["layer"], float(fn(c)))
                 fq.flexiq_mixed_conv_implicit(L["layer"], L["X"], L["stride"], L["pad"], q=True, out_scale=L["so"], bufs={"q": L["outs"][j]})
                 t = fq.debug_last_launch()["tile"]
-                routes["resident input tile" if t >= n_tiled else {-2: "row-streaming", -3: "3x3, resident weights", -6: "weights in registers"}.get(t, "tiled")] += 1
+                routes["resident input tile" if t >= n_tiled else {-2: "row-streaming", -3: "3x3, resident weights", -6: "weights in registers",
+                                                                           -7: "activations chunk by chunk"}.get(t, "tiled")] += 1
             torch.cuda.synchronize()
             rec(wl, "int8 kernels, " + tag, float(fn(0)) if tag == "fixed r" else None, us, ops=ops, GBs=round(byts / us / 1e3, 1),
                 frac_hbm_peak=round(byts / us / 1e3 / HBM_PEAK_GBS, 4), bound="mixed (mfma / hbm per layer)", calls_per_kernel=routes)
@@ -487,12 +488,13 @@ def measure_shapes(torch, fq, workloads, dev, resnet=True):
                 fq.flexiq_set_ratio(L["chained"], r)
                 fq.flexiq_input_prelowered(L["chained"], L["fed"])
             us = _median_graph_us(torch, lambda: chained_pass(r), 1, repeats=5, settle_s=0.04)
-            routes = {"tiled": 0, "row-streaming": 0, "weights in registers": 0, "3x3, resident weights": 0, "resident input tile": 0}
+            routes = {"tiled": 0, "row-streaming": 0, "weights in registers": 0, "activations chunk by chunk": 0, "3x3, resident weights": 0, "resident input tile": 0}
             for L, j in calls:
                 fq.flexiq_mixed_conv_implicit(L["chained"], L["X"], L["stride"], L["pad"], q=True, out_scale=L["so"], bufs={"q": L["outs"][j]},
                                               lower_for=L["consumer"])
                 t = fq.debug_last_launch()["tile"]
-                routes["resident input tile" if t >= n_tiled else {-2: "row-streaming", -3: "3x3, resident weights", -6: "weights in registers"}.get(t, "tiled")] += 1
+                routes["resident input tile" if t >= n_tiled else {-2: "row-streaming", -3: "3x3, resident weights", -6: "weights in registers",
+                                                                           -7: "activations chunk by chunk"}.get(t, "tiled")] += 1
             torch.cuda.synchronize()
             rec(wl, "int8 kernels, fixed r, bottleneck chains fused: %d of %d calls lower for their consumer, %d read lowered input"
                 % (sum(1 for L, _ in calls if L["consumer"] is not None), len(calls), sum(1 for L, _ in calls if L["fed"])),
