@@ -171,10 +171,10 @@ int flexiq_permute_channels(const flexiq_layer *layer, const int8_t *src, int8_t
  *   scan_for  : optional, not together with lower_for.  The layer that will consume q (same conditions).  The
  *               run-time scan of flexiq_dynamic_positions (Section 4.1; Section 9 "Finding extraction positions at
  *               runtime") is done on q in the same call, by the producing kernel (every block ORs the magnitude bits of the codes it
- *               writes per channel group of the consumer, the block that finishes last leaves the positions) or, where the
- *               product is small, by a kernel behind it: the consumer's run-time positions for its 4-bit groups (its ratio
- *               when this call is made) are left in place and it is switched to them, exactly as
- *               flexiq_dynamic_positions(consumer, q, M) would.  Uses the consumer's scan
+ *               writes per channel group of the consumer, the block that finishes last leaves the positions) or by a kernel
+ *               behind it (which of the two follows from the kernel that serves the product: a call may be one launch or two).
+ *               The consumer's run-time positions for its 4-bit groups (its ratio when this call is made) are left in
+ *               place and it is switched to them, exactly as flexiq_dynamic_positions(consumer, q, M) would.  Uses the consumer's scan
  *               scratch, which the call leaves clean (safe to replay from a captured graph): calls that scan for
  *               the same consumer must not overlap, nor overlap its flexiq_dynamic_positions.  A call with M == 0
  *               launches nothing and leaves the positions as they were.  NULL: no scan
@@ -206,7 +206,8 @@ typedef struct {
  * those of the last flexiq_dynamic_positions scan); the weights of 4-bit groups are read from the handle's cached
  * lowered copies.  Layer must be linear (R = S = 1).  Which kernel serves the call (tiled, row-streaming for at most 256
  * channels, the few-row kernels for at most 64 rows, a tile per block for few tiles, a resident row tile for short calls, weights in
- * registers for 288 to 1280 channels) follows from the shape; the int32 sums are the same bit for bit.
+ * registers for 288 to 1280 channels, activations chunk by chunk for some hundred to some thousand rows of more channels) follows from the
+ * shape; the int32 sums are the same bit for bit.
  * Launches on `stream`; allocates nothing; returns before the kernel has run.  Errors: FLEXIQ_EINVAL (null / inconsistent arguments, M >= 2^31 - 512, more than 159 channel
  * groups, a padded weight matrix of 1 GiB or more, current device is not the handle's), FLEXIQ_EALIGN, FLEXIQ_EHIP. */
 int flexiq_mixed_gemm(const flexiq_layer *layer, const int8_t *X, int64_t M, const flexiq_out *out, void *stream);

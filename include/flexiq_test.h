@@ -28,7 +28,8 @@ int flexiq_debug_force_packed4(int mode);
 int flexiq_debug_max_blocks(int n);
 
 /* What the last GEMM / convolution launch used.  which = 0: tile shape index of the tiled kernel; below 0: another kernel (-2 row-
- * streaming, -3 3x3 with resident weights, -4 few rows, -5 tile per block, -6 weights in registers); from the table's size on: the
+ * streaming, -3 3x3 with resident weights, -4 few rows, -5 tile per block, -6 weights in registers, -7 activations chunk by
+ * chunk); from the table's size on: the
  * kernel of flexiq_debug_force_halo.  1: blocks launched, 2: blocks of that kernel resident per compute unit (0 for the others).
  * 3: 1 if it was a few-row kernel that reads packed codes for the 4-bit weights on the matrix cores, else 0. */
 int flexiq_debug_last_launch(int which);
@@ -42,11 +43,12 @@ int flexiq_debug_last_launch(int which);
  * calls of at most 64 rows are also kept off the kernel of flexiq_debug_force_tile_splitk (so that 0 means "the tiled kernel"). */
 int flexiq_debug_force_few_rows(int mode);
 
-/* The kernel that gives a block one output tile and splits the reduction over its waves (linear calls of more than 64 rows with
+/* The kernel that gives a block one output tile and splits the reduction over its waves (linear calls of more than 32 rows with
  * few tiles and a long reduction; last launch: tile shape index -5): 1 = take it whenever the call qualifies (whatever the
  * tile count and reduction length), 2 / 3 / 4 = the same with tiles of 64 x 64 / 32 x 64 / 32 x 32 (rows x columns), 0 = never,
- * -1 = automatic (more than 32 rows, at most one 64 x 64 tile per compute unit, at least 12 K-steps of 64 channels).  Serves
- * flexiq_mixed_gemm and flexiq_mixed_gemm_fp6 (FP6 build; forced FP6 tile shapes go first; FP6 calls with lower_for at any row
+ * -1 = automatic (more than 32 rows, at most one 64 x 64 tile per compute unit, at least 12 K-steps of 64 channels; calls that read
+ * packed codes from 17 rows, calls that write them from int8 activations at any row count, both from 6 K-steps on).  Serves
+ * flexiq_mixed_gemm, flexiq_mixed_gemm_packed4 and flexiq_mixed_gemm_fp6 (FP6 build; forced FP6 tile shapes go first; FP6 calls with lower_for at any row
  * count), from 17 rows when forced.
  * Returns the tile the last call it was offered ran on (1 / 2 / 3 in that order; 0: another kernel). */
 int flexiq_debug_force_tile_splitk(int mode);

@@ -103,7 +103,7 @@ struct LowerArgs {
     int32_t K4P = 0;
 };
 int lower_for_args(const flexiq_layer *L, const flexiq_out *out, LowerArgs *la);
-// (smallm.hip) linear calls of more than 64 rows with few 64 x 64 tiles and a long reduction: a tile per block, the reduction
+// (smallm.hip) linear calls of more than 32 rows (packed codes: fewer) with few 64 x 64 tiles and a long reduction: a tile per block, the reduction
 // split over its waves; *taken = 0: the call does not qualify
 int launch_tile_splitk(const flexiq_layer *L, const int8_t *X, int64_t M, const flexiq_out *out, void *stream, int num_cu, int *taken,
                        const LowerArgs *lower = nullptr, const uint8_t *X4 = nullptr);   // X4: a producer's packed activation codes

@@ -865,7 +865,9 @@ __global__ __launch_bounds__(64 * NW) void k_tile_splitk(const RowsParams p)
 static int g_force_tile_splitk = -1;   // test hook: 1 = take k_tile_splitk whenever the call qualifies, 0 = never, -1 = automatic
 static int g_last_tile_splitk = 0;
 static bool g_tile_splitk_ready[64] = {};
-constexpr int kTileMinRows = 32;   // up to here the few-row kernels measure faster
+// up to here the few-row kernels measure faster (r = 0 / 1, us there and on a tile per block: 4096 -> 1024 channels, 32 rows 4.4 / 5.9 and 4.9 / 6.3, 33 rows 5.2 / 7.0 and 4.95 / 6.4; 3072 ->
+// 768, 32 rows 4.2 / 5.1 and 4.5 / 5.5, 33 rows 4.8 / 6.1 and 4.55 / 5.6)
+constexpr int kTileMinRows = 32;
 
 static int g_force_cg = 0;      // test hook: column groups per block of k_few_rows_dot (0 = automatic)
 static int g_force_rows = -1;   // test hook: 1 / 2 = take k_few_rows / k_few_rows_dot whenever the call qualifies (3: k_few_rows with packed weight codes), 0 = never, -1 = automatic
@@ -891,8 +893,9 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     if (out->lower_for && !lower) return FLEXIQ_OK;   // (the caller has checked the consumer; null positions: nothing to lower)
     if ((reinterpret_cast<uintptr_t>(X) & 15u) || (L->C & 15)) return FLEXIQ_OK;   // 16-byte activation pieces
     // Every block reads all activation rows: with more than 16 rows that traffic (blocks x M x C bytes through the compute
-    // units' 64 B/clk path) decides, and beyond about one block per compute unit the tiled kernel's 64 x 64 tiles win
-    // (16384 x 4096 weights, 32 / 64 rows: 23 / 38 us here against 18 / 19 us tiled; 4096 x 1024, 64 rows: 4.9 against 6.7 us).
+    // units' 64 B/clk path) decides, and beyond about one block per compute unit the kernels with taller tiles win (r = 0 / 1, us here and in the kernel taken,
+    // kept in cache: 16384 x 4096 weights, 17 rows 14.0 / 16.8 and 13.5 / 13.4, 32 rows 16.0 / 18.4 and 13.9 / 13.9, 64 rows 25.3 / 29.0 and 14.1 / 15.0; 8192 x 2048, 17 rows
+    // 5.2 / 6.8 and 5.3 / 6.0, 32 rows 5.25 / 7.0 and 5.3 / 6.0).
     if (g_force_rows < 0 && M > 16 && (L->N + kRowCols - 1) / kRowCols > num_cu) return FLEXIQ_OK;
     RowsParams p = {};
     p.X = X; p.W8 = L->d_w8; p.W4 = L->d_w4; p.wshift = L->d_wshift;
@@ -909,13 +912,15 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     p.w4x_delta = L->U * 32 * L->Npad;
     if (lower && lower->ashift) { p.next_ashift = lower->ashift; p.next_K4 = lower->K4; p.next_gs_log2 = lower->gs_log2; }
     // packed activation codes of the leading whole K-steps of 4-bit channels (the caller has checked alignment): the dot-product
-    // kernel takes them as they are; the matrix-core kernel has no use for them and leaves such a call to the tiled kernel
+    // kernel takes them as they are; the matrix-core kernel has no use for them and leaves such a call to the tiled kernel (from 17 rows on
+    // k_tile_splitk has been asked before)
     p.X4 = X4 && !L->x_prelowered ? X4 : nullptr;
     p.pieces_p = p.X4 ? (L->max_4bit_ch / 64) * 4 : 0;
     // One or two rows: the dot-product kernel.  Three or four rows: where the layer has columns enough for four column groups per
-    // block and at least half of the channels run at 4 bits (measured on 16384 x 4096 weights at four rows, r = 0 / 0.5 / 1: 14.7 / 13.1 /
-    // 11.6 us against 13.1 / 12.9 / 14.4 us on the matrix-core kernel; from six rows on it is bound by its vector-ALU work, 22 us; at
-    // ViT-L sizes the matrix-core kernel is ahead from three rows on).
+    // block and at least half of the channels run at 4 bits (us here and on the matrix-core kernel with expanded weights, r = 0.5 / 1, from HBM: 16384 x 4096 weights, three rows
+    // 14.8 / 11.9 and 15.6 / 15.8, four 15.6 / 12.9 and 16.1 / 16.2; 8192 x 8192, four rows 16.3 / 15.1 and 15.4 / 16.8; from six rows on it is bound by its vector-ALU work, 22
+    // us; at ViT-L sizes the matrix-core kernel is ahead from three rows on).  The line is older than the loads of whole rows there: with packed weight codes that
+    // kernel takes 13.9 / 12.6 us on the first of them, and on layers of short rows it is ahead, 16384 x 1024, four rows, 6.3 / 6.4 against 7.7 / 7.0.
     const int ncg = (L->N + kVecCols - 1) / kVecCols;
     const bool wide = ncg >= 4 * num_cu && (ncg + 3) / 4 * 4 * kVecCols <= L->Npad;
     if (g_force_rows == 2 || (g_force_rows < 0 && (M <= 2 || (M <= 4 && wide && 2 * L->max_4bit_ch >= L->C)))) {
@@ -951,10 +956,10 @@ int launch_few_rows(const flexiq_layer *L, const int8_t *X, int64_t M, const fle
     const int nw = (int)blocks >= 2 * num_cu ? 4 : (p.steps >= 12 ? 16 : (p.steps >= 6 ? 8 : 4));
     size_t lds = (size_t)nw * mf * 64 * 16;
     // Packed codes where the weight bytes decide: up to eight rows from 40 MiB of 8-bit weights on, more from above 41 MiB and half of the channels
-    // at 4 bits on.  Weights from HBM, the expanded copies and the codes, r = 0.5 / 1, when the lines were drawn (operands loaded in another order, about
-    // 1 to 2 us slower on both sides): 8192 x 5120 (40 MiB), 8 rows 12.4 / 13.4 and 12.5 / 12.1, kept in cache 6 to 25 % faster; 8192 x 4096 (32 MiB),
-    // ahead from HBM but not for every shape kept in cache; 4096 x 4096 17 to 30 % slower in cache; 11008 x 4096 (43 MiB), 12 rows 13.0 / 13.6 and 12.6 / 12.5;
-    // 8192 x 5120, 12 rows 11.9 / 12.2 and 12.6 / 12.3.
+    // at 4 bits on.  The expanded copies and the codes, us, r = 0.5 / 1, from HBM and (kept in cache): 8192 x 5120 (40 MiB), 8 rows 12.5 / 13.9 (11.1 / 12.5) and
+    // 12.6 / 10.5 (9.8 / 8.8), 12 rows 11.6 / 12.1 (9.9 / 10.6) and 12.75 / 10.4 (9.85 / 8.7); 11008 x 4096 (43 MiB), 12 rows 12.65 / 13.4 (10.1 / 10.9) and 11.4 / 10.0 (9.5 / 9.4);
+    // 8192 x 4096 (32 MiB), 8 rows 10.6 / 11.7 (7.4 / 8.6) and 10.1 / 8.95 (7.2 / 7.7), 5 rows 10.2 / 10.6 (6.9 / 7.4) and 10.3 / 9.0 (7.2 / 7.7); 4096 x 4096, 8 rows 6.7 / 6.9 (4.5 / 4.8) and
+    // 6.15 / 5.5 (5.0 / 5.15).
     p.s4 = p.units4 / 2;
     const bool p4 = mf == 1 && L->group_size == 64 && p.s4 > 0 && (g_force_rows == 3 || (g_force_rows < 0 && (M <= 8 ? (int64_t)L->N * L->C >= (40 << 20)
                                                                                                                      : (int64_t)L->N * L->C > (41 << 20) && 2 * L->max_4bit_ch >= L->C)));
