@@ -69,7 +69,7 @@ __device__ __forceinline__ uint32_t expand4(uint32_t hi, int s)
 // A wave's K-steps ks, ks + stride, ...: `left` of them, D in flight, each slot loaded again as soon as it is used up.  BEGUN: the first D are on their way.
 // EXACT: D steps have a path of their own, on which the compiler knows how many loads are in flight; behind loads that depend on `left` the first step waits for all
 // of them, and the steps' ways through LDS follow one by one.  r = 0, us with loads in operand order, without that path and with it: 3 x 3520 -> 128 3.25 / 3.53 /
-// 3.48, 4 x 864 -> 10912 3.26 / 3.6 / 3.46, 4 x 3936 -> 480 3.5 / 3.75 / 3.6.  (Where registers are short it costs more: FP6 builds of few rows up to 1.07 times slower with
+// 3.48, 4 x 864 -> 10912 3.26 / 3.6 / 3.46, 4 x 3936 -> 480 3.5 / 3.75 / 3.6.  (Elsewhere it costs more: FP6 builds of few rows up to 1.07 times slower with
 // it, those of a tile per block spill.  Tried: one step's way through LDS ahead of the multiplication: no gain; loads masked to the rows there are: few rows 1.01, tiles of FP6 calls
 // of few rows 0.95, of others 1.01.)
 template <int D, bool BEGUN, bool EXACT, class Load, class Use>
@@ -336,11 +336,16 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
         for (int i = 0; i < 4; ++i) acc[0][i] += t[i] >> ((down >> (8 * i)) & 31u);
     };
     auto count = [&](int first, int end) { return first < end ? (end - first + nw - 1) / nw : 0; };
+    int left4 = 0;
     if constexpr (P4) {
-        wave_steps<U4, false, true>(load4, use4, wave, count(wave, p.s4), nw);
+        left4 = count(wave, p.s4);
+#pragma unroll
+        for (int k = 0; k < U4; ++k)
+            if (k < left4) load4(k, wave + k * nw);
         ks0 = p.s4 + (wave + nw - p.s4 % nw) % nw;   // (the deal goes on with the other K-steps)
     }
     const int left8 = count(ks0, p.steps);
+    if constexpr (P4) wave_steps<U4, true, false>(load4, use4, wave, left4, nw);
     if constexpr (COOP) {
 #pragma unroll
         for (int k = 0; k < UN; ++k)
@@ -358,7 +363,7 @@ __global__ __launch_bounds__(1024) void k_few_rows(const RowsParams p)
         }
         __syncthreads();
     }
-    wave_steps<UN, COOP, !FP6>(load8, use8, ks0, left8, nw);
+    wave_steps<UN, COOP, !FP6 && !P4>(load8, use8, ks0, left8, nw);
 
     // ---- the waves' sums meet in LDS
 #pragma unroll
@@ -1046,7 +1051,8 @@ static int launch_tile_any(const flexiq_layer *L, const int8_t *X, const uint8_t
     // Calls that read or write packed codes have the tiled kernel alone else, whose few blocks each walk the reduction with a barrier per K-step: they
     // come here from 17 rows on, producers at any row count, and with shorter reductions.  us there and here, r = 0.5 / 1, reading: 100 x 384 -> 1536 5.8 / 6.2
     // and 4.0 / 4.0; 20 x 832 -> 576 8.45 / 7.7 and 4.1 / 4.1; 200 x 3072 -> 768 14.9 / 16.8 and 5.5 / 5.8; 200 x 2880 -> 2784 15.7 / 16.2 and 8.6 / 8.9; writing: 6 x 768 ->
-    // 3072 7.1 / 7.8 and 4.0 / 4.15, 1000 x 1024 -> 1024 8.4 / 9.1 and 6.4 / 7.0.  Beyond one tile per compute unit it is behind: 1000 x 768 -> 3072 10.2 there, 11.7 here.
+    // 3072 7.1 / 7.8 and 4.0 / 4.15, 1000 x 1024 -> 1024 8.4 / 9.1 and 6.4 / 7.0.  Beyond one tile per compute unit it is behind: 1000 x 768 -> 3072 10.2 there, 11.7 here.  (Readers of 3 to 16 rows stay in the
+    // tiled kernel: not measured here.)
     const bool packed = X4 || out->x4;
     if (g_force_tile_splitk == 0 || M < 1 || (M <= 16 && !only_here) || M > 0x7fffffff / 2) return FLEXIQ_OK;
     // (calls of at most 64 rows: the few-row hook, in any forced state, keeps this kernel out of its comparisons)
